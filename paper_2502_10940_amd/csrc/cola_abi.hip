@@ -9,8 +9,7 @@
 //              K4  dX = dZ A
 //              K5  dA partials = dZ^T X             (split over tokens)
 //              K6  dB partials = dY^T H             (split over tokens)
-//                  (bf16 with both outputs wider than 128: K5 and K6 in one
-//                  launch, one split of T for both)
+//                  (bf16: K5 and K6 in one launch, one split of T for both)
 //              K7  dA, dB = fixed-order sums of the partials
 //   dense    : Y = X W^T ; dX = dY W ; dW = dY^T X (split over tokens + K7)
 #include <mutex>
@@ -153,24 +152,27 @@ int check_desc(const cola_desc* d, Dims* out) {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Split of a token-long (K = T) weight-gradient GEMM into chunks of whole K
-// tiles (at least four per chunk).  Depends only on the shape, so results are
-// reproducible run to run.
+// tiles, and the kernel it was planned for.  Depends only on the shape (and
+// the tuning options), so results are reproducible run to run.
 struct Split {
     int splits;
     int64_t k_chunk;
+    int route;
 };
 
-// The split count S minimises a modelled time: rounds(S) * ceil(ktiles / S)
-// K-tile steps of about 2 us each, where rounds(S) = ceil(tiles * S / slots)
-// and slots is the number of workgroups the chip runs at once -- a split that
-// leaves a few workgroups for a second round costs a whole round -- plus
-// writing and re-reading the S fp32 partials at about 4 TB/s.
-// Split of K for `tiles` output tiles (workgroups) on `slots` resident
-// workgroups, whose fp32 partials total `elems` values per split.
-Split plan_split_tiles(bool bf16, int64_t tiles, int64_t slots, int64_t K, double elems) {
-    const int64_t bk = bf16 ? BF16_BK : F32_BK;
+struct WShape {
+    int64_t M, N;
+};
+
+// Split of a kernel without a cost model (fp32, streaming bf16): the split
+// count S minimises rounds(S) * ceil(ktiles / S) K-tile steps of about 2 us
+// each, where rounds(S) = ceil(tiles * S / slots) and slots is the number of
+// workgroups the chip runs at once -- a split that leaves a few workgroups for a
+// second round costs a whole round -- plus writing and re-reading the S fp32
+// partials (`elems` values per split) at about 4 TB/s.
+Split plan_split_tiles(int64_t bk, int64_t tiles, int64_t slots, int64_t K, double elems) {
     const int64_t ktiles = (K + bk - 1) / bk;
-    if (ktiles < 1) return Split{1, bk};                       // empty batch: nothing to split
+    if (ktiles < 1) return Split{1, bk, ROUTE_AUTO};           // empty batch: nothing to split
     const double step_us = 2.0;
     const double partial_us_per_split = elems * 8.0 / 4.0e6;
     int64_t maxs = ktiles / 4;
@@ -194,27 +196,65 @@ Split plan_split_tiles(bool bf16, int64_t tiles, int64_t slots, int64_t K, doubl
     s.k_chunk = chunk_tiles * bk;
     s.splits = (int)((K + s.k_chunk - 1) / s.k_chunk);
     if (s.splits < 1) s.splits = 1;
+    s.route = ROUTE_AUTO;
     return s;
 }
 
-Split plan_split(bool bf16, int64_t M, int64_t N, int64_t K, int tag) {
-    return plan_split_tiles(bf16, gemm_tiles(bf16, M, N, tag), gemm_slots(bf16, M, N, tag), K,
-                            (double)M * (double)N);
+// Route and split of the n weight gradients that share a launch and one split
+// of K = T: the pair that minimises the routes' cost model plus writing and
+// re-reading the partials (about 4 TB/s) and the reduction's launch (4 us).
+// Products with unaligned rows (aligned false) run in the streaming family.
+Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned) {
+    const int64_t ktiles = (K + BF16_BK - 1) / BF16_BK;
+    if (ktiles < 1) return Split{1, BF16_BK, ROUTE_AUTO};
+    double elems = 0.0;
+    for (int i = 0; i < n; ++i) elems += (double)w[i].M * (double)w[i].N;
+    if (!aligned || get_option(OPT_STREAM_ONLY) == 1) {
+        int64_t tiles = 0;
+        for (int i = 0; i < n; ++i) tiles += ((w[i].M + 255) / (w[i].M > 128 ? 256 : 128)) * ((w[i].N + 127) / 128);
+        return plan_split_tiles(BF16_BK, tiles, 512, K, elems);
+    }
+    int64_t maxs = ktiles / 4;
+    if (maxs < 1) maxs = 1;
+    if (maxs > 64) maxs = 64;
+    Split best{1, ktiles * BF16_BK, ROUTE_AUTO};
+    double best_cost = -1.0;
+    for (int route = ROUTE_PP; route <= ROUTE_MID_64x64; ++route) {
+        int64_t tiles = 0;
+        bool fits = true;
+        for (int i = 0; i < n; ++i) {
+            tiles += route_tiles(route, w[i].M, w[i].N);
+            fits = fits && route_fits(route, w[i].M, w[i].N, maxs);
+        }
+        if (!fits) continue;
+        for (int64_t s = 1; s <= maxs; ++s) {
+            const int64_t chunk = (ktiles + s - 1) / s;
+            const int64_t eff_s = (ktiles + chunk - 1) / chunk;
+            const double cost = route_us(route, tiles * eff_s, chunk, true) +
+                                (eff_s > 1 ? 4.0 + (double)eff_s * elems * 8.0 / 4.0e6 : 0.0);
+            if (best_cost < 0 || cost < best_cost) {
+                best_cost = cost;
+                best = Split{(int)eff_s, chunk * BF16_BK, route};
+            }
+        }
+    }
+    return best;
 }
 
-// The two weight gradients of a layer in one launch (bf16, both in the PP
-// family): their tiles share the slots and one split of K = T.  The option
+Split plan_split(bool bf16, int64_t M, int64_t N, int64_t K, bool aligned) {
+    const WShape w{M, N};
+    if (bf16) return plan_split_bf16(&w, 1, K, aligned);
+    return plan_split_tiles(F32_BK, ((M + 63) / 64) * ((N + 63) / 64), 1024, K, (double)M * (double)N);
+}
+
+// The two weight gradients of a layer in one launch (bf16, aligned rows): their
+// tiles share the slots and one split of K = T.  The option
 // COLA_OPT_WGRAD_PAIR = 0 launches them one by one (tuning, comparisons).
-bool wgrad_pairing_on() { return get_option(OPT_WGRAD_PAIR) == 1; }
-bool pair_wgrads(bool bf16, int64_t r, int64_t d_in, int64_t d_out) {
-    return wgrad_pairing_on() && bf16 && gemm_family(r, d_in, TAG_BWD_DA) == FAM_PP &&
-           gemm_family(d_out, r, TAG_BWD_DB) == FAM_PP;
+bool pair_wgrads(bool bf16, bool aligned) {
+    return get_option(OPT_WGRAD_PAIR) == 1 && get_option(OPT_STREAM_ONLY) == 0 && bf16 && aligned;
 }
-Split plan_split_pair(int64_t r, int64_t d_in, int64_t d_out, int64_t T) {
-    const int64_t tiles = gemm_tiles(true, r, d_in, TAG_BWD_DA) + gemm_tiles(true, d_out, r, TAG_BWD_DB);
-    return plan_split_tiles(true, tiles, gemm_slots(true, r, d_in, TAG_BWD_DA), T,
-                            (double)r * (double)d_in + (double)d_out * (double)r);
-}
+// Rows of pitch ld start on 16-byte boundaries (bf16).
+bool pitch16(int64_t ld) { return ld % 8 == 0; }
 
 // Row pitch (elements) of a buffer the library lays out itself: a whole
 // number of 128-byte cache lines, so every K tile of a row starts on a line
@@ -285,12 +325,14 @@ BwdPlan plan_bwd(const Dims& x, bool recompute) {
     BwdPlan p;
     p.ldw = line_pitch(x.bf16, x.r);
     const size_t zbytes = align256((size_t)x.T * (size_t)p.ldw * x.esize);
-    p.pair = pair_wgrads(x.bf16, x.r, x.d_in, x.d_out);
+    const bool al_a = pitch16(x.ldx), al_b = pitch16(x.ldy) && (recompute || pitch16(x.ldz));
+    p.pair = pair_wgrads(x.bf16, al_a && al_b);
     if (p.pair) {
-        p.sa = p.sb = plan_split_pair(x.r, x.d_in, x.d_out, x.T);
+        const WShape w[2] = {{x.r, x.d_in}, {x.d_out, x.r}};
+        p.sa = p.sb = plan_split_bf16(w, 2, x.T, true);
     } else {
-        p.sa = plan_split(x.bf16, x.r, x.d_in, x.T, TAG_BWD_DA);
-        p.sb = plan_split(x.bf16, x.d_out, x.r, x.T, TAG_BWD_DB);
+        p.sa = plan_split(x.bf16, x.r, x.d_in, x.T, al_a);
+        p.sb = plan_split(x.bf16, x.d_out, x.r, x.T, al_b);
     }
     p.off_dz = 0;
     p.off_h = zbytes;
@@ -336,6 +378,7 @@ int wgrad(bool bf16, int64_t M, int64_t N, int64_t T, const void* P, int64_t ldp
     GemmArgs a = make_args(kc, M, N, T, P, ldp, MNMAJ, Q, ldq, MNMAJ, C, N, EPI_STORE_F32, 0);
     a.splits = sp.splits;
     a.k_chunk = sp.k_chunk;
+    a.route = sp.route;
     if (sp.splits > 1) {
         a.c = partials;
         a.split_stride = M * N;
@@ -353,7 +396,7 @@ int wgrad(bool bf16, int64_t M, int64_t N, int64_t T, const void* P, int64_t ldp
 }
 
 // Both weight gradients of a layer, C0[M0][N0] = sum_t P0[t][m] Q0[t][n] and
-// C1 likewise, in one launch with one split of K = T (bf16 PP family), then
+// C1 likewise, in one launch with one split of K = T (bf16), then
 // the fixed-order reductions of their partials.
 int wgrad_pair(int64_t T, const Split& sp, int64_t M0, int64_t N0, const void* P0, int64_t ldp0, const void* Q0,
                int64_t ldq0, float* C0, float* part0, int64_t M1, int64_t N1, const void* P1, int64_t ldp1,
@@ -363,6 +406,7 @@ int wgrad_pair(int64_t T, const Split& sp, int64_t M0, int64_t N0, const void* P
     for (GemmArgs* a : {&a0, &a1}) {
         a->splits = sp.splits;
         a->k_chunk = sp.k_chunk;
+        a->route = sp.route;
     }
     if (sp.splits > 1) {
         a0.c = part0;
@@ -497,7 +541,7 @@ int layer_backward(const Dims& x, int act, bool recompute, const void* dY, int64
         kg.ldzin2 = gate->ld;
         kg.aux = gate->out2;
         kg.ldaux = gate->ld;
-        *gate->fused = x.bf16 && gate_fusion_on() && pp_takes(kg);
+        *gate->fused = x.bf16 && gate_fusion_on() && fused_epilogue_takes(kg);
         if (*gate->fused) {
             k4 = kg;
             b4 = es * ((double)x.T * x.r + (double)x.r * x.d_in + 4.0 * x.T * x.d_in);
@@ -587,7 +631,7 @@ hipError_t launch_up_projection(int64_t T, int64_t d_out, int64_t r, const void*
         kg.ldzin = ldy;
         kg.aux = m;
         kg.ldaux = ldy;
-        *fused = gate_fusion_on() && pp_takes(kg);
+        *fused = gate_fusion_on() && fused_epilogue_takes(kg);
         if (*fused) {
             k2 = kg;
             bytes = 2.0 * ((double)T * r + (double)d_out * r + 3.0 * T * d_out);
@@ -811,7 +855,7 @@ struct DensePlan {
 
 static DensePlan plan_dense(const Dims& x, int phase) {
     DensePlan p;
-    p.sp = plan_split(x.bf16, x.d_out, x.d_in, x.T, TAG_DENSE_DW);
+    p.sp = plan_split(x.bf16, x.d_out, x.d_in, x.T, pitch16(x.ldx) && pitch16(x.ldy));
     p.parts = (phase == 1 && p.sp.splits > 1) ? align256((size_t)p.sp.splits * (size_t)(x.d_out * x.d_in) * 4) : 0;
     p.pw = plan_pack(x.bf16, x.d_out, x.d_in, p.parts);
     p.total = p.pw.off + p.pw.bytes;
@@ -983,8 +1027,7 @@ GFwdPlan plan_group_fwd(const GDims& g, bool recompute) {
 
 // The weight gradients of a group are the products w = 0 (dA_all, R x d_in)
 // and w = 1 + p (dB_p, d_out_p x r_p), all over K = T.  They run in pairs
-// (0, 1), (2, 3), ...: one launch with one split for a pair whose members
-// both go to the PP family (bf16, both output dimensions above 128), else one
+// (0, 1), (2, 3), ...: one launch with one split for a pair (bf16), else one
 // launch each.  Workspace: [dZ_all] [H_all (CoLA-M)] [partials of the first
 // member of a pair] [of the second], both reused pair after pair,
 // [repacked A_all] [repacked B_p ...].
@@ -997,17 +1040,14 @@ struct GBwdPlan {
     Pack wa, wb[COLA_GROUP_MAX];
 };
 
-// Shape (M, N) and kernel tag of weight-gradient product w of a group.
-void group_wgrad_shape(const GDims& g, int w, int64_t* M, int64_t* N, int* tag) {
-    if (w == 0) {
-        *M = g.R;
-        *N = g.d_in;
-        *tag = TAG_BWD_DA;
-    } else {
-        *M = g.d_out[w - 1];
-        *N = g.r[w - 1];
-        *tag = TAG_BWD_DB;
-    }
+// Shape of weight-gradient product w of a group.
+WShape group_wgrad_shape(const GDims& g, int w) {
+    return w == 0 ? WShape{g.R, g.d_in} : WShape{g.d_out[w - 1], g.r[w - 1]};
+}
+
+// H_p starts on a 16-byte boundary in every row (columns off[p] .. of H_all).
+bool group_h_aligned(const GDims& g, bool recompute, int p) {
+    return g.off[p] % 8 == 0 && (recompute || pitch16(g.ldz));
 }
 
 GBwdPlan plan_group_bwd(const GDims& g, bool recompute) {
@@ -1020,22 +1060,22 @@ GBwdPlan plan_group_bwd(const GDims& g, bool recompute) {
     p.nw = g.n + 1;
     size_t pb[2] = {0, 0};
     for (int w0 = 0; w0 < p.nw; w0 += 2) {
-        int64_t M[2], N[2];
-        int tag[2];
         const int cnt = w0 + 1 < p.nw ? 2 : 1;
-        for (int k = 0; k < cnt; ++k) group_wgrad_shape(g, w0 + k, &M[k], &N[k], &tag[k]);
-        p.paired[w0] = cnt == 2 && wgrad_pairing_on() && g.bf16 && gemm_family(M[0], N[0], tag[0]) == FAM_PP &&
-                       gemm_family(M[1], N[1], tag[1]) == FAM_PP;
+        WShape w[2];
+        bool al[2] = {true, true};
+        for (int k = 0; k < cnt; ++k) {
+            w[k] = group_wgrad_shape(g, w0 + k);
+            al[k] = w0 + k == 0 ? pitch16(g.ldx) : group_h_aligned(g, recompute, w0 + k - 1) && pitch16(g.ldy[w0 + k - 1]);
+        }
+        p.paired[w0] = cnt == 2 && pair_wgrads(g.bf16, al[0] && al[1]);
         if (p.paired[w0]) {
-            const int64_t tiles = gemm_tiles(true, M[0], N[0], tag[0]) + gemm_tiles(true, M[1], N[1], tag[1]);
-            p.sp[w0] = p.sp[w0 + 1] = plan_split_tiles(true, tiles, gemm_slots(true, M[0], N[0], tag[0]), g.T,
-                                                       (double)M[0] * N[0] + (double)M[1] * N[1]);
+            p.sp[w0] = p.sp[w0 + 1] = plan_split_bf16(w, 2, g.T, true);
         } else {
-            for (int k = 0; k < cnt; ++k) p.sp[w0 + k] = plan_split(g.bf16, M[k], N[k], g.T, tag[k]);
+            for (int k = 0; k < cnt; ++k) p.sp[w0 + k] = plan_split(g.bf16, w[k].M, w[k].N, g.T, al[k]);
         }
         for (int k = 0; k < cnt; ++k) {
             const Split& sp = p.sp[w0 + k];
-            const size_t b = sp.splits > 1 ? align256((size_t)sp.splits * (size_t)(M[k] * N[k]) * 4) : 0;
+            const size_t b = sp.splits > 1 ? align256((size_t)sp.splits * (size_t)(w[k].M * w[k].N) * 4) : 0;
             if (b > pb[k]) pb[k] = b;
         }
     }
@@ -1116,7 +1156,7 @@ int group_forward(const GDims& g, int act, const void* X, const void* A_all, con
             kg.ldzin = gate->ld;
             kg.aux = gate->out;
             kg.ldaux = gate->ld;
-            *gate->fused = g.bf16 && gate_fusion_on() && g.ldy[q] == gate->ld && pp_takes(kg);
+            *gate->fused = g.bf16 && gate_fusion_on() && g.ldy[q] == gate->ld && fused_epilogue_takes(kg);
             if (*gate->fused) {
                 k2 = kg;
                 if (!gate->keep_u) k2.c = nullptr;

@@ -1,15 +1,17 @@
-// gemm_dispatch.hip -- which bf16 MFMA kernel family runs each GEMM
+// gemm_dispatch.hip -- which bf16 MFMA kernel runs each GEMM
 // C[M][N] = sum_k P(m, k) Q(n, k) of the layer, and the library's tuning
 // options.
 //
-//  * PP (gemm_pp.hip): 256 x 256 tiles, two wave groups in ping-pong, for
-//    every product whose output exceeds one 128-wide tile in both dimensions
-//    (weight gradients: at least 128 in both) and whose operands have
-//    16-byte aligned rows (measured on MI355X:
-//    1.1-1.5x the streaming family on the products of the layer, weight
-//    gradients included).
-//  * STREAM (gemm_stream.hip): BM x 128 tiles, two workgroups per CU, for
-//    skinny outputs, unaligned operands and K tails of any shape.
+//  * PP (gemm_pp.hip): 256 x 256 tiles, two wave groups in ping-pong: the
+//    least traffic and time per flop once its tiles fill the 256 CUs.
+//  * MID (gemm_mid.hip): 128 x 128, 128 x 64 or 64 x 64 tiles, for outputs
+//    that would leave most CUs without a 256 x 256 tile (token batches of a few
+//    thousand, products of width r).
+//  * STREAM (gemm_stream.hip): BM x 128 tiles; operands without 16-byte aligned
+//    rows.
+// PP and MID need 16-byte aligned rows.  Both sum over k in increasing order
+// (as STREAM does with unaligned operands), so the choice never changes a bit
+// of an unsplit product's result.
 #include <atomic>
 
 #include "internal.hpp"
@@ -21,6 +23,32 @@ namespace {
 std::atomic<int> g_force_stream{0};
 std::atomic<int> g_wgrad_pair{1};
 std::atomic<int> g_fuse_gate{1};
+
+// Tile and modelled cost of a route.  A round of up to 256 tiles costs
+// steps * (step + load * x) + store * x microseconds, x the share of the CUs
+// with a tile (all CUs busy share L2 and HBM), after `fixed` for the launch, the
+// first loads and the last stores.  Fitted to MI355X timings of the products of
+// the LLaMA shapes (60M to 7B) at 256 to 65536 tokens; the model is within
+// about 15 % of them.  E.g. T = 1024, K1 of a 1B projection (N = 512, K = 2048):
+// 256 x 256 tiles 42 us (8 of them), 128 x 128 17, 128 x 64 13, 64 x 64 10;
+// T = 4096 at 7B (N = 1024, K = 4096): 75, 36, 45, 55; T = 16384: 108, 138,
+// 164, 210.  Weight gradients of one launch (r = 512, 2048 x 2048): at
+// T = 1024 28, 12, 11, 12 us; at T = 32768, with the best split each and the
+// reduction, 164, 181, 233, 353.
+struct RouteCost {
+    int bm, bn;
+    double fixed, step, load, store;
+    double wstep, wload;                // step and load with both operands m-contiguous (weight gradients)
+};
+constexpr RouteCost kCost[] = {
+    {0, 0, 0, 0, 0, 0, 0, 0},                            // AUTO
+    {256, 128, 0, 0, 0, 0, 0, 0},                        // STREAM (not modelled)
+    {256, 256, 7.0, 1.09, 0.42, 5.0, 1.20, 0.55},        // PP
+    {128, 128, 5.0, 0.36, 0.15, 4.0, 0.36, 0.26},        // MID
+    {128, 64, 5.0, 0.26, 0.06, 1.0, 0.26, 0.12},
+    {64, 64, 5.0, 0.15, 0.06, 0.7, 0.15, 0.15},
+};
+constexpr int kRoutes[] = {ROUTE_PP, ROUTE_MID_128x128, ROUTE_MID_128x64, ROUTE_MID_64x64};
 }  // namespace
 
 int set_option(int option, int value) {
@@ -42,37 +70,119 @@ int get_option(int option) {
     }
 }
 
-// The PP family takes only operands with 16-byte aligned rows whose tile
-// offsets fit its 32-bit per-lane offsets.
-bool pp_operands_ok(const GemmArgs& a) {
+int64_t route_tiles(int route, int64_t M, int64_t N) {
+    const RouteCost& c = kCost[route];
+    return ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+}
+
+double route_us(int route, int64_t tiles, int64_t steps, bool wgrad) {
+    const RouteCost& c = kCost[route];
+    const double rounds = (double)((tiles + 255) / 256);
+    const double x = tiles < 256 ? (double)tiles / 256.0 : 1.0;
+    return c.fixed + rounds * ((double)steps * (wgrad ? c.wstep + c.wload * x : c.step + c.load * x) + c.store * x);
+}
+
+bool route_fits(int route, int64_t M, int64_t N, int64_t splits) {
+    if (route == ROUTE_PP) return M >= 128 && N >= 128;
+    return route_tiles(route, M, N) * splits < kMidMaxBlocks;
+}
+
+int gemm_route(int64_t M, int64_t N, int64_t K) {
+    if (g_force_stream.load(std::memory_order_relaxed)) return ROUTE_STREAM;
+    const int64_t steps = (K + BF16_BK - 1) / BF16_BK;
+    int best = ROUTE_STREAM;
+    double best_us = -1.0;
+    for (int r : kRoutes) {
+        if (!route_fits(r, M, N, 1)) continue;
+        const double us = route_us(r, route_tiles(r, M, N), steps, false);
+        if (best_us < 0 || us < best_us) {
+            best_us = us;
+            best = r;
+        }
+    }
+    return best;
+}
+
+// PP and MID take only operands with 16-byte aligned rows whose tile offsets
+// fit their 32-bit per-lane offsets.
+static bool operands_ok(const GemmArgs& a) {
     auto al = [](const void* p, int64_t ld) {
         return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld & 7) == 0 && ld < (int64_t(1) << 22);
     };
     return al(a.p, a.ldp) && al(a.q, a.ldq);
 }
 
-int gemm_family(int64_t M, int64_t N, int tag) {
-    if (g_force_stream.load(std::memory_order_relaxed)) return FAM_STREAM;
-    // weight gradients take PP down to 128 x 128 outputs: half-empty 256-row
-    // tiles, but the pair of dA and dB in one launch over the whole chip
-    // (measured on MI355X at rank 128: the 60M-shaped step 1.479 -> 1.394 ms)
-    if ((tag == TAG_BWD_DA || tag == TAG_BWD_DB) && M >= 128 && N >= 128) return FAM_PP;
-    return bf16_wide_ok(M, N) ? (int)FAM_PP : (int)FAM_STREAM;
+static int route_of(const GemmArgs& a) {
+    if (!operands_ok(a)) return ROUTE_STREAM;
+    return a.route != ROUTE_AUTO ? a.route : gemm_route(a.M, a.N, a.K);
 }
 
-bool pp_takes(const GemmArgs& a) { return gemm_family(a.M, a.N, a.tag) == FAM_PP && pp_operands_ok(a); }
+static hipError_t launch_route(const GemmArgs* a, int n, int route, hipStream_t s) {
+    if (route >= ROUTE_MID_128x128) {
+        for (int i = 0; i < n; i += kMidBatch) {
+            const int m = n - i < kMidBatch ? n - i : kMidBatch;
+            const hipError_t e = launch_gemm_mid(a + i, m, route - ROUTE_MID_128x128, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    for (int i = 0; i < n; ++i) {
+        const hipError_t e = route == ROUTE_PP ? launch_gemm_pp(a[i], s) : launch_gemm_stream(a[i], s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+bool fused_epilogue_takes(const GemmArgs& a) { return route_of(a) != ROUTE_STREAM; }
 
 hipError_t launch_gemm_bf16_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
-    const bool pp = gemm_family(a0.M, a0.N, a0.tag) == FAM_PP && gemm_family(a1.M, a1.N, a1.tag) == FAM_PP &&
-                    pp_operands_ok(a0) && pp_operands_ok(a1);
-    if (pp) return launch_gemm_pp_pair(a0, a1, s);
-    hipError_t e = launch_gemm_bf16(a0, s);
-    return e == hipSuccess ? launch_gemm_bf16(a1, s) : e;
+    const int r0 = route_of(a0), r1 = route_of(a1);
+    if (r0 == r1 && r0 == ROUTE_PP) return launch_gemm_pp_pair(a0, a1, s);
+    if (r0 == r1 && r0 != ROUTE_STREAM) {
+        const GemmArgs both[2] = {a0, a1};
+        return launch_route(both, 2, r0, s);
+    }
+    const hipError_t e = launch_route(&a0, 1, r0, s);
+    return e == hipSuccess ? launch_route(&a1, 1, r1, s) : e;
 }
 
-hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
-    if (gemm_family(a.M, a.N, a.tag) == FAM_PP && pp_operands_ok(a)) return launch_gemm_pp(a, s);
-    return launch_gemm_stream(a, s);
+hipError_t launch_gemm_bf16_batch(const GemmArgs* a, int n, hipStream_t s) {
+    // The tiles of all n products together decide the route: they run at once.
+    int64_t K = 0;
+    bool ok = n > 1;
+    for (int i = 0; i < n && ok; ++i) {
+        ok = operands_ok(a[i]) && a[i].splits == 1 && !g_force_stream.load(std::memory_order_relaxed);
+        K = a[i].K > K ? a[i].K : K;
+    }
+    if (ok) {
+        const int64_t steps = (K + BF16_BK - 1) / BF16_BK;
+        int best = ROUTE_STREAM;
+        double best_us = -1.0;
+        for (int r : kRoutes) {
+            double us = 0.0;
+            int64_t tiles = 0;
+            bool fits = true;
+            for (int i = 0; i < n; ++i) {
+                tiles += route_tiles(r, a[i].M, a[i].N);
+                us += route_us(r, route_tiles(r, a[i].M, a[i].N), steps, false);    // PP: one launch each
+                fits = fits && route_fits(r, a[i].M, a[i].N, n);
+            }
+            if (!fits) continue;
+            if (r != ROUTE_PP) us = route_us(r, tiles, steps, false);
+            if (best_us < 0 || us < best_us) {
+                best_us = us;
+                best = r;
+            }
+        }
+        return launch_route(a, n, best, s);
+    }
+    for (int i = 0; i < n; ++i) {
+        const hipError_t e = launch_gemm_bf16(a[i], s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
+
+hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) { return launch_route(&a, 1, route_of(a), s); }
 
 }  // namespace cola

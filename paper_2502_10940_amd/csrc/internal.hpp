@@ -48,10 +48,14 @@ struct GemmArgs {
     int splits;                                  // split-K count (>= 1)
     int64_t k_chunk;                             // K range per split (multiple of the K tile)
     int64_t split_stride;                        // elements between partial slices of c
+    int route;                                   // Route: ROUTE_AUTO, or the one a weight-gradient split was planned for
 };
 
 // Enqueue one GEMM.  Return hipSuccess or the launch error.
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
+// n products of one kind (same tag, all unsplit): the ones routed alike to MID
+// tiles share launches.
+hipError_t launch_gemm_bf16_batch(const GemmArgs* a, int n, hipStream_t s);
 // The kernel families behind launch_gemm_bf16:
 //   STREAM -- BM x 128 tiles, direct-to-LDS loads, three K stages, two per CU
 //   PP     -- 256 x 256 tiles, two wave groups per workgroup in ping-pong
@@ -60,18 +64,38 @@ hipError_t launch_gemm_pp(const GemmArgs& a, hipStream_t s);
 // Two weight-gradient products (both operands m-contiguous, fp32 output) in
 // one PP grid: a0's tiles and splits, then a1's.  Operands as for PP.
 hipError_t launch_gemm_pp_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s);
-// a0 and a1 in one launch when both go to the PP family with operands it
-// takes (else one launch each, as launch_gemm_bf16).
+// Two weight-gradient products planned for one route: one launch when their
+// operands are aligned (else one launch each, as launch_gemm_bf16).
 hipError_t launch_gemm_bf16_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s);
 
-enum Family : int { FAM_STREAM = 1, FAM_PP = 4 };
-// Family used for a GEMM (also used by the split planner): PP where both
-// output dimensions exceed 128, else STREAM; the option OPT_STREAM_ONLY
-// sends every product to STREAM.
-int gemm_family(int64_t M, int64_t N, int tag);
-// Whether the PP family runs this GEMM (family and operand alignment): the
-// gated epilogues exist only there.
-bool pp_takes(const GemmArgs& a);
+//   MID -- 128 x 128, 128 x 64 or 64 x 64 tiles, for outputs too small for PP
+// n products of one kind (same layouts and epilogue) in one launch.
+enum MidTile : int { MID_128x128 = 0, MID_128x64 = 1, MID_64x64 = 2 };
+constexpr int kMidBatch = 4;
+constexpr int64_t kMidMaxBlocks = int64_t(1) << 20;
+hipError_t launch_gemm_mid(const GemmArgs* a, int n, int tile, hipStream_t s);
+
+// Kernel and tile of a bf16 product.
+enum Route : int {
+    ROUTE_AUTO = 0,        // GemmArgs: let the launcher choose
+    ROUTE_STREAM, ROUTE_PP, ROUTE_MID_128x128, ROUTE_MID_128x64, ROUTE_MID_64x64
+};
+// Route of an unsplit product with aligned operands: the fastest by the cost
+// model of gemm_dispatch.hip; the option OPT_STREAM_ONLY sends every product
+// to STREAM.
+int gemm_route(int64_t M, int64_t N, int64_t K);
+// Modelled microseconds of `tiles` output tiles (splits included) of `steps`
+// 64-deep K tiles each on a PP or MID route; wgrad: both operands m-contiguous.
+double route_us(int route, int64_t tiles, int64_t steps, bool wgrad);
+// Whether a PP or MID route takes an M x N product in `splits` splits: PP at
+// least 128 x 128 (half a tile), MID fewer than kMidMaxBlocks tiles (its block
+// arithmetic).
+bool route_fits(int route, int64_t M, int64_t N, int64_t splits);
+// Output tiles of an M x N product on a PP or MID route.
+int64_t route_tiles(int route, int64_t M, int64_t N);
+// Whether a PP or MID kernel (not STREAM) runs this GEMM: the gated epilogues
+// exist only there.
+bool fused_epilogue_takes(const GemmArgs& a);
 
 // Process-wide tuning options (the public cola_set_option): the values of
 // cola_option in include/cola.h.  set_option returns 0, or -1 for an unknown
@@ -112,21 +136,5 @@ constexpr int64_t kMaxPitch = int64_t(1) << 22;
 constexpr int BF16_BK = 64;
 // K tile of the fp32 kernel.
 constexpr int F32_BK = 16;
-
-// Tile geometry of the launchers (mirrored here for planning): the PP family
-// uses 256 x 256 (only when M > 128 and N > 128), STREAM BM x 128 with
-// BM = 256 (128 when M <= 128); fp32 uses 64 x 64.
-inline bool bf16_wide_ok(int64_t M, int64_t N) { return M > 128 && N > 128; }
-inline int64_t gemm_tiles(bool bf16, int64_t M, int64_t N, int tag) {
-    const bool wide = bf16 && gemm_family(M, N, tag) == FAM_PP;
-    const int64_t tm = bf16 ? (M > 128 ? 256 : 128) : 64;
-    const int64_t tn = bf16 ? (wide ? 256 : 128) : 64;
-    return ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
-}
-// Workgroups the chip holds at once (256 CUs).
-inline int64_t gemm_slots(bool bf16, int64_t M, int64_t N, int tag) {
-    if (!bf16) return 1024;
-    return gemm_family(M, N, tag) == FAM_PP ? 256 : 512;
-}
 
 }  // namespace cola

@@ -29,8 +29,9 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 
 // Buffer descriptor of a wave-uniform base address (raw buffer, no range
 // check: every offset the kernel uses is in bounds by construction).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const char* ubase) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(ubase), (short)0, 0x7fffffff, 0x00020000);
+// With range 0 every load is out of range: no memory access, zeros.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const char* ubase, int range = 0x7fffffff) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(ubase), (short)0, range, 0x00020000);
 }
 // 16 bytes per lane from base + voff (scalar descriptor, 32-bit per-lane
 // offset: buffer_load_dwordx4 ... lds) to LDS bytes [lds + 16 lane, +16).
@@ -43,7 +44,9 @@ __device__ __forceinline__ void dtl16s(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)lds, 16, voff, soff, 0, 0);
 }
 
+// Eight bf16 at p (16-byte aligned), zeros from `valid` on.
 __device__ __forceinline__ uint4 load8_guarded(const uint16_t* p, int valid) {
+    if (valid >= 8) return *reinterpret_cast<const uint4*>(p);
     uint32_t w[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
