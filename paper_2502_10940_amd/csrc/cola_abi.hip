@@ -9,7 +9,7 @@
 //              K4  dX = dZ A
 //              K5  dA partials = dZ^T X             (split over tokens)
 //              K6  dB partials = dY^T H             (split over tokens)
-//                  (bf16: K5 and K6 in one launch, one split of T for both)
+//                  (K5 and K6 in one launch, one split of T for both)
 //              K7  dA, dB = fixed-order sums of the partials
 //   dense    : Y = X W^T ; dX = dY W ; dW = dY^T X (split over tokens + K7)
 #include <mutex>
@@ -164,8 +164,7 @@ struct WShape {
     int64_t M, N;
 };
 
-// Split of a kernel without a cost model (fp32, streaming bf16): the split
-// count S minimises rounds(S) * ceil(ktiles / S) K-tile steps of about 2 us
+// Split of the streaming family: the split count S minimises rounds(S) * ceil(ktiles / S) K-tile steps of about 2 us
 // each, where rounds(S) = ceil(tiles * S / slots) and slots is the number of
 // workgroups the chip runs at once -- a split that leaves a few workgroups for a
 // second round costs a whole round -- plus writing and re-reading the S fp32
@@ -241,17 +240,43 @@ Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned) {
     return best;
 }
 
-Split plan_split(bool bf16, int64_t M, int64_t N, int64_t K, bool aligned) {
-    const WShape w{M, N};
-    if (bf16) return plan_split_bf16(&w, 1, K, aligned);
-    return plan_split_tiles(F32_BK, ((M + 63) / 64) * ((N + 63) / 64), 1024, K, (double)M * (double)N);
+// Split of the fp32 weight gradients that share a launch: a workgroup of 32 x 32
+// tiles takes four K tiles at once in about 0.6 us (two such workgroups a CU
+// before a round costs more), against the reduction's launch (4 us) and partials
+// at about 4 TB/s.
+Split plan_split_f32(const WShape* w, int n, int64_t K) {
+    const int64_t steps = (K + 4 * F32_BK - 1) / (4 * F32_BK);
+    if (steps < 1) return Split{1, F32_BK, ROUTE_AUTO};
+    double elems = 0.0;
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) {
+        elems += (double)w[i].M * (double)w[i].N;
+        tiles += f32_tiles(32, w[i].M, w[i].N);
+    }
+    Split best{1, steps * 4 * F32_BK, ROUTE_AUTO};
+    double best_cost = -1.0;
+    for (int64_t s = 1; s <= (steps < 64 ? steps : 64); ++s) {
+        const int64_t chunk = (steps + s - 1) / s;
+        const int64_t eff_s = (steps + chunk - 1) / chunk;
+        const double rounds = (double)((tiles * eff_s + 511) / 512);
+        const double cost = rounds * (double)chunk * 0.6 + (eff_s > 1 ? 4.0 + (double)eff_s * elems * 8.0 / 4.0e6 : 0.0);
+        if (best_cost < 0 || cost < best_cost) {
+            best_cost = cost;
+            best = Split{(int)eff_s, chunk * 4 * F32_BK, ROUTE_AUTO};
+        }
+    }
+    return best;
 }
 
-// The two weight gradients of a layer in one launch (bf16, aligned rows): their
+Split plan_split(bool bf16, const WShape* w, int n, int64_t K, bool aligned) {
+    return bf16 ? plan_split_bf16(w, n, K, aligned) : plan_split_f32(w, n, K);
+}
+
+// The two weight gradients of a layer in one launch (bf16: aligned rows): their
 // tiles share the slots and one split of K = T.  The option
 // COLA_OPT_WGRAD_PAIR = 0 launches them one by one (tuning, comparisons).
 bool pair_wgrads(bool bf16, bool aligned) {
-    return get_option(OPT_WGRAD_PAIR) == 1 && get_option(OPT_STREAM_ONLY) == 0 && bf16 && aligned;
+    return get_option(OPT_WGRAD_PAIR) == 1 && (!bf16 || (get_option(OPT_STREAM_ONLY) == 0 && aligned));
 }
 // Rows of pitch ld start on 16-byte boundaries (bf16).
 bool pitch16(int64_t ld) { return ld % 8 == 0; }
@@ -327,12 +352,12 @@ BwdPlan plan_bwd(const Dims& x, bool recompute) {
     const size_t zbytes = align256((size_t)x.T * (size_t)p.ldw * x.esize);
     const bool al_a = pitch16(x.ldx), al_b = pitch16(x.ldy) && (recompute || pitch16(x.ldz));
     p.pair = pair_wgrads(x.bf16, al_a && al_b);
+    const WShape w[2] = {{x.r, x.d_in}, {x.d_out, x.r}};
     if (p.pair) {
-        const WShape w[2] = {{x.r, x.d_in}, {x.d_out, x.r}};
-        p.sa = p.sb = plan_split_bf16(w, 2, x.T, true);
+        p.sa = p.sb = plan_split(x.bf16, w, 2, x.T, true);
     } else {
-        p.sa = plan_split(x.bf16, x.r, x.d_in, x.T, al_a);
-        p.sb = plan_split(x.bf16, x.d_out, x.r, x.T, al_b);
+        p.sa = plan_split(x.bf16, w, 1, x.T, al_a);
+        p.sb = plan_split(x.bf16, w + 1, 1, x.T, al_b);
     }
     p.off_dz = 0;
     p.off_h = zbytes;
@@ -350,7 +375,7 @@ BwdPlan plan_bwd(const Dims& x, bool recompute) {
 size_t fwd_ws(const Dims& x, bool recompute) { return plan_fwd(x, recompute).total; }
 
 hipError_t gemm(const GemmArgs& a, bool bf16, hipStream_t s) {
-    return bf16 ? launch_gemm_bf16(a, s) : launch_gemm_f32(a, s);
+    return bf16 ? launch_gemm_bf16(a, s) : launch_gemm_f32_batch(&a, 1, s);
 }
 
 GemmArgs make_args(int tag, int64_t M, int64_t N, int64_t K, const void* p, int64_t ldp, int pl,
@@ -396,9 +421,9 @@ int wgrad(bool bf16, int64_t M, int64_t N, int64_t T, const void* P, int64_t ldp
 }
 
 // Both weight gradients of a layer, C0[M0][N0] = sum_t P0[t][m] Q0[t][n] and
-// C1 likewise, in one launch with one split of K = T (bf16), then
+// C1 likewise, in one launch with one split of K = T, then
 // the fixed-order reductions of their partials.
-int wgrad_pair(int64_t T, const Split& sp, int64_t M0, int64_t N0, const void* P0, int64_t ldp0, const void* Q0,
+int wgrad_pair(bool bf16, int64_t T, const Split& sp, int64_t M0, int64_t N0, const void* P0, int64_t ldp0, const void* Q0,
                int64_t ldq0, float* C0, float* part0, int64_t M1, int64_t N1, const void* P1, int64_t ldp1,
                const void* Q1, int64_t ldq1, float* C1, float* part1, double bytes_in, hipStream_t s) {
     GemmArgs a0 = make_args(TAG_BWD_DA, M0, N0, T, P0, ldp0, MNMAJ, Q0, ldq0, MNMAJ, C0, N0, EPI_STORE_F32, 0);
@@ -417,7 +442,11 @@ int wgrad_pair(int64_t T, const Split& sp, int64_t M0, int64_t N0, const void* P
     const double elems = (double)M0 * (double)N0 + (double)M1 * (double)N1;
     const double out_bytes = elems * 4.0 * (sp.splits > 1 ? sp.splits : 1);
     hipError_t e = timed(COLA_KC_BWD_DADB, gemm_flops(M0, N0, T) + gemm_flops(M1, N1, T), bytes_in + out_bytes, s,
-                         [&] { return launch_gemm_bf16_pair(a0, a1, s); });
+                         [&] {
+                             if (bf16) return launch_gemm_bf16_pair(a0, a1, s);
+                             const GemmArgs both[2] = {a0, a1};
+                             return launch_gemm_f32_batch(both, 2, s);
+                         });
     if (e != hipSuccess) return hip_fail(e, cola_kernel_name(COLA_KC_BWD_DADB));
     if (sp.splits > 1) {
         e = timed(COLA_KC_REDUCE, 0.0, elems * 4.0 * (sp.splits + 1), s, [&] {
@@ -553,7 +582,7 @@ int layer_backward(const Dims& x, int act, bool recompute, const void* dY, int64
     // K5: dA = dZ^T X ; K6: dB = dY^T H  (+ K7 fixed-order reductions);
     // one launch for both when they share the PP family
     if (p.pair)
-        return wgrad_pair(x.T, p.sa, x.r, x.d_in, dZ, p.ldw, X, x.ldx, dA, reinterpret_cast<float*>(w + p.off_pa),
+        return wgrad_pair(x.bf16, x.T, p.sa, x.r, x.d_in, dZ, p.ldw, X, x.ldx, dA, reinterpret_cast<float*>(w + p.off_pa),
                           x.d_out, x.r, dY, ldy, Hbuf, ldh, dB, reinterpret_cast<float*>(w + p.off_pb),
                           es * ((double)x.T * x.r + (double)x.T * x.d_in + (double)x.T * x.d_out +
                                 (double)x.T * x.r),
@@ -855,7 +884,8 @@ struct DensePlan {
 
 static DensePlan plan_dense(const Dims& x, int phase) {
     DensePlan p;
-    p.sp = plan_split(x.bf16, x.d_out, x.d_in, x.T, pitch16(x.ldx) && pitch16(x.ldy));
+    const WShape w{x.d_out, x.d_in};
+    p.sp = plan_split(x.bf16, &w, 1, x.T, pitch16(x.ldx) && pitch16(x.ldy));
     p.parts = (phase == 1 && p.sp.splits > 1) ? align256((size_t)p.sp.splits * (size_t)(x.d_out * x.d_in) * 4) : 0;
     p.pw = plan_pack(x.bf16, x.d_out, x.d_in, p.parts);
     p.total = p.pw.off + p.pw.bytes;
@@ -1027,8 +1057,8 @@ GFwdPlan plan_group_fwd(const GDims& g, bool recompute) {
 
 // The weight gradients of a group are the products w = 0 (dA_all, R x d_in)
 // and w = 1 + p (dB_p, d_out_p x r_p), all over K = T.  They run in pairs
-// (0, 1), (2, 3), ...: one launch with one split for a pair (bf16), else one
-// launch each.  Workspace: [dZ_all] [H_all (CoLA-M)] [partials of the first
+// (0, 1), (2, 3), ...: one launch with one split for a pair, else one launch
+// each.  Workspace: [dZ_all] [H_all (CoLA-M)] [partials of the first
 // member of a pair] [of the second], both reused pair after pair,
 // [repacked A_all] [repacked B_p ...].
 struct GBwdPlan {
@@ -1069,9 +1099,9 @@ GBwdPlan plan_group_bwd(const GDims& g, bool recompute) {
         }
         p.paired[w0] = cnt == 2 && pair_wgrads(g.bf16, al[0] && al[1]);
         if (p.paired[w0]) {
-            p.sp[w0] = p.sp[w0 + 1] = plan_split_bf16(w, 2, g.T, true);
+            p.sp[w0] = p.sp[w0 + 1] = plan_split(g.bf16, w, 2, g.T, true);
         } else {
-            for (int k = 0; k < cnt; ++k) p.sp[w0 + k] = plan_split(g.bf16, w[k].M, w[k].N, g.T, al[k]);
+            for (int k = 0; k < cnt; ++k) p.sp[w0 + k] = plan_split(g.bf16, w + k, 1, g.T, al[k]);
         }
         for (int k = 0; k < cnt; ++k) {
             const Split& sp = p.sp[w0 + k];
@@ -1326,7 +1356,7 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
             const int cnt = w0 + 1 < p.nw ? 2 : 1;
             if (p.paired[w0]) {
                 const Prod &a = pr[w0], &b = pr[w0 + 1];
-                st = wgrad_pair(g.T, p.sp[w0], a.M, a.N, a.P, a.ldp, a.Q, a.ldq, a.C, part[0], b.M, b.N, b.P, b.ldp,
+                st = wgrad_pair(g.bf16, g.T, p.sp[w0], a.M, a.N, a.P, a.ldp, a.Q, a.ldq, a.C, part[0], b.M, b.N, b.P, b.ldp,
                                 b.Q, b.ldq, b.C, part[1], in_bytes(a) + in_bytes(b), s);
                 if (st != COLA_OK) return st;
                 continue;

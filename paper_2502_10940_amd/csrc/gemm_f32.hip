@@ -1,132 +1,281 @@
-// gemm_f32.hip -- fp32 storage path: C[M][N] = sum_k P(m, k) Q(n, k) with
-// true fp32 fused multiply-adds on the vector ALUs (no reduced-precision
-// matrix shortcut), the same operand layouts and epilogues as the bf16 MFMA
-// kernel.  Tiles of 64 x 64 outputs, K tiles of 16, 256 threads each owning a
-// 4 x 4 block; every access is guarded, so any shape and pitch is accepted.
+// gemm_f32.hip -- fp32 storage path: C[M][N] = sum_k P(m, k) Q(n, k) on the
+// fp32 matrix instruction (v_mfma_f32_32x32x2_f32: fp32 products and sums, no
+// reduced-precision shortcut), the same operand layouts and epilogues as the
+// bf16 kernels; any shape, pitch and 4-byte alignment.
+//
+// What bounds it: the products of this path are small (a few hundred to a few
+// thousand rows), so a launch is a chain of latencies on a mostly idle chip;
+// 32-deep K tiles go global -> registers (one tile ahead) -> LDS -> fragments.
+//  * narrow: 32 x 32 output tiles; the four waves of a workgroup take every
+//    fourth K tile each, through LDS of their own (no barriers in the K loop),
+//    and their sums are added in wave order at the end.  Fills the chip from
+//    256 tiles of 32 x 32 on and shortens the K chain fourfold.
+//  * wide: 64 x 64 tiles, each wave a 32 x 32 quarter over all of K, operands
+//    shared through double-buffered LDS: half the traffic per flop.  Used once
+//    256 such tiles (or splits of them) exist.
+// A training step of T = 256, 512 -> 128 -> 512 takes 45 us, now bound by its five
+// launches; a 64 x 64 VALU kernel took 213 (8 workgroups and 50 us for Z alone).
+// LDS: k-contiguous operands as [row][32 k] with rows of 36 floats, m-contiguous
+// ones as [k][rows] with rows of rows + 8 floats: the 16-byte fragment reads of
+// the former and the two 4-byte half-wave rows (4 k apart) of the latter fall
+// into distinct banks.
 #include "internal.hpp"
 #include "device_math.hpp"
 
 namespace cola {
 namespace {
 
-constexpr int TB = 64;
-constexpr int KT = 16;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-template <int LAYOUT>
-__device__ __forceinline__ float load_op(const float* base, int64_t ld, int64_t row, int64_t rows,
-                                         int64_t k, int64_t kend) {
-    if (row >= rows || k >= kend) return 0.0f;
-    return LAYOUT == KMAJ ? base[row * ld + k] : base[k * ld + row];
+constexpr int BK = F32_BK;
+static_assert(BK == 32, "K tile of 8 four-float chunks");
+
+// Operand tile of R rows x 32 k, moved by NT threads (16 bytes each at a time).
+template <int LAYOUT, int R, int NT>
+struct FTile {
+    static constexpr int LD = LAYOUT == KMAJ ? BK + 4 : R + 8;        // floats per LDS row
+    static constexpr int FLOATS = LAYOUT == KMAJ ? R * LD : BK * LD;
+    static constexpr int CPR = LAYOUT == KMAJ ? BK / 4 : R / 4;       // chunks per LDS row
+    static constexpr int NI = R * BK / 4 / NT;
+    f32x4_t v[NI];
+
+    // rows row0 .., k from k0; zeros past the edges
+    __device__ __forceinline__ void load(const float* base, int64_t ld, int64_t row0, int64_t rows, int64_t k0,
+                                         int64_t kend, int t) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int id = t + NT * i;
+            const int a = id / CPR, c = 4 * (id % CPR);
+            // a: row (k-contiguous) or k; c: first k or first row of the chunk
+            const int64_t o = LAYOUT == KMAJ ? row0 + a : k0 + a, olim = LAYOUT == KMAJ ? rows : kend;
+            const int64_t e = LAYOUT == KMAJ ? k0 + c : row0 + c, elim = LAYOUT == KMAJ ? kend : rows;
+            f32x4_t x = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (o < olim) {
+                const float* p = base + o * ld + e;
+                if (e + 4 <= elim) {
+                    __builtin_memcpy(&x, p, 16);                      // 4-byte alignment is enough
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (e + u < elim) x[u] = p[u];
+                }
+            }
+            v[i] = x;
+        }
+    }
+    __device__ __forceinline__ void put(float* lds, int t) const {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int id = t + NT * i;
+            *reinterpret_cast<f32x4_t*>(lds + (id / CPR) * LD + 4 * (id % CPR)) = v[i];
+        }
+    }
+    // the four matrix steps of k group j (k = 8 j + 4 (lane / 32) + 0..3) of rows
+    // r0 .. r0 + 31
+    __device__ static __forceinline__ f32x4_t frag(const float* lds, int r0, int j, int lane) {
+        const int r = r0 + (lane & 31), k = 8 * j + 4 * (lane >> 5);
+        if constexpr (LAYOUT == KMAJ) {
+            return *reinterpret_cast<const f32x4_t*>(lds + r * LD + k);
+        } else {
+            f32x4_t x;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = lds[(k + u) * LD + r];
+            return x;
+        }
+    }
+};
+
+// Epilogue of 4 consecutive columns gn .. gn + 3 of row gm.
+template <int EPI>
+__device__ __forceinline__ void epilogue(const GemmArgs& a, int split, int64_t gm, int64_t gn, f32x4_t x) {
+    if (gm >= a.M || gn >= a.N) return;
+    const int n = (int)(a.N - gn < 4 ? a.N - gn : 4);
+    auto store = [n](float* p, f32x4_t y) {
+        if (n == 4) {
+            __builtin_memcpy(p, &y, 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (e < n) p[e] = y[e];
+        }
+    };
+    float* c = reinterpret_cast<float*>(a.c) + (int64_t)split * a.split_stride + gm * a.ldc + gn;
+    float* h = a.aux ? reinterpret_cast<float*>(a.aux) + gm * a.ldaux + gn : nullptr;
+    f32x4_t y = x, s = x;
+    if constexpr (EPI == EPI_Z_H || EPI == EPI_H) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = act_sigma<false>(a.act, x[e]);
+        if (EPI == EPI_H) y = s;
+    } else if constexpr (EPI == EPI_DZ) {
+        const float* zp = reinterpret_cast<const float*>(a.zin) + gm * a.ldzin + gn;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float z = e < n ? zp[e] : 0.0f;
+            y[e] = x[e] * act_sigma_prime<false>(a.act, z);
+            if (h) s[e] = act_sigma<false>(a.act, z);
+        }
+    }
+    store(c, y);
+    if constexpr (EPI == EPI_Z_H || EPI == EPI_DZ) {
+        if (h) store(h, s);
+    }
 }
 
-template <int PL, int QL, int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-    __shared__ float Ps[KT][TB + 4];
-    __shared__ float Qs[KT][TB + 4];
+struct F32Batch {
+    GemmArgs a[kF32Batch];
+    int64_t first[kF32Batch + 1];
+    int n;
+};
+
+// acc (C^T: lane l holds row l % 32, registers 4 g .. 4 g + 3 the columns
+// 8 g + 4 (l / 32) + 0..3) += the 32 x 32 products of one K tile
+template <class TP, class TQ>
+__device__ __forceinline__ void mfma_tile(f32x16_t& acc, const float* ps, const float* qs, int rp, int rq, int lane) {
+#pragma unroll
+    for (int j = 0; j < BK / 8; ++j) {
+        const f32x4_t p = TP::frag(ps, rp, j, lane), q = TQ::frag(qs, rq, j, lane);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(q[u], p[u], acc, 0, 0, 0);
+    }
+}
+
+template <int PL, int QL, int EPI, bool WIDE>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Batch bt) {
+    constexpr int TB = WIDE ? 64 : 32;
+    constexpr int NT = WIDE ? 256 : 64;                               // threads that share an LDS tile
+    using TP = FTile<PL, TB, NT>;
+    using TQ = FTile<QL, TB, NT>;
+    constexpr int STAGE = TP::FLOATS + TQ::FLOATS;
+    constexpr int RLD = 36;                                           // narrow: the waves' sums, [wave][32][36]
+    constexpr int TILES = (WIDE ? 2 : 4) * STAGE;
+    constexpr int SMEM = TILES > 4 * 32 * RLD ? TILES : 4 * 32 * RLD;
+    __shared__ __attribute__((aligned(16))) float smem[SMEM];
+
+    int64_t b = blockIdx.x;
+    int pi = 0;
+    while (pi + 1 < bt.n && b >= bt.first[pi + 1]) ++pi;
+    const GemmArgs& a = bt.a[pi];
+    b -= bt.first[pi];
     const int64_t tiles_n = (a.N + TB - 1) / TB;
-    const int64_t tiles_m = (a.M + TB - 1) / TB;
-    const int64_t per_split = tiles_m * tiles_n;
-    const int64_t b = blockIdx.x;
-    const int split = (int)(b / per_split);
-    const int64_t rem = b - (int64_t)split * per_split;
-    const int64_t m0 = (rem / tiles_n) * TB;
-    const int64_t n0 = (rem % tiles_n) * TB;
+    const int64_t per_split = tiles_n * ((a.M + TB - 1) / TB);
+    int split = 0;
+    if (a.splits > 1) {
+        split = (int)(b / per_split);
+        b -= (int64_t)split * per_split;
+    }
+    const int64_t tm = b / tiles_n;
+    const int64_t m0 = tm * TB, n0 = (b - tm * tiles_n) * TB;
     const int64_t kbeg = (int64_t)split * a.k_chunk;
     const int64_t kend = min(a.K, kbeg + a.k_chunk);
     const float* P = reinterpret_cast<const float*>(a.p);
     const float* Q = reinterpret_cast<const float*>(a.q);
-    const int tid = threadIdx.x;
-    const int tx = tid & 15;
-    const int ty = tid >> 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
-    float acc[4][4];
+    f32x16_t acc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
-
-    for (int64_t k0 = kbeg; k0 < kend; k0 += KT) {
-        // 64 rows x 16 k per operand = 1024 values, 4 per thread; the index
-        // order follows the contiguous dimension so loads coalesce.
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + 256 * e;
-            int rp, kp, rq, kq;
-            if (PL == KMAJ) { rp = idx >> 4; kp = idx & 15; } else { kp = idx >> 6; rp = idx & 63; }
-            if (QL == KMAJ) { rq = idx >> 4; kq = idx & 15; } else { kq = idx >> 6; rq = idx & 63; }
-            Ps[kp][rp] = load_op<PL>(P, a.ldp, m0 + rp, a.M, k0 + kp, kend);
-            Qs[kq][rq] = load_op<QL>(Q, a.ldq, n0 + rq, a.N, k0 + kq, kend);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < KT; ++kk) {
-            float pv[4], qv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) pv[i] = Ps[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) qv[j] = Qs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(pv[i], qv[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t gm = m0 + ty * 4 + i;
-        if (gm >= a.M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t gn = n0 + tx * 4 + j;
-            if (gn >= a.N) continue;
-            const float v = acc[i][j];
-            if constexpr (EPI == EPI_STORE || EPI == EPI_STORE_F32) {
-                reinterpret_cast<float*>(a.c)[(int64_t)split * a.split_stride + gm * a.ldc + gn] = v;
-            } else if constexpr (EPI == EPI_Z_H) {
-                reinterpret_cast<float*>(a.c)[gm * a.ldc + gn] = v;
-                if (a.aux) reinterpret_cast<float*>(a.aux)[gm * a.ldaux + gn] = act_sigma<false>(a.act, v);
-            } else if constexpr (EPI == EPI_H) {
-                reinterpret_cast<float*>(a.c)[gm * a.ldc + gn] = act_sigma<false>(a.act, v);
-            } else if constexpr (EPI == EPI_DZ) {
-                const float z = reinterpret_cast<const float*>(a.zin)[gm * a.ldzin + gn];
-                reinterpret_cast<float*>(a.c)[gm * a.ldc + gn] = v * act_sigma_prime<false>(a.act, z);
-                if (a.aux) reinterpret_cast<float*>(a.aux)[gm * a.ldaux + gn] = act_sigma<false>(a.act, z);
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    TP tp;
+    TQ tq;
+    if constexpr (WIDE) {
+        const int t = threadIdx.x;
+        tp.load(P, a.ldp, m0, a.M, kbeg, kend, t);
+        tq.load(Q, a.ldq, n0, a.N, kbeg, kend, t);
+        int buf = 0;
+        for (int64_t k0 = kbeg; k0 < kend; k0 += BK, buf ^= 1) {
+            // a wave writes the buffer of two K tiles ago: every wave has left
+            // it, since it passed the barrier of the K tile in between
+            float* s = smem + buf * STAGE;
+            tp.put(s, t);
+            tq.put(s + TP::FLOATS, t);
+            __syncthreads();
+            if (k0 + BK < kend) {
+                tp.load(P, a.ldp, m0, a.M, k0 + BK, kend, t);
+                tq.load(Q, a.ldq, n0, a.N, k0 + BK, kend, t);
             }
+            mfma_tile<TP, TQ>(acc, s, s + TP::FLOATS, 32 * (wave >> 1), 32 * (wave & 1), lane);
         }
+        const int64_t gm = m0 + 32 * (wave >> 1) + (lane & 31);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            epilogue<EPI>(a, split, gm, n0 + 32 * (wave & 1) + 8 * g + 4 * (lane >> 5),
+                          f32x4_t{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]});
+    } else {
+        float* s = smem + wave * STAGE;                               // this wave's own
+        int64_t k0 = kbeg + wave * BK;
+        tp.load(P, a.ldp, m0, a.M, k0, kend, lane);
+        tq.load(Q, a.ldq, n0, a.N, k0, kend, lane);
+        for (; k0 < kend; k0 += 4 * BK) {
+            // one wave's LDS accesses execute in order: no barrier needed
+            tp.put(s, lane);
+            tq.put(s + TP::FLOATS, lane);
+            if (k0 + 4 * BK < kend) {
+                tp.load(P, a.ldp, m0, a.M, k0 + 4 * BK, kend, lane);
+                tq.load(Q, a.ldq, n0, a.N, k0 + 4 * BK, kend, lane);
+            }
+            __builtin_amdgcn_wave_barrier();
+            mfma_tile<TP, TQ>(acc, s, s + TP::FLOATS, 0, 0, lane);
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();                                              // the tiles give way to the sums
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<f32x4_t*>(smem + (32 * wave + (lane & 31)) * RLD + 8 * g + 4 * (lane >> 5)) =
+                f32x4_t{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+        __syncthreads();
+        const int r = threadIdx.x >> 3, c = 4 * (threadIdx.x & 7);
+        f32x4_t x = *reinterpret_cast<const f32x4_t*>(smem + r * RLD + c);
+#pragma unroll
+        for (int w = 1; w < 4; ++w) x += *reinterpret_cast<const f32x4_t*>(smem + (32 * w + r) * RLD + c);
+        epilogue<EPI>(a, split, m0 + r, n0 + c, x);
     }
 }
 
 template <int PL, int QL, int EPI>
-hipError_t launch_t(const GemmArgs& a, hipStream_t s) {
-    const int64_t tiles = ((a.M + TB - 1) / TB) * ((a.N + TB - 1) / TB) * (int64_t)a.splits;
-    if (tiles <= 0) return hipSuccess;
-    if (tiles > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((gemm_f32_kernel<PL, QL, EPI>), dim3((unsigned)tiles), dim3(256), 0, s, a);
+hipError_t launch_t(const GemmArgs* a, int n, hipStream_t s) {
+    int64_t t64 = 0;
+    for (int i = 0; i < n; ++i) {
+        if (a[i].p_layout != PL || a[i].q_layout != QL || a[i].epi != EPI) return hipErrorInvalidValue;
+        t64 += f32_tiles(64, a[i].M, a[i].N) * a[i].splits;
+    }
+    const bool wide = t64 >= 256;
+    F32Batch bt;
+    bt.n = n;
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        bt.a[i] = a[i];
+        bt.first[i] = blocks;
+        blocks += f32_tiles(wide ? 64 : 32, a[i].M, a[i].N) * a[i].splits;
+    }
+    for (int i = n; i <= kF32Batch; ++i) bt.first[i] = blocks;
+    if (blocks <= 0) return hipSuccess;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    if (wide) hipLaunchKernelGGL((gemm_f32_kernel<PL, QL, EPI, true>), dim3((unsigned)blocks), dim3(256), 0, s, bt);
+    else hipLaunchKernelGGL((gemm_f32_kernel<PL, QL, EPI, false>), dim3((unsigned)blocks), dim3(256), 0, s, bt);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
-    const int pl = a.p_layout, ql = a.q_layout;
-    switch (a.epi) {
+hipError_t launch_gemm_f32_batch(const GemmArgs* a, int n, hipStream_t s) {
+    if (n < 1 || n > kF32Batch) return hipErrorInvalidValue;
+    const int pl = a[0].p_layout, ql = a[0].q_layout;
+    switch (a[0].epi) {
         case EPI_Z_H:
-            if (pl == KMAJ && ql == KMAJ) return launch_t<KMAJ, KMAJ, EPI_Z_H>(a, s);
+            if (pl == KMAJ && ql == KMAJ) return launch_t<KMAJ, KMAJ, EPI_Z_H>(a, n, s);
             break;
         case EPI_H:
-            if (pl == KMAJ && ql == KMAJ) return launch_t<KMAJ, KMAJ, EPI_H>(a, s);
+            if (pl == KMAJ && ql == KMAJ) return launch_t<KMAJ, KMAJ, EPI_H>(a, n, s);
             break;
         case EPI_STORE:
-            if (pl == KMAJ && ql == KMAJ) return launch_t<KMAJ, KMAJ, EPI_STORE>(a, s);
-            if (pl == KMAJ && ql == MNMAJ) return launch_t<KMAJ, MNMAJ, EPI_STORE>(a, s);
+            if (pl == KMAJ && ql == KMAJ) return launch_t<KMAJ, KMAJ, EPI_STORE>(a, n, s);
+            if (pl == KMAJ && ql == MNMAJ) return launch_t<KMAJ, MNMAJ, EPI_STORE>(a, n, s);
             break;
         case EPI_DZ:
-            if (pl == KMAJ && ql == MNMAJ) return launch_t<KMAJ, MNMAJ, EPI_DZ>(a, s);
+            if (pl == KMAJ && ql == MNMAJ) return launch_t<KMAJ, MNMAJ, EPI_DZ>(a, n, s);
             break;
         case EPI_STORE_F32:
-            if (pl == MNMAJ && ql == MNMAJ) return launch_t<MNMAJ, MNMAJ, EPI_STORE_F32>(a, s);
+            if (pl == MNMAJ && ql == MNMAJ) return launch_t<MNMAJ, MNMAJ, EPI_STORE_F32>(a, n, s);
             break;
         default:
             break;

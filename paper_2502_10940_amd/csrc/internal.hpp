@@ -104,8 +104,11 @@ enum Option : int { OPT_STREAM_ONLY = 0, OPT_WGRAD_PAIR = 1, OPT_FUSE_GATE = 2 }
 int set_option(int option, int value);
 int get_option(int option);
 
-// fp32 storage: the VALU GEMM of gemm_f32.hip (true fp32 FMAs).
-hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s);
+// fp32 storage: n products of one kind (same layouts and epilogue) in one launch.
+constexpr int kF32Batch = 4;
+hipError_t launch_gemm_f32_batch(const GemmArgs* a, int n, hipStream_t s);
+// tb x tb output tiles of an M x N product.
+inline int64_t f32_tiles(int64_t tb, int64_t M, int64_t N) { return ((M + tb - 1) / tb) * ((N + tb - 1) / tb); }
 
 // out[i] = sum_{s < splits} part[s * stride + i], s in increasing order (fp32).
 hipError_t launch_reduce_splits(const float* part, int splits, int64_t stride,
@@ -135,6 +138,6 @@ constexpr int64_t kMaxPitch = int64_t(1) << 22;
 // K tile of the bf16 kernel: split-K chunks are multiples of it.
 constexpr int BF16_BK = 64;
 // K tile of the fp32 kernel.
-constexpr int F32_BK = 16;
+constexpr int F32_BK = 32;
 
 }  // namespace cola
