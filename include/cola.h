@@ -41,8 +41,10 @@
  * untouched.  No C++ exception crosses this boundary.
  *
  * Alignment.  Base pointers that are 16-byte aligned with ld a multiple of
- * 16 bytes take the vector path; anything else is accepted and takes a
- * per-element path (same results, slower).
+ * 16 bytes are the fastest.  Rows of any other pitch are accepted: bf16 inputs
+ * are copied to aligned rows in the workspace first (cola_workspace_bytes()
+ * includes the room), and element-aligned base pointers take a per-element
+ * path (slower).
  *
  * Determinism.  Results are bitwise reproducible run to run: the T-long
  * weight-gradient sums are split into a fixed number of chunks whose fp32
@@ -80,7 +82,7 @@ typedef enum {
     COLA_ERR_INVALID_ARG = 1,      /* NULL desc/pointer, bad enum, H vs recompute mismatch */
     COLA_ERR_BAD_SHAPE = 2,        /* d_in, d_out or r < 1, T < 0, ld < width, a row pitch above
                                       COLA_MAX_PITCH, size overflow */
-    COLA_ERR_WORKSPACE = 3,        /* ws_bytes below the size cola_workspace_bytes() returns */
+    COLA_ERR_WORKSPACE = 3,        /* ws_bytes below what the call needs (cola_workspace_bytes() is enough) */
     COLA_ERR_HIP = 4,              /* a launch failed; cola_strerror() returns HIP's text */
     COLA_ERR_UNSUPPORTED = 5,      /* combination not compiled in */
     COLA_ERR_SCRATCH = 6           /* cola_bwd_scratch: needs more than COLA_SCRATCH_BYTES */
@@ -144,15 +146,18 @@ int cola_bwd(const cola_desc* desc,
 
 /* Backward for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
- * same computation and results as cola_bwd (bitwise), with its workspace in a
- * static device array of the library instead of a caller buffer.  Nothing is
+ * same computation and results as cola_bwd (bitwise, where that call's workspace
+ * fits the array), with its workspace in a static device array of the library
+ * instead of a caller buffer.  Nothing is
  * allocated or freed by the call; the array (COLA_SCRATCH_BYTES per GPU) is
  * placed when the library's code object is loaded on a GPU and held until the
  * process ends.  Each GPU has its own array, shared by every call on that
  * GPU: calls that overlap on one GPU (concurrent streams, threads or graph
  * replays in flight) race on it and must be ordered by the caller.  A call
- * whose workspace (cola_workspace_bytes(desc, 1)) exceeds COLA_SCRATCH_BYTES
- * returns COLA_ERR_SCRATCH and enqueues nothing.  Arguments, ownership,
+ * whose dZ, H (CoLA-M), repacked weights and weight-gradient partials exceed
+ * COLA_SCRATCH_BYTES returns COLA_ERR_SCRATCH and enqueues nothing; aligned
+ * copies of unaligned token rows and surplus splits are left out where only
+ * they would exceed it.  Arguments, ownership,
  * errors and T = 0 as cola_bwd. */
 #define COLA_SCRATCH_BYTES ((size_t)64 << 20)
 int cola_bwd_scratch(const cola_desc* desc,

@@ -169,14 +169,14 @@ struct WShape {
 // workgroups the chip runs at once -- a split that leaves a few workgroups for a
 // second round costs a whole round -- plus writing and re-reading the S fp32
 // partials (`elems` values per split) at about 4 TB/s.
-Split plan_split_tiles(int64_t bk, int64_t tiles, int64_t slots, int64_t K, double elems) {
+Split plan_split_tiles(int64_t bk, int64_t tiles, int64_t slots, int64_t K, double elems, int64_t cap) {
     const int64_t ktiles = (K + bk - 1) / bk;
     if (ktiles < 1) return Split{1, bk, ROUTE_AUTO};           // empty batch: nothing to split
     const double step_us = 2.0;
     const double partial_us_per_split = elems * 8.0 / 4.0e6;
     int64_t maxs = ktiles / 4;
     if (maxs < 1) maxs = 1;
-    if (maxs > 64) maxs = 64;
+    if (maxs > cap) maxs = cap;
     int64_t best_s = 1;
     double best_cost = -1.0;
     for (int64_t s = 1; s <= maxs; ++s) {
@@ -203,7 +203,7 @@ Split plan_split_tiles(int64_t bk, int64_t tiles, int64_t slots, int64_t K, doub
 // of K = T: the pair that minimises the routes' cost model plus writing and
 // re-reading the partials (about 4 TB/s) and the reduction's launch (4 us).
 // Products with unaligned rows (aligned false) run in the streaming family.
-Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned) {
+Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned, int64_t cap) {
     const int64_t ktiles = (K + BF16_BK - 1) / BF16_BK;
     if (ktiles < 1) return Split{1, BF16_BK, ROUTE_AUTO};
     double elems = 0.0;
@@ -211,11 +211,11 @@ Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned) {
     if (!aligned || get_option(OPT_STREAM_ONLY) == 1) {
         int64_t tiles = 0;
         for (int i = 0; i < n; ++i) tiles += ((w[i].M + 255) / (w[i].M > 128 ? 256 : 128)) * ((w[i].N + 127) / 128);
-        return plan_split_tiles(BF16_BK, tiles, 512, K, elems);
+        return plan_split_tiles(BF16_BK, tiles, 512, K, elems, cap);
     }
     int64_t maxs = ktiles / 4;
     if (maxs < 1) maxs = 1;
-    if (maxs > 64) maxs = 64;
+    if (maxs > cap) maxs = cap;
     Split best{1, ktiles * BF16_BK, ROUTE_AUTO};
     double best_cost = -1.0;
     for (int route = ROUTE_PP; route <= ROUTE_MID_64x64; ++route) {
@@ -244,7 +244,7 @@ Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned) {
 // tiles takes four K tiles at once in about 0.6 us (two such workgroups a CU
 // before a round costs more), against the reduction's launch (4 us) and partials
 // at about 4 TB/s.
-Split plan_split_f32(const WShape* w, int n, int64_t K) {
+Split plan_split_f32(const WShape* w, int n, int64_t K, int64_t cap) {
     const int64_t steps = (K + 4 * F32_BK - 1) / (4 * F32_BK);
     if (steps < 1) return Split{1, F32_BK, ROUTE_AUTO};
     double elems = 0.0;
@@ -255,7 +255,7 @@ Split plan_split_f32(const WShape* w, int n, int64_t K) {
     }
     Split best{1, steps * 4 * F32_BK, ROUTE_AUTO};
     double best_cost = -1.0;
-    for (int64_t s = 1; s <= (steps < 64 ? steps : 64); ++s) {
+    for (int64_t s = 1; s <= (steps < cap ? steps : cap); ++s) {
         const int64_t chunk = (steps + s - 1) / s;
         const int64_t eff_s = (steps + chunk - 1) / chunk;
         const double rounds = (double)((tiles * eff_s + 511) / 512);
@@ -268,8 +268,11 @@ Split plan_split_f32(const WShape* w, int n, int64_t K) {
     return best;
 }
 
-Split plan_split(bool bf16, const WShape* w, int n, int64_t K, bool aligned) {
-    return bf16 ? plan_split_bf16(w, n, K, aligned) : plan_split_f32(w, n, K);
+// At most kMaxSplits splits, or `cap` of them where the workspace is short.
+constexpr int64_t kMaxSplits = 64;
+
+Split plan_split(bool bf16, const WShape* w, int n, int64_t K, bool aligned, int64_t cap = kMaxSplits) {
+    return bf16 ? plan_split_bf16(w, n, K, aligned, cap) : plan_split_f32(w, n, K, cap);
 }
 
 // The two weight gradients of a layer in one launch (bf16: aligned rows): their
@@ -289,51 +292,68 @@ int64_t line_pitch(bool bf16, int64_t width) {
     return (width + per - 1) / per * per;
 }
 
-// A bf16 weight whose rows are not a whole number of 16-byte chunks (width
-// not a multiple of 8) is copied to the workspace with a line-aligned pitch,
-// so the MFMA kernel keeps its vector loads.  Depends only on the shape.
+// A bf16 operand whose rows are not a whole number of 16-byte chunks apart is
+// copied to the workspace with a line-aligned pitch, so that the fast MFMA
+// kernels, whose loads need aligned rows, take the products that read it.
+// Weights (contiguous rows, width not a multiple of 8) and token rows (pitch
+// not a multiple of 8).  One pass over the operand instead of element loads in
+// every product: X A^T of 4095 tight rows of 5461 took 960 us with them, 36 us
+// and a 20 us copy without (MI355X).  Depends only on the shape.
 struct Pack {
     bool on;
-    int64_t ld;     // pitch to use for the weight
+    int64_t rows, width;
+    int64_t ld;     // pitch to use for the operand
     size_t off, bytes;
 };
 
-Pack plan_pack(bool bf16, int64_t rows, int64_t width, size_t off) {
+Pack plan_pack(bool on, int64_t rows, int64_t width, int64_t ld, size_t off) {
     Pack p;
     p.off = off;
-    p.on = bf16 && (width % 8) != 0;
-    p.ld = p.on ? line_pitch(true, width) : width;
+    p.on = on;
+    p.rows = rows;
+    p.width = width;
+    p.ld = p.on ? line_pitch(true, width) : ld;
     p.bytes = p.on ? align256((size_t)rows * (size_t)p.ld * 2) : 0;
     return p;
 }
 
-// Resolve a weight to (pointer, pitch), enqueueing its repack if planned.
-hipError_t use_weight(const Pack& pk, const void* w, int64_t rows, int64_t width, char* ws,
-                      const void** out, int64_t* ld, hipStream_t s) {
+Pack plan_weight(bool bf16, int64_t rows, int64_t width, size_t off) {
+    return plan_pack(bf16 && !pitch16(width), rows, width, width, off);
+}
+
+// Resolve an operand (rows src_ld apart) to a pointer, enqueueing its copy if
+// planned; its pitch is pk.ld.
+hipError_t use_packed(const Pack& pk, const void* src, int64_t src_ld, char* ws, const void** out, hipStream_t s) {
     if (!pk.on) {
-        *out = w;
-        *ld = width;
+        *out = src;
         return hipSuccess;
     }
     *out = ws + pk.off;
-    *ld = pk.ld;
-    return launch_pack_rows(w, rows, width, ws + pk.off, pk.ld, s);
+    return launch_pack_rows(src, src_ld, pk.rows, pk.width, ws + pk.off, pk.ld, s);
 }
 
+// Token rows are copied (copies = true) when the workspace has room for them; a
+// caller that brings only the `lean` size gets the kernels for unaligned rows.
+// cola_workspace_bytes returns the full size.
 struct FwdPlan {
     int64_t ldw;          // pitch of the workspace copy of H (CoLA-M)
     size_t off_h, total;
     Pack pa, pb;          // repacked A [r][d_in] and B [d_out][r]
+    Pack px, ph;          // repacked X and H
 };
 
-FwdPlan plan_fwd(const Dims& x, bool recompute) {
+FwdPlan plan_fwd(const Dims& x, bool recompute, bool copies = true) {
     FwdPlan p;
     p.ldw = line_pitch(x.bf16, x.r);
     p.off_h = 0;
     const size_t hbytes = recompute ? align256((size_t)x.T * (size_t)p.ldw * x.esize) : 0;
-    p.pa = plan_pack(x.bf16, x.r, x.d_in, hbytes);
-    p.pb = plan_pack(x.bf16, x.d_out, x.r, p.pa.off + p.pa.bytes);
-    p.total = p.pb.off + p.pb.bytes;
+    p.pa = plan_weight(x.bf16, x.r, x.d_in, hbytes);
+    p.pb = plan_weight(x.bf16, x.d_out, x.r, p.pa.off + p.pa.bytes);
+    copies = copies && x.bf16;
+    p.px = plan_pack(copies && !pitch16(x.ldx), x.T, x.d_in, x.ldx, p.pb.off + p.pb.bytes);
+    p.ph = plan_pack(copies && !recompute && !pitch16(x.ldz), x.T, x.r, recompute ? p.ldw : x.ldz,
+                     p.px.off + p.px.bytes);
+    p.total = p.ph.off + p.ph.bytes;
     if (x.T == 0) p.total = 0;
     return p;
 }
@@ -344,20 +364,22 @@ struct BwdPlan {
     Split sa, sb;         // the same split for both when pair
     bool pair;            // dA and dB in one launch
     Pack wa, wb;          // repacked A and B
+    Pack px, py, ph;      // repacked X, dY and H
 };
 
-BwdPlan plan_bwd(const Dims& x, bool recompute) {
+BwdPlan plan_bwd(const Dims& x, bool recompute, bool copies = true, int64_t cap = kMaxSplits) {
     BwdPlan p;
     p.ldw = line_pitch(x.bf16, x.r);
     const size_t zbytes = align256((size_t)x.T * (size_t)p.ldw * x.esize);
-    const bool al_a = pitch16(x.ldx), al_b = pitch16(x.ldy) && (recompute || pitch16(x.ldz));
+    copies = copies && x.bf16;
+    const bool al_a = copies || pitch16(x.ldx), al_b = copies || (pitch16(x.ldy) && (recompute || pitch16(x.ldz)));
     p.pair = pair_wgrads(x.bf16, al_a && al_b);
     const WShape w[2] = {{x.r, x.d_in}, {x.d_out, x.r}};
     if (p.pair) {
-        p.sa = p.sb = plan_split(x.bf16, w, 2, x.T, true);
+        p.sa = p.sb = plan_split(x.bf16, w, 2, x.T, true, cap);
     } else {
-        p.sa = plan_split(x.bf16, w, 1, x.T, al_a);
-        p.sb = plan_split(x.bf16, w + 1, 1, x.T, al_b);
+        p.sa = plan_split(x.bf16, w, 1, x.T, al_a, cap);
+        p.sb = plan_split(x.bf16, w + 1, 1, x.T, al_b, cap);
     }
     p.off_dz = 0;
     p.off_h = zbytes;
@@ -365,14 +387,23 @@ BwdPlan plan_bwd(const Dims& x, bool recompute) {
     const size_t pa = p.sa.splits > 1 ? align256((size_t)p.sa.splits * (size_t)(x.r * x.d_in) * 4) : 0;
     p.off_pb = p.off_pa + pa;
     const size_t pb = p.sb.splits > 1 ? align256((size_t)p.sb.splits * (size_t)(x.d_out * x.r) * 4) : 0;
-    p.wa = plan_pack(x.bf16, x.r, x.d_in, p.off_pb + pb);
-    p.wb = plan_pack(x.bf16, x.d_out, x.r, p.wa.off + p.wa.bytes);
-    p.total = p.wb.off + p.wb.bytes;
+    p.wa = plan_weight(x.bf16, x.r, x.d_in, p.off_pb + pb);
+    p.wb = plan_weight(x.bf16, x.d_out, x.r, p.wa.off + p.wa.bytes);
+    p.px = plan_pack(copies && !pitch16(x.ldx), x.T, x.d_in, x.ldx, p.wb.off + p.wb.bytes);
+    p.py = plan_pack(copies && !pitch16(x.ldy), x.T, x.d_out, x.ldy, p.px.off + p.px.bytes);
+    p.ph = plan_pack(copies && !recompute && !pitch16(x.ldz), x.T, x.r, recompute ? p.ldw : x.ldz,
+                     p.py.off + p.py.bytes);
+    p.total = p.ph.off + p.ph.bytes;
     if (x.T == 0) p.total = 0;
     return p;
 }
 
-size_t fwd_ws(const Dims& x, bool recompute) { return plan_fwd(x, recompute).total; }
+// The plan that `ws_bytes` has room for: with copies of unaligned rows, or the
+// lean one (which is refused if that is too large as well).
+template <class Plan>
+Plan fitting(size_t ws_bytes, Plan full, Plan lean) {
+    return ws_bytes >= full.total ? full : lean;
+}
 
 hipError_t gemm(const GemmArgs& a, bool bf16, hipStream_t s) {
     return bf16 ? launch_gemm_bf16(a, s) : launch_gemm_f32_batch(&a, 1, s);
@@ -490,21 +521,20 @@ bool gate_fusion_on() { return get_option(OPT_FUSE_GATE) == 1; }
 
 // Forward of one validated layer with its pointers and workspace checked.
 // outer >= 0: the both-sigma variant (K2 stores P and Y = sigma_out(P)).
-int layer_forward(const Dims& x, int act, bool recompute, const void* X, const void* A, const void* B, void* Y,
-                  void* Z, void* H, int outer, void* P, char* w, hipStream_t s) {
-    const FwdPlan p = plan_fwd(x, recompute);
+int layer_forward(const Dims& x, const FwdPlan& p, int act, bool recompute, const void* X, const void* A,
+                  const void* B, void* Y, void* Z, void* H, int outer, void* P, char* w, hipStream_t s) {
     void* Hbuf = recompute ? (void*)(w + p.off_h) : H;
     const int64_t ldh = recompute ? p.ldw : x.ldz;
     const double es = (double)x.esize;
-    const void* Aw;
-    const void* Bw;
-    int64_t lda, ldb;
-    hipError_t e = use_weight(p.pa, A, x.r, x.d_in, w, &Aw, &lda, s);
-    if (e == hipSuccess) e = use_weight(p.pb, B, x.d_out, x.r, w, &Bw, &ldb, s);
+    const void *Aw, *Bw, *Xw, *Hw;
+    hipError_t e = use_packed(p.pa, A, x.d_in, w, &Aw, s);
+    if (e == hipSuccess) e = use_packed(p.pb, B, x.r, w, &Bw, s);
+    if (e == hipSuccess) e = use_packed(p.px, X, x.ldx, w, &Xw, s);
     if (e != hipSuccess) return hip_fail(e, "pack_rows");
+    const int64_t lda = p.pa.ld, ldb = p.pb.ld;
 
     // K1: Z = X A^T, H = sigma(Z)
-    GemmArgs k1 = make_args(TAG_FWD_Z, x.T, x.r, x.d_in, X, x.ldx, KMAJ, Aw, lda, KMAJ, Z, x.ldz, EPI_Z_H,
+    GemmArgs k1 = make_args(TAG_FWD_Z, x.T, x.r, x.d_in, Xw, p.px.ld, KMAJ, Aw, lda, KMAJ, Z, x.ldz, EPI_Z_H,
                             act);
     k1.aux = Hbuf;
     k1.ldaux = ldh;
@@ -514,10 +544,12 @@ int layer_forward(const Dims& x, int act, bool recompute, const void* X, const v
 
     // K2: Y = H B^T; with an outer sigma (outer >= 0) K2 stores P = H B^T
     // and Y = sigma_out(P)
-    GemmArgs k2 = make_args(TAG_FWD_Y, x.T, x.d_out, x.r, Hbuf, ldh, KMAJ, Bw, ldb, KMAJ, Y, x.ldy, EPI_STORE,
+    e = use_packed(p.ph, Hbuf, ldh, w, &Hw, s);
+    if (e != hipSuccess) return hip_fail(e, "pack_rows");
+    GemmArgs k2 = make_args(TAG_FWD_Y, x.T, x.d_out, x.r, Hw, p.ph.ld, KMAJ, Bw, ldb, KMAJ, Y, x.ldy, EPI_STORE,
                             act);
     if (outer >= 0) {
-        k2 = make_args(TAG_FWD_YP, x.T, x.d_out, x.r, Hbuf, ldh, KMAJ, Bw, ldb, KMAJ, P, x.ldy, EPI_Z_H, outer);
+        k2 = make_args(TAG_FWD_YP, x.T, x.d_out, x.r, Hw, p.ph.ld, KMAJ, Bw, ldb, KMAJ, P, x.ldy, EPI_Z_H, outer);
         k2.aux = Y;
         k2.ldaux = x.ldy;
     }
@@ -529,21 +561,21 @@ int layer_forward(const Dims& x, int act, bool recompute, const void* X, const v
 }
 
 // Backward of one validated layer with a non-empty batch, its pointers and
-// workspace checked; dY has row pitch ldy.
-int layer_backward(const Dims& x, int act, bool recompute, const void* dY, int64_t ldy, const void* X,
+// workspace checked against the plan p.
+int layer_backward(const Dims& x, const BwdPlan& p, int act, bool recompute, const void* dY_in, const void* X_in,
                    const void* Z, const void* H, const void* A, const void* B, void* dX, float* dA, float* dB,
                    char* w, hipStream_t s, const Gate* gate = nullptr) {
-    const BwdPlan p = plan_bwd(x, recompute);
     void* dZ = w + p.off_dz;
-    const void* Hbuf = recompute ? (const void*)(w + p.off_h) : H;
-    const int64_t ldh = recompute ? p.ldw : x.ldz;
     const double es = (double)x.esize;
-    const void* Aw;
-    const void* Bw;
-    int64_t lda, ldb;
-    hipError_t e = use_weight(p.wa, A, x.r, x.d_in, w, &Aw, &lda, s);
-    if (e == hipSuccess) e = use_weight(p.wb, B, x.d_out, x.r, w, &Bw, &ldb, s);
+    const void *Aw, *Bw, *X, *dY, *Hbuf;
+    hipError_t e = use_packed(p.wa, A, x.d_in, w, &Aw, s);
+    if (e == hipSuccess) e = use_packed(p.wb, B, x.r, w, &Bw, s);
+    if (e == hipSuccess) e = use_packed(p.px, X_in, x.ldx, w, &X, s);
+    if (e == hipSuccess) e = use_packed(p.py, dY_in, x.ldy, w, &dY, s);
+    if (e == hipSuccess) e = use_packed(p.ph, recompute ? (const void*)(w + p.off_h) : H, recompute ? p.ldw : x.ldz, w,
+                                        &Hbuf, s);
     if (e != hipSuccess) return hip_fail(e, "pack_rows");
+    const int64_t lda = p.wa.ld, ldb = p.wb.ld, ldx = p.px.ld, ldy = p.py.ld, ldh = p.ph.ld;
 
     // K3: dZ = (dY B) (.) sigma'(Z); CoLA-M regenerates H = sigma(Z) here
     GemmArgs k3 = make_args(TAG_BWD_DZ, x.T, x.r, x.d_out, dY, ldy, KMAJ, Bw, ldb, MNMAJ, dZ, p.ldw, EPI_DZ,
@@ -582,12 +614,12 @@ int layer_backward(const Dims& x, int act, bool recompute, const void* dY, int64
     // K5: dA = dZ^T X ; K6: dB = dY^T H  (+ K7 fixed-order reductions);
     // one launch for both when they share the PP family
     if (p.pair)
-        return wgrad_pair(x.bf16, x.T, p.sa, x.r, x.d_in, dZ, p.ldw, X, x.ldx, dA, reinterpret_cast<float*>(w + p.off_pa),
+        return wgrad_pair(x.bf16, x.T, p.sa, x.r, x.d_in, dZ, p.ldw, X, ldx, dA, reinterpret_cast<float*>(w + p.off_pa),
                           x.d_out, x.r, dY, ldy, Hbuf, ldh, dB, reinterpret_cast<float*>(w + p.off_pb),
                           es * ((double)x.T * x.r + (double)x.T * x.d_in + (double)x.T * x.d_out +
                                 (double)x.T * x.r),
                           s);
-    int st = wgrad(x.bf16, x.r, x.d_in, x.T, dZ, p.ldw, X, x.ldx, dA, p.sa,
+    int st = wgrad(x.bf16, x.r, x.d_in, x.T, dZ, p.ldw, X, ldx, dA, p.sa,
                reinterpret_cast<float*>(w + p.off_pa), COLA_KC_BWD_DA,
                es * ((double)x.T * x.r + (double)x.T * x.d_in), s);
     if (st != COLA_OK) return st;
@@ -619,9 +651,9 @@ int bwd_checked(const cola_desc* desc, const void* dY, const void* X, const void
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (x.T == 0) return zero_weight_grads(x, dA, dB, s);
     if (!dY || !X || !Z || !A || !B || !dX) return COLA_ERR_INVALID_ARG;
-    const BwdPlan p = plan_bwd(x, recompute);
+    const BwdPlan p = fitting(ws_bytes, plan_bwd(x, recompute), plan_bwd(x, recompute, false));
     if (!ws || ws_bytes < p.total) return COLA_ERR_WORKSPACE;
-    return layer_backward(x, desc->act, recompute, dY, x.ldy, X, Z, H, A, B, dX, dA, dB,
+    return layer_backward(x, p, desc->act, recompute, dY, X, Z, H, A, B, dX, dA, dB,
                           reinterpret_cast<char*>(ws), s, gate);
 }
 
@@ -629,12 +661,16 @@ int bwd_checked(const cola_desc* desc, const void* dY, const void* X, const void
 struct OuterPlan {
     int64_t ldg;
     size_t off_g, total;
+    BwdPlan bwd;          // of the layer, which reads dP
 };
 
-OuterPlan plan_outer_bwd(const Dims& x, bool recompute) {
+OuterPlan plan_outer_bwd(const Dims& x, bool recompute, bool copies = true) {
     OuterPlan o;
     o.ldg = line_pitch(x.bf16, x.d_out);
-    o.off_g = plan_bwd(x, recompute).total;
+    Dims dp = x;
+    dp.ldy = o.ldg;
+    o.bwd = plan_bwd(dp, recompute, copies);
+    o.off_g = o.bwd.total;
     o.total = x.T == 0 ? 0 : o.off_g + align256((size_t)x.T * (size_t)o.ldg * x.esize);
     return o;
 }
@@ -708,9 +744,9 @@ const char* cola_kernel_name(int kc) {
 size_t cola_workspace_bytes(const cola_desc* desc, int phase) {
     Dims x;
     if (check_desc(desc, &x) != COLA_OK) return 0;
-    if (phase == 0) return fwd_ws(x, desc->recompute == 1);
+    if (phase == 0) return plan_fwd(x, desc->recompute == 1).total;
     if (phase == 1) return plan_bwd(x, desc->recompute == 1).total;
-    if (phase == 2) return fwd_ws(x, true);     // inference: H in the workspace, as CoLA-M's forward
+    if (phase == 2) return plan_fwd(x, true).total;     // inference: H in the workspace, as CoLA-M's forward
     if (phase == 3) return plan_outer_bwd(x, desc->recompute == 1).total;
     return 0;
 }
@@ -726,9 +762,9 @@ int cola_fwd(const cola_desc* desc, const void* X, const void* A, const void* B,
         if (recompute ? (H != nullptr) : (H == nullptr && x.T > 0)) return COLA_ERR_INVALID_ARG;
         if (x.T == 0) return COLA_OK;
         if (!X || !A || !B || !Y || !Z) return COLA_ERR_INVALID_ARG;
-        const FwdPlan p = plan_fwd(x, recompute);
+        const FwdPlan p = fitting(ws ? ws_bytes : 0, plan_fwd(x, recompute), plan_fwd(x, recompute, false));
         if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
-        return layer_forward(x, desc->act, recompute, X, A, B, Y, Z, H, -1, nullptr, reinterpret_cast<char*>(ws),
+        return layer_forward(x, p, desc->act, recompute, X, A, B, Y, Z, H, -1, nullptr, reinterpret_cast<char*>(ws),
                              reinterpret_cast<hipStream_t>(stream));
     });
 }
@@ -744,9 +780,9 @@ int cola_fwd_outer(const cola_desc* desc, int outer_act, const void* X, const vo
         if (recompute ? (H != nullptr) : (H == nullptr && x.T > 0)) return COLA_ERR_INVALID_ARG;
         if (x.T == 0) return COLA_OK;
         if (!X || !A || !B || !Y || !P || !Z) return COLA_ERR_INVALID_ARG;
-        const FwdPlan p = plan_fwd(x, recompute);
+        const FwdPlan p = fitting(ws ? ws_bytes : 0, plan_fwd(x, recompute), plan_fwd(x, recompute, false));
         if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
-        return layer_forward(x, desc->act, recompute, X, A, B, Y, Z, H, outer_act, P, reinterpret_cast<char*>(ws),
+        return layer_forward(x, p, desc->act, recompute, X, A, B, Y, Z, H, outer_act, P, reinterpret_cast<char*>(ws),
                              reinterpret_cast<hipStream_t>(stream));
     });
 }
@@ -780,6 +816,39 @@ struct ScratchPtrs {
 ScratchPtrs& scratch_ptrs() {
     static ScratchPtrs* s = new ScratchPtrs();   // never destroyed
     return *s;
+}
+
+// The size by which cola_bwd_scratch accepts a call: dZ, H (CoLA-M), repacked
+// weights and the partials of the 256 x 256, streaming and 64 x 64 fp32 kernels'
+// splits.  A rule of its own, so that which calls are accepted does not move
+// with the choice of kernels.
+size_t scratch_demand(const Dims& x, bool recompute) {
+    if (x.T == 0) return 0;
+    const WShape w[2] = {{x.r, x.d_in}, {x.d_out, x.r}};
+    const bool stream = get_option(OPT_STREAM_ONLY) == 1;
+    int64_t tiles[2], slots[2];
+    double elems[2];
+    bool wide[2];
+    for (int i = 0; i < 2; ++i) {
+        const int64_t M = w[i].M, N = w[i].N;
+        wide[i] = x.bf16 && !stream && M >= 128 && N >= 128;
+        const int64_t bm = x.bf16 ? (M > 128 ? 256 : 128) : 64, bn = x.bf16 ? (wide[i] ? 256 : 128) : 64;
+        tiles[i] = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+        slots[i] = !x.bf16 ? 1024 : (wide[i] ? 256 : 512);
+        elems[i] = (double)M * (double)N;
+    }
+    const int64_t bk = x.bf16 ? 64 : 16;
+    Split s[2];
+    if (wide[0] && wide[1] && get_option(OPT_WGRAD_PAIR) == 1) {
+        s[0] = s[1] = plan_split_tiles(bk, tiles[0] + tiles[1], 256, x.T, elems[0] + elems[1], kMaxSplits);
+    } else {
+        for (int i = 0; i < 2; ++i) s[i] = plan_split_tiles(bk, tiles[i], slots[i], x.T, elems[i], kMaxSplits);
+    }
+    size_t total = align256((size_t)x.T * (size_t)line_pitch(x.bf16, x.r) * x.esize) * (recompute ? 2 : 1);
+    for (int i = 0; i < 2; ++i)
+        total += (s[i].splits > 1 ? align256((size_t)s[i].splits * (size_t)(w[i].M * w[i].N) * 4) : 0) +
+                 plan_weight(x.bf16, w[i].M, w[i].N, 0).bytes;
+    return total;
 }
 
 // Device address of this device's scratch (looked up once per device, with
@@ -824,12 +893,17 @@ int cola_bwd_scratch(const cola_desc* desc, const void* dY, const void* X, const
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         if (x.T == 0) return zero_weight_grads(x, dA, dB, s);
         if (!dY || !X || !Z || !A || !B || !dX) return COLA_ERR_INVALID_ARG;
-        const BwdPlan p = plan_bwd(x, recompute);
+        if (scratch_demand(x, recompute) > COLA_SCRATCH_BYTES) return COLA_ERR_SCRATCH;
+        BwdPlan p = fitting(COLA_SCRATCH_BYTES, plan_bwd(x, recompute), plan_bwd(x, recompute, false));
+        // fewer splits where their partials do not fit (with one split the rest
+        // is part of the demand)
+        for (int64_t cap = kMaxSplits / 2; p.total > COLA_SCRATCH_BYTES && cap >= 1; cap /= 2)
+            p = plan_bwd(x, recompute, false, cap);
         if (p.total > COLA_SCRATCH_BYTES) return COLA_ERR_SCRATCH;
         void* w = nullptr;
         st = scratch_of_current_device(&w);
         if (st != COLA_OK) return st;
-        return layer_backward(x, desc->act, recompute, dY, x.ldy, X, Z, H, A, B, dX, dA, dB,
+        return layer_backward(x, p, desc->act, recompute, dY, X, Z, H, A, B, dX, dA, dB,
                               reinterpret_cast<char*>(w), s);
     });
 }
@@ -848,7 +922,7 @@ int cola_bwd_outer(const cola_desc* desc, int outer_act, const void* dY, const v
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         if (x.T == 0) return zero_weight_grads(x, dA, dB, s);
         if (!dY || !P || !X || !Z || !A || !B || !dX) return COLA_ERR_INVALID_ARG;
-        const OuterPlan o = plan_outer_bwd(x, recompute);
+        const OuterPlan o = fitting(ws_bytes, plan_outer_bwd(x, recompute), plan_outer_bwd(x, recompute, false));
         if (!ws || ws_bytes < o.total) return COLA_ERR_WORKSPACE;
         char* w = reinterpret_cast<char*>(ws);
         // dP = dY (.) sigma_out'(P), rounded to the storage dtype like dZ
@@ -858,7 +932,7 @@ int cola_bwd_outer(const cola_desc* desc, int outer_act, const void* dY, const v
             return launch_outer_grad(x.bf16, dY, x.ldy, P, x.ldy, dP, o.ldg, x.T, x.d_out, outer_act, s);
         });
         if (e != hipSuccess) return hip_fail(e, "outer_grad");
-        return layer_backward(x, desc->act, recompute, dP, o.ldg, X, Z, H, A, B, dX, dA, dB, w, s);
+        return layer_backward(x, o.bwd, desc->act, recompute, dP, X, Z, H, A, B, dX, dA, dB, w, s);
     });
 }
 
@@ -887,7 +961,7 @@ static DensePlan plan_dense(const Dims& x, int phase) {
     const WShape w{x.d_out, x.d_in};
     p.sp = plan_split(x.bf16, &w, 1, x.T, pitch16(x.ldx) && pitch16(x.ldy));
     p.parts = (phase == 1 && p.sp.splits > 1) ? align256((size_t)p.sp.splits * (size_t)(x.d_out * x.d_in) * 4) : 0;
-    p.pw = plan_pack(x.bf16, x.d_out, x.d_in, p.parts);
+    p.pw = plan_weight(x.bf16, x.d_out, x.d_in, p.parts);
     p.total = p.pw.off + p.pw.bytes;
     if (x.T == 0) p.total = 0;
     return p;
@@ -912,8 +986,8 @@ int dense_fwd(const dense_desc* desc, const void* X, const void* W, void* Y, voi
         if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         const void* Ww;
-        int64_t ldw;
-        hipError_t e = use_weight(p.pw, W, x.d_out, x.d_in, reinterpret_cast<char*>(ws), &Ww, &ldw, s);
+        hipError_t e = use_packed(p.pw, W, x.d_in, reinterpret_cast<char*>(ws), &Ww, s);
+        const int64_t ldw = p.pw.ld;
         if (e != hipSuccess) return hip_fail(e, "pack_rows");
         GemmArgs a = make_args(TAG_DENSE_FWD, x.T, x.d_out, x.d_in, X, x.ldx, KMAJ, Ww, ldw, KMAJ, Y, x.ldy, EPI_STORE, 0);
         const double b = (double)x.esize * ((double)x.T * x.d_in + (double)x.d_out * x.d_in + (double)x.T * x.d_out);
@@ -940,8 +1014,8 @@ int dense_bwd(const dense_desc* desc, const void* dY, const void* X, const void*
         if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
         char* w = reinterpret_cast<char*>(ws);
         const void* Ww;
-        int64_t ldw;
-        hipError_t e = use_weight(p.pw, W, x.d_out, x.d_in, w, &Ww, &ldw, s);
+        hipError_t e = use_packed(p.pw, W, x.d_in, w, &Ww, s);
+        const int64_t ldw = p.pw.ld;
         if (e != hipSuccess) return hip_fail(e, "pack_rows");
         GemmArgs a = make_args(TAG_DENSE_DX, x.T, x.d_in, x.d_out, dY, x.ldy, KMAJ, Ww, ldw, MNMAJ, dX, x.ldx, EPI_STORE, 0);
         const double b = (double)x.esize * ((double)x.T * x.d_out + (double)x.d_out * x.d_in + (double)x.T * x.d_in);
@@ -1033,23 +1107,36 @@ int check_group(const cola_group_desc* d, GDims* out) {
     return COLA_OK;
 }
 
-// Workspace: [H_all copy (CoLA-M)] [repacked A_all] [repacked B_p ...]
+// Workspace: [H_all copy (CoLA-M)] [repacked A_all] [repacked B_p ...] [repacked X]
+// [repacked H_p ...] (token rows where they are not 16-byte aligned)
 struct GFwdPlan {
     int64_t ldw;
     size_t off_h, total;
-    Pack pa, pb[COLA_GROUP_MAX];
+    Pack pa, pb[COLA_GROUP_MAX], px, ph[COLA_GROUP_MAX];
 };
 
-GFwdPlan plan_group_fwd(const GDims& g, bool recompute) {
+// H_p starts on a 16-byte boundary in every row (columns off[p] .. of H_all).
+bool group_h_aligned(const GDims& g, bool recompute, int p) {
+    return g.off[p] % 8 == 0 && (recompute || pitch16(g.ldz));
+}
+
+GFwdPlan plan_group_fwd(const GDims& g, bool recompute, bool copies = true) {
     GFwdPlan p;
     p.ldw = line_pitch(g.bf16, g.R);
     p.off_h = 0;
     const size_t hbytes = recompute ? align256((size_t)g.T * (size_t)p.ldw * g.esize) : 0;
-    p.pa = plan_pack(g.bf16, g.R, g.d_in, hbytes);
+    p.pa = plan_weight(g.bf16, g.R, g.d_in, hbytes);
     size_t next = p.pa.off + p.pa.bytes;
     for (int q = 0; q < g.n; ++q) {
-        p.pb[q] = plan_pack(g.bf16, g.d_out[q], g.r[q], next);
+        p.pb[q] = plan_weight(g.bf16, g.d_out[q], g.r[q], next);
         next = p.pb[q].off + p.pb[q].bytes;
+    }
+    copies = copies && g.bf16;
+    p.px = plan_pack(copies && !pitch16(g.ldx), g.T, g.d_in, g.ldx, next);
+    next = p.px.off + p.px.bytes;
+    for (int q = 0; q < g.n; ++q) {
+        p.ph[q] = plan_pack(copies && !group_h_aligned(g, recompute, q), g.T, g.r[q], recompute ? p.ldw : g.ldz, next);
+        next = p.ph[q].off + p.ph[q].bytes;
     }
     p.total = g.T == 0 ? 0 : next;
     return p;
@@ -1060,14 +1147,14 @@ GFwdPlan plan_group_fwd(const GDims& g, bool recompute) {
 // (0, 1), (2, 3), ...: one launch with one split for a pair, else one launch
 // each.  Workspace: [dZ_all] [H_all (CoLA-M)] [partials of the first
 // member of a pair] [of the second], both reused pair after pair,
-// [repacked A_all] [repacked B_p ...].
+// [repacked A_all] [repacked B_p ...] [repacked X] [repacked dY_p, H_p ...].
 struct GBwdPlan {
     int64_t ldw;
     size_t off_dz, off_h, off_p0, off_p1, total;
     int nw;                                // 1 + number of projections
     Split sp[COLA_GROUP_MAX + 1];          // split of each product (shared within a launched pair)
     bool paired[COLA_GROUP_MAX + 1];       // pair starting at an even w launched together
-    Pack wa, wb[COLA_GROUP_MAX];
+    Pack wa, wb[COLA_GROUP_MAX], px, py[COLA_GROUP_MAX], ph[COLA_GROUP_MAX];
 };
 
 // Shape of weight-gradient product w of a group.
@@ -1075,18 +1162,14 @@ WShape group_wgrad_shape(const GDims& g, int w) {
     return w == 0 ? WShape{g.R, g.d_in} : WShape{g.d_out[w - 1], g.r[w - 1]};
 }
 
-// H_p starts on a 16-byte boundary in every row (columns off[p] .. of H_all).
-bool group_h_aligned(const GDims& g, bool recompute, int p) {
-    return g.off[p] % 8 == 0 && (recompute || pitch16(g.ldz));
-}
-
-GBwdPlan plan_group_bwd(const GDims& g, bool recompute) {
+GBwdPlan plan_group_bwd(const GDims& g, bool recompute, bool copies = true) {
     GBwdPlan p;
     p.ldw = line_pitch(g.bf16, g.R);
     const size_t zbytes = align256((size_t)g.T * (size_t)p.ldw * g.esize);
     p.off_dz = 0;
     p.off_h = zbytes;
     p.off_p0 = p.off_h + (recompute ? zbytes : 0);
+    copies = copies && g.bf16;
     p.nw = g.n + 1;
     size_t pb[2] = {0, 0};
     for (int w0 = 0; w0 < p.nw; w0 += 2) {
@@ -1095,7 +1178,8 @@ GBwdPlan plan_group_bwd(const GDims& g, bool recompute) {
         bool al[2] = {true, true};
         for (int k = 0; k < cnt; ++k) {
             w[k] = group_wgrad_shape(g, w0 + k);
-            al[k] = w0 + k == 0 ? pitch16(g.ldx) : group_h_aligned(g, recompute, w0 + k - 1) && pitch16(g.ldy[w0 + k - 1]);
+            al[k] = copies || (w0 + k == 0 ? pitch16(g.ldx)
+                                           : group_h_aligned(g, recompute, w0 + k - 1) && pitch16(g.ldy[w0 + k - 1]));
         }
         p.paired[w0] = cnt == 2 && pair_wgrads(g.bf16, al[0] && al[1]);
         if (p.paired[w0]) {
@@ -1110,11 +1194,19 @@ GBwdPlan plan_group_bwd(const GDims& g, bool recompute) {
         }
     }
     p.off_p1 = p.off_p0 + pb[0];
-    p.wa = plan_pack(g.bf16, g.R, g.d_in, p.off_p1 + pb[1]);
+    p.wa = plan_weight(g.bf16, g.R, g.d_in, p.off_p1 + pb[1]);
     size_t next = p.wa.off + p.wa.bytes;
     for (int q = 0; q < g.n; ++q) {
-        p.wb[q] = plan_pack(g.bf16, g.d_out[q], g.r[q], next);
+        p.wb[q] = plan_weight(g.bf16, g.d_out[q], g.r[q], next);
         next = p.wb[q].off + p.wb[q].bytes;
+    }
+    p.px = plan_pack(copies && !pitch16(g.ldx), g.T, g.d_in, g.ldx, next);
+    next = p.px.off + p.px.bytes;
+    for (int q = 0; q < g.n; ++q) {
+        p.py[q] = plan_pack(copies && !pitch16(g.ldy[q]), g.T, g.d_out[q], g.ldy[q], next);
+        p.ph[q] = plan_pack(copies && !group_h_aligned(g, recompute, q), g.T, g.r[q], recompute ? p.ldw : g.ldz,
+                            p.py[q].off + p.py[q].bytes);
+        next = p.ph[q].off + p.ph[q].bytes;
     }
     p.total = g.T == 0 ? 0 : next;
     return p;
@@ -1140,22 +1232,22 @@ namespace {
 // Forward of a validated group with the pointers checked.  Z_all == NULL is
 // the inference forward: K1 stores only H (into the workspace), nothing is
 // kept for a backward pass.
-int group_forward(const GDims& g, int act, const void* X, const void* A_all, const void* const* B,
-                  void* const* Y, void* Z_all, void* H_all, bool h_in_ws, char* w, hipStream_t s,
+int group_forward(const GDims& g, const GFwdPlan& p, int act, const void* X_in, const void* A_all,
+                  const void* const* B, void* const* Y, void* Z_all, void* H_all, bool h_in_ws, char* w, hipStream_t s,
                   const Gate* gate = nullptr) {
-    const GFwdPlan p = plan_group_fwd(g, h_in_ws);
     char* Hbuf = h_in_ws ? w + p.off_h : reinterpret_cast<char*>(H_all);
     const int64_t ldh = h_in_ws ? p.ldw : g.ldz;
     const double es = (double)g.esize;
 
-    const void* Aw;
-    int64_t lda;
-    hipError_t e = use_weight(p.pa, A_all, g.R, g.d_in, w, &Aw, &lda, s);
+    const void *Aw, *X;
+    hipError_t e = use_packed(p.pa, A_all, g.d_in, w, &Aw, s);
+    if (e == hipSuccess) e = use_packed(p.px, X_in, g.ldx, w, &X, s);
     if (e != hipSuccess) return hip_fail(e, "pack_rows");
+    const int64_t lda = p.pa.ld, ldx = p.px.ld;
 
     // K1 for every projection at once: Z_all = X A_all^T, H_all = sigma(Z_all)
     if (Z_all) {
-        GemmArgs k1 = make_args(TAG_FWD_Z, g.T, g.R, g.d_in, X, g.ldx, KMAJ, Aw, lda, KMAJ, Z_all, g.ldz, EPI_Z_H,
+        GemmArgs k1 = make_args(TAG_FWD_Z, g.T, g.R, g.d_in, X, ldx, KMAJ, Aw, lda, KMAJ, Z_all, g.ldz, EPI_Z_H,
                                 act);
         k1.aux = Hbuf;
         k1.ldaux = ldh;
@@ -1163,7 +1255,7 @@ int group_forward(const GDims& g, int act, const void* X, const void* A_all, con
         e = timed(COLA_KC_FWD_Z, gemm_flops(g.T, g.R, g.d_in), b1, s, [&] { return gemm(k1, g.bf16, s); });
         if (e != hipSuccess) return hip_fail(e, "fwd_z_sigma");
     } else {
-        GemmArgs k1 = make_args(TAG_INFER_H, g.T, g.R, g.d_in, X, g.ldx, KMAJ, Aw, lda, KMAJ, Hbuf, ldh, EPI_H, act);
+        GemmArgs k1 = make_args(TAG_INFER_H, g.T, g.R, g.d_in, X, ldx, KMAJ, Aw, lda, KMAJ, Hbuf, ldh, EPI_H, act);
         const double b1 = es * ((double)g.T * g.d_in + (double)g.R * g.d_in + (double)g.T * g.R);
         e = timed(COLA_KC_INFER_H, gemm_flops(g.T, g.R, g.d_in), b1, s, [&] { return gemm(k1, g.bf16, s); });
         if (e != hipSuccess) return hip_fail(e, "infer_h");
@@ -1171,17 +1263,18 @@ int group_forward(const GDims& g, int act, const void* X, const void* A_all, con
 
     // K2 per projection: Y_p = H_p B_p^T
     for (int q = 0; q < g.n; ++q) {
-        const void* Bw;
-        int64_t ldb;
-        e = use_weight(p.pb[q], B[q], g.d_out[q], g.r[q], w, &Bw, &ldb, s);
+        const void *Bw, *Hq;
+        e = use_packed(p.pb[q], B[q], g.r[q], w, &Bw, s);
+        if (e == hipSuccess) e = use_packed(p.ph[q], Hbuf + g.off[q] * g.esize, ldh, w, &Hq, s);
         if (e != hipSuccess) return hip_fail(e, "pack_rows");
-        GemmArgs k2 = make_args(TAG_FWD_Y, g.T, g.d_out[q], g.r[q], Hbuf + g.off[q] * g.esize, ldh, KMAJ, Bw,
-                                ldb, KMAJ, Y[q], g.ldy[q], EPI_STORE, act);
+        const int64_t ldb = p.pb[q].ld;
+        GemmArgs k2 = make_args(TAG_FWD_Y, g.T, g.d_out[q], g.r[q], Hq, p.ph[q].ld, KMAJ, Bw, ldb, KMAJ,
+                                Y[q], g.ldy[q], EPI_STORE, act);
         double b2 = es * ((double)g.T * g.r[q] + (double)g.d_out[q] * g.r[q] + (double)g.T * g.d_out[q]);
         if (gate && q == g.n - 1) {
             // the last projection also stores m = g u (g: the group's first output)
-            GemmArgs kg = make_args(TAG_FWD_YG, g.T, g.d_out[q], g.r[q], Hbuf + g.off[q] * g.esize, ldh, KMAJ, Bw,
-                                    ldb, KMAJ, Y[q], gate->ld, EPI_GATE, act);
+            GemmArgs kg = make_args(TAG_FWD_YG, g.T, g.d_out[q], g.r[q], Hq, p.ph[q].ld, KMAJ, Bw, ldb, KMAJ,
+                                    Y[q], gate->ld, EPI_GATE, act);
             kg.zin = gate->g;
             kg.ldzin = gate->ld;
             kg.aux = gate->out;
@@ -1222,9 +1315,9 @@ int group_fwd_checked(const cola_group_desc* desc, const void* X, const void* A_
     if (!X || !A_all || !B || !Y || !Z_all) return COLA_ERR_INVALID_ARG;
     for (int q = 0; q < g.n; ++q)
         if (!B[q] || !Y[q]) return COLA_ERR_INVALID_ARG;
-    const GFwdPlan p = plan_group_fwd(g, recompute);
+    const GFwdPlan p = fitting(ws ? ws_bytes : 0, plan_group_fwd(g, recompute), plan_group_fwd(g, recompute, false));
     if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
-    return group_forward(g, desc->act, X, A_all, B, Y, Z_all, H_all, recompute, reinterpret_cast<char*>(ws),
+    return group_forward(g, p, desc->act, X, A_all, B, Y, Z_all, H_all, recompute, reinterpret_cast<char*>(ws),
                          reinterpret_cast<hipStream_t>(stream), gate);
 }
 
@@ -1234,9 +1327,9 @@ int infer_checked(const GDims& g, int act, const void* X, const void* A_all, con
     if (!X || !A_all || !B || !Y) return COLA_ERR_INVALID_ARG;
     for (int q = 0; q < g.n; ++q)
         if (!B[q] || !Y[q]) return COLA_ERR_INVALID_ARG;
-    const size_t need = plan_group_fwd(g, true).total;
-    if (need > 0 && (!ws || ws_bytes < need)) return COLA_ERR_WORKSPACE;
-    return group_forward(g, act, X, A_all, B, Y, nullptr, nullptr, true, reinterpret_cast<char*>(ws),
+    const GFwdPlan p = fitting(ws ? ws_bytes : 0, plan_group_fwd(g, true), plan_group_fwd(g, true, false));
+    if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
+    return group_forward(g, p, act, X, A_all, B, Y, nullptr, nullptr, true, reinterpret_cast<char*>(ws),
                          reinterpret_cast<hipStream_t>(stream));
 }
 
@@ -1273,7 +1366,7 @@ int cola_infer(const cola_desc* desc, const void* X, const void* A, const void* 
     });
 }
 
-int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const void* X, const void* Z_all,
+int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const void* X_in, const void* Z_all,
                    const void* H_all, const void* A_all, const void* const* B, void* dX, float* dA_all,
                    float* const* dB, void* ws, size_t ws_bytes, cola_stream_t stream) {
     return guarded([&]() -> int {
@@ -1295,10 +1388,10 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
                           [&] { return launch_fill_zero(dB[q], g.d_out[q] * g.r[q], s); });
             return e == hipSuccess ? COLA_OK : hip_fail(e, "fill_zero");
         }
-        if (!dY || !X || !Z_all || !A_all || !B || !dX) return COLA_ERR_INVALID_ARG;
+        if (!dY || !X_in || !Z_all || !A_all || !B || !dX) return COLA_ERR_INVALID_ARG;
         for (int q = 0; q < g.n; ++q)
             if (!dY[q] || !B[q]) return COLA_ERR_INVALID_ARG;
-        const GBwdPlan p = plan_group_bwd(g, recompute);
+        const GBwdPlan p = fitting(ws_bytes, plan_group_bwd(g, recompute), plan_group_bwd(g, recompute, false));
         if (!ws || ws_bytes < p.total) return COLA_ERR_WORKSPACE;
 
         char* w = reinterpret_cast<char*>(ws);
@@ -1306,18 +1399,19 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
         const char* Hbuf = recompute ? w + p.off_h : reinterpret_cast<const char*>(H_all);
         const int64_t ldh = recompute ? p.ldw : g.ldz;
         const double es = (double)g.esize;
-        const void* Aw;
-        int64_t lda;
-        hipError_t e = use_weight(p.wa, A_all, g.R, g.d_in, w, &Aw, &lda, s);
+        const void *Aw, *X, *dYw[COLA_GROUP_MAX], *Hw[COLA_GROUP_MAX];
+        hipError_t e = use_packed(p.wa, A_all, g.d_in, w, &Aw, s);
+        if (e == hipSuccess) e = use_packed(p.px, X_in, g.ldx, w, &X, s);
+        for (int q = 0; q < g.n && e == hipSuccess; ++q) e = use_packed(p.py[q], dY[q], g.ldy[q], w, &dYw[q], s);
         if (e != hipSuccess) return hip_fail(e, "pack_rows");
+        const int64_t lda = p.wa.ld;
 
         // K3 per projection: dZ_p = (dY_p B_p) (.) sigma'(Z_p)  [+ H_p for CoLA-M]
         for (int q = 0; q < g.n; ++q) {
             const void* Bw;
-            int64_t ldb;
-            e = use_weight(p.wb[q], B[q], g.d_out[q], g.r[q], w, &Bw, &ldb, s);
+            e = use_packed(p.wb[q], B[q], g.r[q], w, &Bw, s);
             if (e != hipSuccess) return hip_fail(e, "pack_rows");
-            GemmArgs k3 = make_args(TAG_BWD_DZ, g.T, g.r[q], g.d_out[q], dY[q], g.ldy[q], KMAJ, Bw, ldb, MNMAJ,
+            GemmArgs k3 = make_args(TAG_BWD_DZ, g.T, g.r[q], g.d_out[q], dYw[q], p.py[q].ld, KMAJ, Bw, p.wb[q].ld, MNMAJ,
                                     dZ + g.off[q] * g.esize, p.ldw, EPI_DZ, desc->act);
             k3.zin = reinterpret_cast<const char*>(Z_all) + g.off[q] * g.esize;
             k3.ldzin = g.ldz;
@@ -1346,10 +1440,12 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
             int kc;
         };
         Prod pr[COLA_GROUP_MAX + 1];
-        pr[0] = Prod{g.R, g.d_in, dZ, X, p.ldw, g.ldx, dA_all, COLA_KC_BWD_DA};
-        for (int q = 0; q < g.n; ++q)
-            pr[q + 1] = Prod{g.d_out[q], g.r[q], dY[q], Hbuf + g.off[q] * g.esize, g.ldy[q], ldh, dB[q],
-                             COLA_KC_BWD_DB};
+        pr[0] = Prod{g.R, g.d_in, dZ, X, p.ldw, p.px.ld, dA_all, COLA_KC_BWD_DA};
+        for (int q = 0; q < g.n; ++q) {
+            e = use_packed(p.ph[q], Hbuf + g.off[q] * g.esize, ldh, w, &Hw[q], s);   // CoLA-M: K3 wrote it
+            if (e != hipSuccess) return hip_fail(e, "pack_rows");
+            pr[q + 1] = Prod{g.d_out[q], g.r[q], dYw[q], Hw[q], p.py[q].ld, p.ph[q].ld, dB[q], COLA_KC_BWD_DB};
+        }
         float* part[2] = {reinterpret_cast<float*>(w + p.off_p0), reinterpret_cast<float*>(w + p.off_p1)};
         auto in_bytes = [&](const Prod& a) { return es * ((double)g.T * a.M + (double)g.T * a.N); };
         for (int w0 = 0; w0 < p.nw; w0 += 2) {

@@ -403,15 +403,30 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ out,
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) out[i] = 0.0f;
 }
 
-__global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t* __restrict__ src, int64_t rows,
-                                                        int64_t width, uint16_t* __restrict__ dst,
-                                                        int64_t ld) {
-    const int64_t n = rows * ld;
-    const int64_t step = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) {
-        const int64_t r = i / ld;
-        const int64_t c = i - r * ld;
-        dst[i] = c < width ? src[r * width + c] : (uint16_t)0;
+// dst[r][c] = src[r][c], c < width, 0 up to ld: rows of 16-byte chunks, 1 << shift
+// threads a row (a power of two near the chunk count), whole chunks read with one
+// element-aligned 16-byte load.
+__global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t* __restrict__ src, int64_t src_ld,
+                                                        int64_t rows, int64_t width, uint16_t* __restrict__ dst,
+                                                        int64_t ld, int shift) {
+    const int per = 256 >> shift;                            // rows a block takes at a time
+    const int t = threadIdx.x & ((1 << shift) - 1);
+    const int64_t chunks = ld >> 3;
+    for (int64_t r = (int64_t)blockIdx.x * per + (threadIdx.x >> shift); r < rows; r += (int64_t)gridDim.x * per) {
+        const uint16_t* s = src + r * src_ld;
+        uint16_t* d = dst + r * ld;
+        for (int64_t c = t; c < chunks; c += 1 << shift) {
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (8 * c + 8 <= width) {
+                __builtin_memcpy(&v, s + 8 * c, 16);
+            } else {
+                uint32_t e[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) e[k] = 8 * c + k < width ? (uint32_t)s[8 * c + k] : 0u;
+                v = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+            }
+            *reinterpret_cast<uint4*>(d + 8 * c) = v;
+        }
     }
 }
 
@@ -519,11 +534,15 @@ hipError_t launch_reduce_splits(const float* part, int splits, int64_t stride, f
     return hipGetLastError();
 }
 
-hipError_t launch_pack_rows(const void* src, int64_t rows, int64_t width, void* dst, int64_t ld,
+hipError_t launch_pack_rows(const void* src, int64_t src_ld, int64_t rows, int64_t width, void* dst, int64_t ld,
                             hipStream_t s) {
     if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(pack_rows_kernel, dim3(grid_for(rows * ld)), dim3(256), 0, s,
-                       reinterpret_cast<const uint16_t*>(src), rows, width, reinterpret_cast<uint16_t*>(dst), ld);
+    int shift = 3;                                           // 8 threads: a 128-byte line
+    while (shift < 8 && (int64_t(1) << shift) < ld / 8) ++shift;
+    int64_t grid = (rows + (256 >> shift) - 1) / (256 >> shift);
+    if (grid > 8192) grid = 8192;
+    hipLaunchKernelGGL(pack_rows_kernel, dim3((unsigned)grid), dim3(256), 0, s, reinterpret_cast<const uint16_t*>(src),
+                       src_ld, rows, width, reinterpret_cast<uint16_t*>(dst), ld, shift);
     return hipGetLastError();
 }
 

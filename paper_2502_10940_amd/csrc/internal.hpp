@@ -116,10 +116,10 @@ hipError_t launch_reduce_splits(const float* part, int splits, int64_t stride,
 // Both at once for two outputs with the same split count (one launch).
 hipError_t launch_reduce_splits2(const float* p0, int64_t st0, float* o0, int64_t n0, const float* p1, int64_t st1,
                                  float* o1, int64_t n1, int splits, hipStream_t s);
-// dst[r][c] = src[r][c] for c < width, 0 for width <= c < ld (16-bit
-// elements; src rows are contiguous).  Gives weights with odd widths a
-// 16-byte aligned row pitch.
-hipError_t launch_pack_rows(const void* src, int64_t rows, int64_t width, void* dst, int64_t ld,
+// dst[r][c] = src[r][c] for c < width, 0 for width <= c < ld (16-bit elements;
+// src rows src_ld apart, any alignment; dst 16-byte aligned, ld a multiple of
+// 8).  Gives operands with odd widths or pitches aligned rows.
+hipError_t launch_pack_rows(const void* src, int64_t src_ld, int64_t rows, int64_t width, void* dst, int64_t ld,
                             hipStream_t s);
 // out[i] = 0 for i < n (fp32 words).
 hipError_t launch_fill_zero(float* out, int64_t n, hipStream_t s);
