@@ -56,7 +56,7 @@ def test_tight_rows(case, recompute):
     d = lean.desc
     odd_h = not recompute and r % 8 != 0
     wf = cola.workspace_bytes(d, 0) - (1 if d_in % 8 or odd_h else 0)
-    wb = cola.workspace_bytes(d, 1) - (1 if d_in % 8 or d_out % 8 or odd_h else 0)
+    wb = cola.workspace_bytes(d, 1) - (1 if d_in % 8 or d_out % 8 else 0)   # a copy of H alone is less than the splits
     cola.fwd(d, lean.X, lean.A, lean.B, lean.Y, lean.Z, lean.H, lean.ws, ws_bytes=wf)
     cola.bwd(d, lean.dY, lean.X, lean.Z, lean.H, lean.A, lean.B, lean.dX, lean.dA, lean.dB, lean.ws, ws_bytes=wb)
     torch.cuda.synchronize()
