@@ -321,6 +321,16 @@ Pack plan_weight(bool bf16, int64_t rows, int64_t width, size_t off) {
     return plan_pack(bf16 && !pitch16(width), rows, width, width, off);
 }
 
+// The forward products of a few tokens take rows of any alignment: a copy of
+// operands that are read once would only add a pass.
+Pack direct(Pack p, bool skinny, int64_t src_ld) {
+    if (skinny && p.on) {
+        p.on = false;
+        p.ld = src_ld;
+    }
+    return p;
+}
+
 // Resolve an operand (rows src_ld apart) to a pointer, enqueueing its copy if
 // planned; its pitch is pk.ld.
 hipError_t use_packed(const Pack& pk, const void* src, int64_t src_ld, char* ws, const void** out, hipStream_t s) {
@@ -407,6 +417,19 @@ Plan fitting(size_t ws_bytes, Plan full, Plan lean) {
 
 hipError_t gemm(const GemmArgs& a, bool bf16, hipStream_t s) {
     return bf16 ? launch_gemm_bf16(a, s) : launch_gemm_f32_batch(&a, 1, s);
+}
+
+// n products of one kind and step, timed as one launch of class kc.
+hipError_t gemms(const GemmArgs* a, int n, int kc, double flops, double bytes, bool bf16, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    return timed(kc, flops, bytes, s, [&]() -> hipError_t {
+        if (bf16) return launch_gemm_bf16_batch(a, n, s);
+        for (int i = 0; i < n; i += kF32Batch) {
+            const hipError_t e = launch_gemm_f32_batch(a + i, n - i < kF32Batch ? n - i : kF32Batch, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    });
 }
 
 GemmArgs make_args(int tag, int64_t M, int64_t N, int64_t K, const void* p, int64_t ldp, int pl,
@@ -521,11 +544,16 @@ bool gate_fusion_on() { return get_option(OPT_FUSE_GATE) == 1; }
 
 // Forward of one validated layer with its pointers and workspace checked.
 // outer >= 0: the both-sigma variant (K2 stores P and Y = sigma_out(P)).
-int layer_forward(const Dims& x, const FwdPlan& p, int act, bool recompute, const void* X, const void* A,
+int layer_forward(const Dims& x, FwdPlan p, int act, bool recompute, const void* X, const void* A,
                   const void* B, void* Y, void* Z, void* H, int outer, void* P, char* w, hipStream_t s) {
     void* Hbuf = recompute ? (void*)(w + p.off_h) : H;
     const int64_t ldh = recompute ? p.ldw : x.ldz;
     const double es = (double)x.esize;
+    const bool few = x.bf16 && skinny_rows(x.T);
+    p.pa = direct(p.pa, few, x.d_in);
+    p.pb = direct(p.pb, few, x.r);
+    p.px = direct(p.px, few, x.ldx);
+    p.ph = direct(p.ph, few, ldh);
     const void *Aw, *Bw, *Xw, *Hw;
     hipError_t e = use_packed(p.pa, A, x.d_in, w, &Aw, s);
     if (e == hipSuccess) e = use_packed(p.pb, B, x.r, w, &Bw, s);
@@ -1232,13 +1260,20 @@ namespace {
 // Forward of a validated group with the pointers checked.  Z_all == NULL is
 // the inference forward: K1 stores only H (into the workspace), nothing is
 // kept for a backward pass.
-int group_forward(const GDims& g, const GFwdPlan& p, int act, const void* X_in, const void* A_all,
+int group_forward(const GDims& g, GFwdPlan p, int act, const void* X_in, const void* A_all,
                   const void* const* B, void* const* Y, void* Z_all, void* H_all, bool h_in_ws, char* w, hipStream_t s,
                   const Gate* gate = nullptr) {
     char* Hbuf = h_in_ws ? w + p.off_h : reinterpret_cast<char*>(H_all);
     const int64_t ldh = h_in_ws ? p.ldw : g.ldz;
     const double es = (double)g.esize;
 
+    const bool few = g.bf16 && skinny_rows(g.T);
+    p.pa = direct(p.pa, few, g.d_in);
+    p.px = direct(p.px, few, g.ldx);
+    for (int q = 0; q < g.n; ++q) {
+        p.pb[q] = direct(p.pb[q], few, g.r[q]);
+        p.ph[q] = direct(p.ph[q], few, ldh);
+    }
     const void *Aw, *X;
     hipError_t e = use_packed(p.pa, A_all, g.d_in, w, &Aw, s);
     if (e == hipSuccess) e = use_packed(p.px, X_in, g.ldx, w, &X, s);
@@ -1261,35 +1296,45 @@ int group_forward(const GDims& g, const GFwdPlan& p, int act, const void* X_in, 
         if (e != hipSuccess) return hip_fail(e, "infer_h");
     }
 
-    // K2 per projection: Y_p = H_p B_p^T
+    // K2: Y_p = H_p B_p^T, the projections together
+    GemmArgs k2[COLA_GROUP_MAX];
+    double f2 = 0.0, b2 = 0.0;
+    int n2 = 0;
     for (int q = 0; q < g.n; ++q) {
         const void *Bw, *Hq;
         e = use_packed(p.pb[q], B[q], g.r[q], w, &Bw, s);
         if (e == hipSuccess) e = use_packed(p.ph[q], Hbuf + g.off[q] * g.esize, ldh, w, &Hq, s);
         if (e != hipSuccess) return hip_fail(e, "pack_rows");
         const int64_t ldb = p.pb[q].ld;
-        GemmArgs k2 = make_args(TAG_FWD_Y, g.T, g.d_out[q], g.r[q], Hq, p.ph[q].ld, KMAJ, Bw, ldb, KMAJ,
-                                Y[q], g.ldy[q], EPI_STORE, act);
-        double b2 = es * ((double)g.T * g.r[q] + (double)g.d_out[q] * g.r[q] + (double)g.T * g.d_out[q]);
+        const double fq = gemm_flops(g.T, g.d_out[q], g.r[q]);
+        const double bq = es * ((double)g.T * g.r[q] + (double)g.d_out[q] * g.r[q]);
         if (gate && q == g.n - 1) {
             // the last projection also stores m = g u (g: the group's first output)
-            GemmArgs kg = make_args(TAG_FWD_YG, g.T, g.d_out[q], g.r[q], Hq, p.ph[q].ld, KMAJ, Bw, ldb, KMAJ,
-                                    Y[q], gate->ld, EPI_GATE, act);
+            GemmArgs kg = make_args(TAG_FWD_YG, g.T, g.d_out[q], g.r[q], Hq, p.ph[q].ld, KMAJ, Bw, ldb, KMAJ, Y[q],
+                                    gate->ld, EPI_GATE, act);
             kg.zin = gate->g;
             kg.ldzin = gate->ld;
             kg.aux = gate->out;
             kg.ldaux = gate->ld;
             *gate->fused = g.bf16 && gate_fusion_on() && g.ldy[q] == gate->ld && fused_epilogue_takes(kg);
             if (*gate->fused) {
-                k2 = kg;
-                if (!gate->keep_u) k2.c = nullptr;
-                b2 = es * ((double)g.T * g.r[q] + (double)g.d_out[q] * g.r[q] +
-                           (gate->keep_u ? 3.0 : 2.0) * g.T * g.d_out[q]);
+                if (!gate->keep_u) kg.c = nullptr;
+                e = gemms(k2, n2, COLA_KC_FWD_Y, f2, b2, g.bf16, s);      // first: g is one of their outputs
+                n2 = 0;
+                if (e == hipSuccess)
+                    e = timed(COLA_KC_FWD_Y, fq, bq + es * (gate->keep_u ? 3.0 : 2.0) * g.T * g.d_out[q], s,
+                              [&] { return gemm(kg, g.bf16, s); });
+                if (e != hipSuccess) return hip_fail(e, "fwd_y");
+                continue;
             }
         }
-        e = timed(COLA_KC_FWD_Y, gemm_flops(g.T, g.d_out[q], g.r[q]), b2, s, [&] { return gemm(k2, g.bf16, s); });
-        if (e != hipSuccess) return hip_fail(e, "fwd_y");
+        k2[n2++] = make_args(TAG_FWD_Y, g.T, g.d_out[q], g.r[q], Hq, p.ph[q].ld, KMAJ, Bw, ldb, KMAJ, Y[q], g.ldy[q],
+                             EPI_STORE, act);
+        f2 += fq;
+        b2 += bq + es * (double)g.T * g.d_out[q];
     }
+    e = gemms(k2, n2, COLA_KC_FWD_Y, f2, b2, g.bf16, s);
+    if (e != hipSuccess) return hip_fail(e, "fwd_y");
     return COLA_OK;
 }
 
@@ -1406,22 +1451,25 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
         if (e != hipSuccess) return hip_fail(e, "pack_rows");
         const int64_t lda = p.wa.ld;
 
-        // K3 per projection: dZ_p = (dY_p B_p) (.) sigma'(Z_p)  [+ H_p for CoLA-M]
+        // K3: dZ_p = (dY_p B_p) (.) sigma'(Z_p)  [+ H_p for CoLA-M], the projections together
+        GemmArgs k3[COLA_GROUP_MAX];
+        double f3 = 0.0, b3 = 0.0;
         for (int q = 0; q < g.n; ++q) {
             const void* Bw;
             e = use_packed(p.wb[q], B[q], g.r[q], w, &Bw, s);
             if (e != hipSuccess) return hip_fail(e, "pack_rows");
-            GemmArgs k3 = make_args(TAG_BWD_DZ, g.T, g.r[q], g.d_out[q], dYw[q], p.py[q].ld, KMAJ, Bw, p.wb[q].ld, MNMAJ,
-                                    dZ + g.off[q] * g.esize, p.ldw, EPI_DZ, desc->act);
-            k3.zin = reinterpret_cast<const char*>(Z_all) + g.off[q] * g.esize;
-            k3.ldzin = g.ldz;
-            k3.aux = recompute ? (void*)(w + p.off_h + g.off[q] * g.esize) : nullptr;
-            k3.ldaux = p.ldw;
-            const double b3 = es * ((double)g.T * g.d_out[q] + (double)g.d_out[q] * g.r[q] +
-                                    (double)g.T * g.r[q] * (recompute ? 3.0 : 2.0));
-            e = timed(COLA_KC_BWD_DZ, gemm_flops(g.T, g.r[q], g.d_out[q]), b3, s, [&] { return gemm(k3, g.bf16, s); });
-            if (e != hipSuccess) return hip_fail(e, "bwd_dz");
+            k3[q] = make_args(TAG_BWD_DZ, g.T, g.r[q], g.d_out[q], dYw[q], p.py[q].ld, KMAJ, Bw, p.wb[q].ld, MNMAJ,
+                              dZ + g.off[q] * g.esize, p.ldw, EPI_DZ, desc->act);
+            k3[q].zin = reinterpret_cast<const char*>(Z_all) + g.off[q] * g.esize;
+            k3[q].ldzin = g.ldz;
+            k3[q].aux = recompute ? (void*)(w + p.off_h + g.off[q] * g.esize) : nullptr;
+            k3[q].ldaux = p.ldw;
+            f3 += gemm_flops(g.T, g.r[q], g.d_out[q]);
+            b3 += es * ((double)g.T * g.d_out[q] + (double)g.d_out[q] * g.r[q] +
+                        (double)g.T * g.r[q] * (recompute ? 3.0 : 2.0));
         }
+        e = gemms(k3, g.n, COLA_KC_BWD_DZ, f3, b3, g.bf16, s);
+        if (e != hipSuccess) return hip_fail(e, "bwd_dz");
 
         // K4 for every projection at once: dX = dZ_all A_all = sum_p dZ_p A_p
         GemmArgs k4 = make_args(TAG_BWD_DX, g.T, g.d_in, g.R, dZ, p.ldw, KMAJ, Aw, lda, MNMAJ, dX, g.ldx, EPI_STORE,

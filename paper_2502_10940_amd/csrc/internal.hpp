@@ -70,6 +70,13 @@ hipError_t launch_gemm_bf16_pair(const GemmArgs& a0, const GemmArgs& a1, hipStre
 
 //   MID -- 128 x 128, 128 x 64 or 64 x 64 tiles, for outputs too small for PP
 // n products of one kind (same layouts and epilogue) in one launch.
+//   SKINNY -- at most kSkinnyRows token rows against weight rows (both
+//   k-contiguous, any alignment), K shared by a workgroup's waves; n products
+//   of one kind and the same tokens in one launch (n <= kMidBatch).
+constexpr int64_t kSkinnyRows = 64;
+hipError_t launch_gemm_skinny(const GemmArgs* a, int n, hipStream_t s);
+// Whether the forward products of M tokens run there.
+bool skinny_rows(int64_t M);
 enum MidTile : int { MID_128x128 = 0, MID_128x64 = 1, MID_64x64 = 2 };
 constexpr int kMidBatch = 4;
 constexpr int64_t kMidMaxBlocks = int64_t(1) << 20;
@@ -78,7 +85,8 @@ hipError_t launch_gemm_mid(const GemmArgs* a, int n, int tile, hipStream_t s);
 // Kernel and tile of a bf16 product.
 enum Route : int {
     ROUTE_AUTO = 0,        // GemmArgs: let the launcher choose
-    ROUTE_STREAM, ROUTE_PP, ROUTE_MID_128x128, ROUTE_MID_128x64, ROUTE_MID_64x64
+    ROUTE_STREAM, ROUTE_PP, ROUTE_MID_128x128, ROUTE_MID_128x64, ROUTE_MID_64x64,
+    ROUTE_SKINNY           // forward products of at most kSkinnyRows tokens
 };
 // Route of an unsplit product with aligned operands: the fastest by the cost
 // model of gemm_dispatch.hip; the option OPT_STREAM_ONLY sends every product
