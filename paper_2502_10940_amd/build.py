@@ -16,6 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libcola.so")
+ARGS = os.path.join(PKG, "_torch_args.so")          # CPython extension: checked calls of cola.py
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -49,6 +50,25 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
+def _build_args(verbose: bool) -> None:
+    """torch_args.cpp against this interpreter's torch, linked to libcola.so."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    inc = [sysconfig.get_paths()["include"], *cpp_extension.include_paths()]
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f for i in inc for f in ("-isystem", i)], os.path.join(CSRC, "torch_args.cpp"), "-o", ARGS + ".tmp",
+           "-L" + PKG, "-l:libcola.so", "-L" + tlib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + tlib]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(ARGS + ".tmp", ARGS)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     with ThreadPoolExecutor(len(SOURCES)) as ex:
@@ -58,6 +78,7 @@ def build(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(LIB + ".tmp", LIB)
+    _build_args(verbose)
     return LIB
 
 

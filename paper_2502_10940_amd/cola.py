@@ -243,6 +243,49 @@ def _check_layer(d, **ts):
         _on_gpu(ts.items())
 
 
+# The checked calls in native code (csrc/torch_args.cpp): they return None for
+# whatever is not the plain case, and the checks here decide.  Without the
+# extension every call takes the checks here.
+_native = None
+_raw_stream = _device = None
+
+
+def _native_calls():
+    """Load the extension once (after libcola.so); False if it is not built."""
+    global _native, _raw_stream, _device
+    lib()
+    import torch
+    try:
+        from . import _torch_args as m
+        _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    except (ImportError, AttributeError):
+        m = False
+    _native = m
+    return m
+
+
+def _try(name, stream, args):
+    """The native call: True when it ran, False when the checks here must decide."""
+    m = _native if _native is not None else _native_calls()
+    if not m:
+        return False
+    if stream is None:
+        import torch
+        # the current device's current stream (initialised devices only: on
+        # others no argument can be in GPU memory)
+        if not torch.cuda.is_initialized():
+            return False
+        stream = _raw_stream(_device())
+    elif not isinstance(stream, int):
+        stream = stream.cuda_stream
+    st = getattr(m, name)(*args, stream)
+    if st is None:
+        return False
+    if st != OK:
+        _check(st)
+    return True
+
+
 def _stream(stream):
     if stream is None:
         import torch
@@ -339,6 +382,8 @@ def group_workspace_bytes(d: GroupDesc, phase: int) -> int:
 
 def group_fwd(d: GroupDesc, X, A_all, B, Y, Z_all, H_all, ws=None, ws_bytes=None, stream=None):
     """Z_all = X A_all^T, H_all = sigma(Z_all), Y_p = H_p B_p^T (B, Y: lists)."""
+    if _try("group_fwd", stream, (d, X, A_all, B, Y, Z_all, H_all, ws, ws_bytes)):
+        return
     ws_bytes = _ws_bytes(ws, ws_bytes)
     _check_group(d, X=X, A_all=A_all, Z_all=Z_all, H_all=H_all, B=B, Y=Y)
     pb, _kb = _ptr_array(B)
@@ -349,6 +394,8 @@ def group_fwd(d: GroupDesc, X, A_all, B, Y, Z_all, H_all, ws=None, ws_bytes=None
 
 def group_infer(d: GroupDesc, X, A_all, B, Y, ws=None, ws_bytes=None, stream=None):
     """Inference forward: Y_p = sigma(X A_p^T) B_p^T, nothing kept for a backward pass."""
+    if _try("group_infer", stream, (d, X, A_all, B, Y, ws, ws_bytes)):
+        return
     ws_bytes = _ws_bytes(ws, ws_bytes)
     _check_group(d, X=X, A_all=A_all, B=B, Y=Y)
     pb, _kb = _ptr_array(B)
@@ -359,6 +406,8 @@ def group_infer(d: GroupDesc, X, A_all, B, Y, ws=None, ws_bytes=None, stream=Non
 
 def group_bwd(d: GroupDesc, dY, X, Z_all, H_all, A_all, B, dX, dA_all, dB, ws=None, ws_bytes=None, stream=None):
     """dZ_p = (dY_p B_p) * sigma'(Z_p), dX = sum_p dZ_p A_p, dA_all = dZ_all^T X, dB_p = dY_p^T H_p."""
+    if _try("group_bwd", stream, (d, dY, X, Z_all, H_all, A_all, B, dX, dA_all, dB, ws, ws_bytes)):
+        return
     ws_bytes = _ws_bytes(ws, ws_bytes)
     _check_group(d, X=X, A_all=A_all, Z_all=Z_all, H_all=H_all, dX=dX, dA_all=dA_all, B=B, dY=dY, dB=dB)
     pdy, _k1 = _ptr_array(dY)
@@ -382,6 +431,8 @@ def dense_workspace_bytes(d: DenseDesc, phase: int) -> int:
 
 def fwd(d: ColaDesc, X, A, B, Y, Z, H, ws=None, ws_bytes=None, stream=None):
     """Z = X A^T, H = sigma(Z), Y = H B^T (H is None in CoLA-M mode)."""
+    if _try("fwd", stream, (d, X, A, B, Y, Z, H, ws, ws_bytes)):
+        return
     ws_bytes = _ws_bytes(ws, ws_bytes)
     _check_layer(d, X=X, A=A, B=B, Y=Y, Z=Z, H=H)
     _check(lib().cola_fwd(ctypes.byref(d), _ptr(X), _ptr(A), _ptr(B), _ptr(Y), _ptr(Z), _ptr(H),
@@ -390,6 +441,8 @@ def fwd(d: ColaDesc, X, A, B, Y, Z, H, ws=None, ws_bytes=None, stream=None):
 
 def fwd_outer(d: ColaDesc, outer, X, A, B, Y, P, Z, H, ws=None, ws_bytes=None, stream=None):
     """Both-sigma variant: P = H B^T, Y = sigma_out(P) (outer: a sigma name or code)."""
+    if _try("fwd_outer", stream, (d, ACTS.get(outer, -1) if isinstance(outer, str) else outer, X, A, B, Y, P, Z, H, ws, ws_bytes)):
+        return
     ws_bytes = _ws_bytes(ws, ws_bytes)
     _check_layer(d, X=X, A=A, B=B, Y=Y, P=P, Z=Z, H=H)
     _check(lib().cola_fwd_outer(ctypes.byref(d), ACTS[outer] if isinstance(outer, str) else int(outer), _ptr(X),
@@ -399,6 +452,8 @@ def fwd_outer(d: ColaDesc, outer, X, A, B, Y, P, Z, H, ws=None, ws_bytes=None, s
 
 def bwd_outer(d: ColaDesc, outer, dY, P, X, Z, H, A, B, dX, dA, dB, ws=None, ws_bytes=None, stream=None):
     """Both-sigma backward: dP = dY * sigma_out'(P), then the layer backward on dP."""
+    if _try("bwd_outer", stream, (d, ACTS.get(outer, -1) if isinstance(outer, str) else outer, dY, P, X, Z, H, A, B, dX, dA, dB, ws, ws_bytes)):
+        return
     ws_bytes = _ws_bytes(ws, ws_bytes)
     _check_layer(d, dY=dY, P=P, X=X, Z=Z, H=H, A=A, B=B, dX=dX, dA=dA, dB=dB)
     _check(lib().cola_bwd_outer(ctypes.byref(d), ACTS[outer] if isinstance(outer, str) else int(outer), _ptr(dY),
@@ -408,6 +463,8 @@ def bwd_outer(d: ColaDesc, outer, dY, P, X, Z, H, A, B, dX, dA, dB, ws=None, ws_
 
 def infer(d: ColaDesc, X, A, B, Y, ws=None, ws_bytes=None, stream=None):
     """Inference forward: Y = sigma(X A^T) B^T, nothing kept for a backward pass."""
+    if _try("infer", stream, (d, X, A, B, Y, ws, ws_bytes)):
+        return
     ws_bytes = _ws_bytes(ws, ws_bytes)
     _check_layer(d, X=X, A=A, B=B, Y=Y)
     _check(lib().cola_infer(ctypes.byref(d), _ptr(X), _ptr(A), _ptr(B), _ptr(Y), _ptr(ws), ws_bytes,
@@ -416,6 +473,8 @@ def infer(d: ColaDesc, X, A, B, Y, ws=None, ws_bytes=None, stream=None):
 
 def bwd(d: ColaDesc, dY, X, Z, H, A, B, dX, dA, dB, ws=None, ws_bytes=None, stream=None):
     """dZ = (dY B) * sigma'(Z), dX = dZ A, dA = dZ^T X, dB = dY^T H (H None in CoLA-M)."""
+    if _try("bwd", stream, (d, dY, X, Z, H, A, B, dX, dA, dB, ws, ws_bytes)):
+        return
     ws_bytes = _ws_bytes(ws, ws_bytes)
     _check_layer(d, dY=dY, X=X, Z=Z, H=H, A=A, B=B, dX=dX, dA=dA, dB=dB)
     _check(lib().cola_bwd(ctypes.byref(d), _ptr(dY), _ptr(X), _ptr(Z), _ptr(H), _ptr(A), _ptr(B),
