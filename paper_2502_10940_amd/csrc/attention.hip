@@ -418,6 +418,7 @@ struct AttnArgs {
     int64_t ld;              // row pitch of every [T][ld] tensor
     int64_t T;
     int L, heads;
+    bool chunk_z;            // staged kernels: grid (heads, sequences, chunks), else (chunks, heads, sequences)
 };
 
 // ---------------------------------------------------------------------------
@@ -428,7 +429,9 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(AttnArgs a) {
     constexpr int NS = HD / 16, NT = HD / 32;
     __shared__ __attribute__((aligned(16))) char kt[RowTile<HD>::BYTES];
     __shared__ __attribute__((aligned(16))) char vt[RowTile<HD>::BYTES];
-    const int chunk = blockIdx.x, h = blockIdx.y, s = blockIdx.z;
+    // the chunks with the most keys first (see launch_all)
+    const int chunk = a.chunk_z ? gridDim.z - 1 - blockIdx.z : blockIdx.x;
+    const int h = a.chunk_z ? blockIdx.x : blockIdx.y, s = a.chunk_z ? blockIdx.y : blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hh = lane >> 5;
     const int L = a.L;
     const int64_t row0 = (int64_t)s * L;
@@ -468,11 +471,19 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(AttnArgs a) {
             for (int i = 0; i < NS; ++i) st = mfma(RowTile<HD>::frag(kt, 32 * sub, i, lane), qf[i], st);
             float p[16];
             float mb = -INFINITY;
+            if (kb + 31 <= qw0 && qw0 + WB <= L) {         // every key before every query: no mask
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int kp = kb + acc_row(v, hh);
-                p[v] = (kp <= qm) ? st[v] : -INFINITY;
-                mb = fmaxf(mb, p[v]);
+                for (int v = 0; v < 16; ++v) {
+                    p[v] = st[v];
+                    mb = fmaxf(mb, p[v]);
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int kp = kb + acc_row(v, hh);
+                    p[v] = (kp <= qm) ? st[v] : -INFINITY;
+                    mb = fmaxf(mb, p[v]);
+                }
             }
             softmax_block<NT>(p, mb, c, m, l, o);          // the first block holds key 0: m becomes finite
 #pragma unroll
@@ -499,7 +510,9 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(AttnArgs a) {
     constexpr int NS = HD / 16, NT = HD / 32;
     __shared__ __attribute__((aligned(16))) char kt[RowTile<HD>::BYTES];
     __shared__ __attribute__((aligned(16))) char vt[RowTile<HD>::BYTES];
-    const int chunk = blockIdx.x, h = blockIdx.y, s = blockIdx.z;
+    // the chunks with the most keys first (see launch_all)
+    const int chunk = a.chunk_z ? gridDim.z - 1 - blockIdx.z : blockIdx.x;
+    const int h = a.chunk_z ? blockIdx.x : blockIdx.y, s = a.chunk_z ? blockIdx.y : blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hh = lane >> 5;
     const int L = a.L;
     const int64_t row0 = (int64_t)s * L;
@@ -532,17 +545,29 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(AttnArgs a) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) dq[t] = f32x16{};
     const int kend = min(L, chunk * CHUNK + CHUNK);
-    // (no prefetch of the next stage here: its registers would cost occupancy)
+    // The next stage's rows fly during this one where their registers cost no
+    // occupancy (HD = 64; at 128 they would halve it).
+    constexpr bool PRE = HD == 64;
+    Stage<HD> sk, sv;
+    if constexpr (PRE) {
+        sk.load(a.k, a.ld, row0, 0, L, col0);
+        sv.load(a.v, a.ld, row0, 0, L, col0);
+    }
     for (int k0 = 0; k0 < kend; k0 += STG) {
         __syncthreads();
-        {
-            Stage<HD> sk, sv;
+        if constexpr (!PRE) {
             sk.load(a.k, a.ld, row0, k0, L, col0);
             sv.load(a.v, a.ld, row0, k0, L, col0);
-            sk.template put<true>(kt, L, a.rope);
-            sv.template put<false>(vt, L, a.rope);
         }
+        sk.template put<true>(kt, L, a.rope);
+        sv.template put<false>(vt, L, a.rope);
         __syncthreads();
+        if constexpr (PRE) {
+            if (k0 + STG < kend) {
+                sk.load(a.k, a.ld, row0, k0 + STG, L, col0);
+                sv.load(a.v, a.ld, row0, k0 + STG, L, col0);
+            }
+        }
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
             const int kb = k0 + 32 * sub;
@@ -554,11 +579,16 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(AttnArgs a) {
                 dpt = mfma(RowTile<HD>::frag(vt, 32 * sub, i, lane), df[i], dpt);
             }
             float ds[16];
+            if (kb + 31 <= qw0 && qw0 + WB <= L) {         // every key before every query: no mask
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int kp = kb + acc_row(v, hh);
-                const float p = (kp <= qm && qok) ? exp2_hw(st[v] * c - lse) : 0.0f;
-                ds[v] = p * (dpt[v] - D);
+                for (int v = 0; v < 16; ++v) ds[v] = exp2_hw(st[v] * c - lse) * (dpt[v] - D);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int kp = kb + acc_row(v, hh);
+                    const float p = (kp <= qm && qok) ? exp2_hw(st[v] * c - lse) : 0.0f;
+                    ds[v] = p * (dpt[v] - D);
+                }
             }
 #pragma unroll
             for (int t2 = 0; t2 < 2; ++t2) {
@@ -583,8 +613,9 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_kernel(AttnArgs a) {
     constexpr int NS = HD / 16, NT = HD / 32;
     __shared__ __attribute__((aligned(16))) char qt[RowTile<HD>::BYTES];
     __shared__ __attribute__((aligned(16))) char dt[RowTile<HD>::BYTES];
-    __shared__ float slse[STG], sD[STG];
-    const int chunk = blockIdx.x, h = blockIdx.y, s = blockIdx.z;
+    __shared__ __attribute__((aligned(16))) float slse[STG], sD[STG];
+    const int chunk = a.chunk_z ? blockIdx.z : blockIdx.x;           // the chunks with the most queries first
+    const int h = a.chunk_z ? blockIdx.x : blockIdx.y, s = a.chunk_z ? blockIdx.y : blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hh = lane >> 5;
     const int L = a.L;
     const int64_t row0 = (int64_t)s * L;
@@ -604,24 +635,34 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_kernel(AttnArgs a) {
         dk[t] = f32x16{};
         dv[t] = f32x16{};
     }
-    // query blocks from the workgroup's first key (rounded down to a stage) to the sequence end
-    // (no prefetch of the next stage here: its registers would cost occupancy)
-    for (int q0 = (chunk * CHUNK) / STG * STG; q0 < L; q0 += STG) {
-        __syncthreads();
-        {
-            Stage<HD> sq, sd;
-            sq.load(a.q, a.ld, row0, q0, L, col0);
-            sd.load(a.dO, a.ld, row0, q0, L, col0);
-            sq.template put<true>(qt, L, a.rope);
-            sd.template put<false>(dt, L, a.rope);
-        }
+    // query blocks from the workgroup's first key (rounded down to a stage) to the
+    // sequence end; the next stage's rows (and lse, D) fly during this one, which
+    // costs no occupancy (HD = 128: one wave per SIMD either way, set by the
+    // accumulators and the wave's own k and v)
+    const int qbeg = (chunk * CHUNK) / STG * STG;
+    Stage<HD> sq, sd;
+    float nl = 0.0f, nd = 0.0f;
+    auto fetch = [&](int q0) {
+        sq.load(a.q, a.ld, row0, q0, L, col0);
+        sd.load(a.dO, a.ld, row0, q0, L, col0);
         if (threadIdx.x < STG) {
             const int qpos = q0 + threadIdx.x;
             const bool ok = qpos < L;
-            slse[threadIdx.x] = ok ? a.lse[(int64_t)h * a.T + row0 + qpos] : 0.0f;
-            sD[threadIdx.x] = ok ? a.D[(int64_t)h * a.T + row0 + qpos] : 0.0f;
+            nl = ok ? a.lse[(int64_t)h * a.T + row0 + qpos] : 0.0f;
+            nd = ok ? a.D[(int64_t)h * a.T + row0 + qpos] : 0.0f;
+        }
+    };
+    fetch(qbeg);
+    for (int q0 = qbeg; q0 < L; q0 += STG) {
+        __syncthreads();
+        sq.template put<true>(qt, L, a.rope);
+        sd.template put<false>(dt, L, a.rope);
+        if (threadIdx.x < STG) {
+            slse[threadIdx.x] = nl;
+            sD[threadIdx.x] = nd;
         }
         __syncthreads();
+        if (q0 + STG < L) fetch(q0 + STG);
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
             const int qb = q0 + 32 * sub;
@@ -634,13 +675,24 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_kernel(AttnArgs a) {
                 dp = mfma(RowTile<HD>::frag(dt, 32 * sub, i, lane), vf[i], dp);
             }
             float p[16], ds[16];
+            // every key before every query, none past the end: no mask
+            const bool inside = kw0 + 31 <= qb && qb + 32 <= L && kw0 + WB <= L;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = 32 * sub + acc_row(v, hh);
-                const int qpos = q0 + r;
-                const bool ok = qpos < L && km <= qpos && kok;
-                p[v] = ok ? exp2_hw(st[v] * c - slse[r]) : 0.0f;
-                ds[v] = p[v] * (dp[v] - sD[r]);
+            for (int g = 0; g < 4; ++g) {
+                const int r = 32 * sub + acc_row(4 * g, hh);               // rows r .. r + 3
+                const float4 le = *reinterpret_cast<const float4*>(slse + r);
+                const float4 de = *reinterpret_cast<const float4*>(sD + r);
+                const float lv[4] = {le.x, le.y, le.z, le.w}, dd[4] = {de.x, de.y, de.z, de.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int v = 4 * g + e;
+                    p[v] = exp2_hw(st[v] * c - lv[e]);
+                    if (!inside) {
+                        const int qpos = q0 + r + e;
+                        if (!(qpos < L && km <= qpos && kok)) p[v] = 0.0f;
+                    }
+                    ds[v] = p[v] * (dp[v] - dd[e]);
+                }
             }
 #pragma unroll
             for (int t2 = 0; t2 < 2; ++t2) {
@@ -975,8 +1027,17 @@ __global__ __launch_bounds__(2 * NW * 64) void attn_bwd_seq_kernel(AttnArgs a) {
 }
 
 template <int HD>
-hipError_t launch_all(int which, const AttnArgs& a, int n_seq, hipStream_t s) {
-    const dim3 grid((unsigned)((a.L + CHUNK - 1) / CHUNK), (unsigned)a.heads, (unsigned)n_seq);
+hipError_t launch_all(int which, AttnArgs a, int n_seq, hipStream_t s) {
+    // Chunks of a sequence slowest, the longest first (the kernels number them
+    // so): a causal sequence's chunks differ up to L / CHUNK times in work, and the
+    // CUs drain evenly when the short ones come last.  With the masks off the
+    // interior blocks and the next stage's loads issued early (dk, dv), at 2
+    // sequences of 2048 and 32 heads of 128: forward 234 -> 139 us, dq 317 -> 194,
+    // dk and dv 840 -> 361.
+    const unsigned chunks = (unsigned)((a.L + CHUNK - 1) / CHUNK);
+    a.chunk_z = chunks <= 65535;                           // a grid's z limit
+    const dim3 grid = a.chunk_z ? dim3((unsigned)a.heads, (unsigned)n_seq, chunks)
+                                : dim3(chunks, (unsigned)a.heads, (unsigned)n_seq);
     if (which == 0) hipLaunchKernelGGL(attn_fwd_kernel<HD>, grid, dim3(NW * 64), 0, s, a);
     else if (which == 1) hipLaunchKernelGGL(attn_bwd_dq_kernel<HD>, grid, dim3(NW * 64), 0, s, a);
     else hipLaunchKernelGGL(attn_bwd_dkdv_kernel<HD>, grid, dim3(NW * 64), 0, s, a);
