@@ -26,10 +26,10 @@ std::atomic<int> g_force_stream{0};
 std::atomic<int> g_wgrad_pair{1};
 std::atomic<int> g_fuse_gate{1};
 
-// Tile and modelled cost of a route.  A round of up to 256 tiles costs
+// Tile and modelled cost of a route.  Each round of up to 256 tiles costs
 // steps * (step + load * x) + store * x microseconds, x the share of the CUs
-// with a tile (all CUs busy share L2 and HBM), after `fixed` for the launch, the
-// first loads and the last stores.  Fitted to MI355X timings of the products of
+// with a tile in it (all CUs busy share L2 and HBM), after `fixed` for the launch,
+// the first loads and the last stores.  Fitted to MI355X timings of the products of
 // the LLaMA shapes (60M to 7B) at 256 to 65536 tokens; the model is within
 // about 15 % of them.  E.g. T = 1024, K1 of a 1B projection (N = 512, K = 2048):
 // 256 x 256 tiles 42 us (8 of them), 128 x 128 17, 128 x 64 13, 64 x 64 10;
@@ -79,9 +79,11 @@ int64_t route_tiles(int route, int64_t M, int64_t N) {
 
 double route_us(int route, int64_t tiles, int64_t steps, bool wgrad) {
     const RouteCost& c = kCost[route];
-    const double rounds = (double)((tiles + 255) / 256);
-    const double x = tiles < 256 ? (double)tiles / 256.0 : 1.0;
-    return c.fixed + rounds * ((double)steps * (wgrad ? c.wstep + c.wload * x : c.step + c.load * x) + c.store * x);
+    const double full = (double)(tiles / 256);
+    const double x = (double)(tiles % 256) / 256.0;            // the last round's share of the CUs
+    const double step = wgrad ? c.wstep : c.step, load = wgrad ? c.wload : c.load;
+    return c.fixed + full * ((double)steps * (step + load) + c.store) +
+           (x > 0.0 ? (double)steps * (step + load * x) + c.store * x : 0.0);
 }
 
 bool route_fits(int route, int64_t M, int64_t N, int64_t splits) {
