@@ -308,7 +308,8 @@ hipError_t rms_bwd_nc(const void* x, const void* g, const void* dy, const void* 
                        nwg, d, groups);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_reduce_splits(groups, (int)ng, d, dg, d, s);
+    const ReduceJob job{groups, dg, d};
+    return launch_reduce(&job, 1, (int)ng, s);
 }
 
 }  // namespace

@@ -450,63 +450,49 @@ GemmArgs make_args(int tag, int64_t M, int64_t N, int64_t K, const void* p, int6
 
 double gemm_flops(int64_t M, int64_t N, int64_t K) { return 2.0 * (double)M * (double)N * (double)K; }
 
-// Weight gradient C[M][N] = sum_t P[t][m] Q[t][n] with K = T split into
-// chunks whose partials are summed in a fixed order.
-int wgrad(bool bf16, int64_t M, int64_t N, int64_t T, const void* P, int64_t ldp, const void* Q,
-          int64_t ldq, float* C, const Split& sp, float* partials, int kc, double bytes_in,
-          hipStream_t s) {
-    GemmArgs a = make_args(kc, M, N, T, P, ldp, MNMAJ, Q, ldq, MNMAJ, C, N, EPI_STORE_F32, 0);
-    a.splits = sp.splits;
-    a.k_chunk = sp.k_chunk;
-    a.route = sp.route;
-    if (sp.splits > 1) {
-        a.c = partials;
-        a.split_stride = M * N;
+// A weight gradient C[M][N] = sum_t P[t][m] Q[t][n]; its partials, if split.
+struct WProd {
+    int64_t M, N;
+    const void *P, *Q;
+    int64_t ldp, ldq;
+    float *C, *part;
+    int kc;               // timing class on its own
+};
+
+// n weight gradients (n <= kWSet) over K = T in one launch with one split, then
+// the fixed-order reductions of their partials in another.
+constexpr int kWSet = 4;
+static_assert(kWSet <= kMidBatch && kWSet <= kF32Batch && kWSet <= kReduceBatch, "a set is one launch");
+
+int wgrads(bool bf16, int64_t T, const Split& sp, const WProd* w, int n, hipStream_t s) {
+    GemmArgs a[kWSet];
+    ReduceJob red[kWSet];
+    double flops = 0.0, elems = 0.0, in = 0.0;
+    for (int i = 0; i < n; ++i) {
+        a[i] = make_args(i == 0 ? TAG_BWD_DA : TAG_BWD_DB, w[i].M, w[i].N, T, w[i].P, w[i].ldp, MNMAJ, w[i].Q, w[i].ldq,
+                         MNMAJ, w[i].C, w[i].N, EPI_STORE_F32, 0);
+        if (n == 1) a[i].tag = w[i].kc;
+        a[i].splits = sp.splits;
+        a[i].k_chunk = sp.k_chunk;
+        a[i].route = sp.route;
+        if (sp.splits > 1) {
+            a[i].c = w[i].part;
+            a[i].split_stride = w[i].M * w[i].N;
+        }
+        red[i] = ReduceJob{w[i].part, w[i].C, w[i].M * w[i].N};
+        flops += gemm_flops(w[i].M, w[i].N, T);
+        elems += (double)w[i].M * (double)w[i].N;
+        in += (bf16 ? 2.0 : 4.0) * (double)T * (double)(w[i].M + w[i].N);
     }
-    const double out_bytes = (double)M * (double)N * 4.0 * (sp.splits > 1 ? sp.splits : 1);
-    hipError_t e = timed(kc, gemm_flops(M, N, T), bytes_in + out_bytes, s, [&] { return gemm(a, bf16, s); });
+    const int kc = n > 1 ? (int)COLA_KC_BWD_DADB : w[0].kc;
+    hipError_t e = timed(kc, flops, in + elems * 4.0 * sp.splits, s, [&] {
+        if (!bf16) return launch_gemm_f32_batch(a, n, s);
+        return n > 1 ? launch_gemm_bf16_wgrads(a, n, s) : launch_gemm_bf16(a[0], s);
+    });
     if (e != hipSuccess) return hip_fail(e, cola_kernel_name(kc));
     if (sp.splits > 1) {
-        const double rb = (double)M * (double)N * 4.0 * (sp.splits + 1);
-        e = timed(COLA_KC_REDUCE, 0.0, rb, s,
-                  [&] { return launch_reduce_splits(partials, sp.splits, M * N, C, M * N, s); });
-        if (e != hipSuccess) return hip_fail(e, "reduce");
-    }
-    return COLA_OK;
-}
-
-// Both weight gradients of a layer, C0[M0][N0] = sum_t P0[t][m] Q0[t][n] and
-// C1 likewise, in one launch with one split of K = T, then
-// the fixed-order reductions of their partials.
-int wgrad_pair(bool bf16, int64_t T, const Split& sp, int64_t M0, int64_t N0, const void* P0, int64_t ldp0, const void* Q0,
-               int64_t ldq0, float* C0, float* part0, int64_t M1, int64_t N1, const void* P1, int64_t ldp1,
-               const void* Q1, int64_t ldq1, float* C1, float* part1, double bytes_in, hipStream_t s) {
-    GemmArgs a0 = make_args(TAG_BWD_DA, M0, N0, T, P0, ldp0, MNMAJ, Q0, ldq0, MNMAJ, C0, N0, EPI_STORE_F32, 0);
-    GemmArgs a1 = make_args(TAG_BWD_DB, M1, N1, T, P1, ldp1, MNMAJ, Q1, ldq1, MNMAJ, C1, N1, EPI_STORE_F32, 0);
-    for (GemmArgs* a : {&a0, &a1}) {
-        a->splits = sp.splits;
-        a->k_chunk = sp.k_chunk;
-        a->route = sp.route;
-    }
-    if (sp.splits > 1) {
-        a0.c = part0;
-        a0.split_stride = M0 * N0;
-        a1.c = part1;
-        a1.split_stride = M1 * N1;
-    }
-    const double elems = (double)M0 * (double)N0 + (double)M1 * (double)N1;
-    const double out_bytes = elems * 4.0 * (sp.splits > 1 ? sp.splits : 1);
-    hipError_t e = timed(COLA_KC_BWD_DADB, gemm_flops(M0, N0, T) + gemm_flops(M1, N1, T), bytes_in + out_bytes, s,
-                         [&] {
-                             if (bf16) return launch_gemm_bf16_pair(a0, a1, s);
-                             const GemmArgs both[2] = {a0, a1};
-                             return launch_gemm_f32_batch(both, 2, s);
-                         });
-    if (e != hipSuccess) return hip_fail(e, cola_kernel_name(COLA_KC_BWD_DADB));
-    if (sp.splits > 1) {
-        e = timed(COLA_KC_REDUCE, 0.0, elems * 4.0 * (sp.splits + 1), s, [&] {
-            return launch_reduce_splits2(part0, M0 * N0, C0, M0 * N0, part1, M1 * N1, C1, M1 * N1, sp.splits, s);
-        });
+        e = timed(COLA_KC_REDUCE, 0.0, elems * 4.0 * (sp.splits + 1), s,
+                  [&] { return launch_reduce(red, n, sp.splits, s); });
         if (e != hipSuccess) return hip_fail(e, "reduce");
     }
     return COLA_OK;
@@ -640,22 +626,13 @@ int layer_backward(const Dims& x, const BwdPlan& p, int act, bool recompute, con
     e = timed(COLA_KC_BWD_DX, gemm_flops(x.T, x.d_in, x.r), b4, s, [&] { return gemm(k4, x.bf16, s); });
     if (e != hipSuccess) return hip_fail(e, "bwd_dx");
 
-    // K5: dA = dZ^T X ; K6: dB = dY^T H  (+ K7 fixed-order reductions);
-    // one launch for both when they share the PP family
-    if (p.pair)
-        return wgrad_pair(x.bf16, x.T, p.sa, x.r, x.d_in, dZ, p.ldw, X, ldx, dA, reinterpret_cast<float*>(w + p.off_pa),
-                          x.d_out, x.r, dY, ldy, Hbuf, ldh, dB, reinterpret_cast<float*>(w + p.off_pb),
-                          es * ((double)x.T * x.r + (double)x.T * x.d_in + (double)x.T * x.d_out +
-                                (double)x.T * x.r),
-                          s);
-    int st = wgrad(x.bf16, x.r, x.d_in, x.T, dZ, p.ldw, X, ldx, dA, p.sa,
-               reinterpret_cast<float*>(w + p.off_pa), COLA_KC_BWD_DA,
-               es * ((double)x.T * x.r + (double)x.T * x.d_in), s);
-    if (st != COLA_OK) return st;
-    st = wgrad(x.bf16, x.d_out, x.r, x.T, dY, ldy, Hbuf, ldh, dB, p.sb,
-               reinterpret_cast<float*>(w + p.off_pb), COLA_KC_BWD_DB,
-               es * ((double)x.T * x.d_out + (double)x.T * x.r), s);
-    return st;
+    // K5: dA = dZ^T X ; K6: dB = dY^T H  (+ K7 fixed-order reductions); one launch
+    // for both where planned
+    const WProd wp[2] = {{x.r, x.d_in, dZ, X, p.ldw, ldx, dA, reinterpret_cast<float*>(w + p.off_pa), COLA_KC_BWD_DA},
+                         {x.d_out, x.r, dY, Hbuf, ldy, ldh, dB, reinterpret_cast<float*>(w + p.off_pb), COLA_KC_BWD_DB}};
+    if (p.pair) return wgrads(x.bf16, x.T, p.sa, wp, 2, s);
+    const int st = wgrads(x.bf16, x.T, p.sa, wp, 1, s);
+    return st != COLA_OK ? st : wgrads(x.bf16, x.T, p.sb, wp + 1, 1, s);
 }
 
 // dA = dB = 0 for an empty batch (the token sums are empty).
@@ -1050,8 +1027,8 @@ int dense_bwd(const dense_desc* desc, const void* dY, const void* X, const void*
         const double b = (double)x.esize * ((double)x.T * x.d_out + (double)x.d_out * x.d_in + (double)x.T * x.d_in);
         e = timed(COLA_KC_DENSE_DX, gemm_flops(x.T, x.d_in, x.d_out), b, s, [&] { return gemm(a, x.bf16, s); });
         if (e != hipSuccess) return hip_fail(e, "dense_dx");
-        return wgrad(x.bf16, x.d_out, x.d_in, x.T, dY, x.ldy, X, x.ldx, dW, p.sp, reinterpret_cast<float*>(w),
-                     COLA_KC_DENSE_DW, (double)x.esize * ((double)x.T * x.d_out + (double)x.T * x.d_in), s);
+        const WProd wp{x.d_out, x.d_in, dY, X, x.ldy, x.ldx, dW, reinterpret_cast<float*>(w), COLA_KC_DENSE_DW};
+        return wgrads(x.bf16, x.T, p.sp, &wp, 1, s);
     });
 }
 
@@ -1172,17 +1149,19 @@ GFwdPlan plan_group_fwd(const GDims& g, bool recompute, bool copies = true) {
 }
 
 // The weight gradients of a group are the products w = 0 (dA_all, R x d_in)
-// and w = 1 + p (dB_p, d_out_p x r_p), all over K = T.  They run in pairs
-// (0, 1), (2, 3), ...: one launch with one split for a pair, else one launch
-// each.  Workspace: [dZ_all] [H_all (CoLA-M)] [partials of the first
-// member of a pair] [of the second], both reused pair after pair,
-// [repacked A_all] [repacked B_p ...] [repacked X] [repacked dY_p, H_p ...].
+// and w = 1 + p (dB_p, d_out_p x r_p), all over K = T.  They run in sets of up to
+// kWSet, w = 0 .. 3, 4 .. 7, 8: one launch with one split for a set, or one launch
+// each where sets are off or rows unaligned.  Their tiles together fill the CUs with
+// fewer splits (gate and up of the 350M shape at 32768 tokens: dA with one dB and
+// the other dB apart 197 us with their reductions, the three together 141).
+// Workspace: [dZ_all] [H_all (CoLA-M)] [partials of the set's products, reused set
+// after set] [repacked A_all] [repacked B_p ...] [repacked X] [repacked dY_p, H_p ...].
 struct GBwdPlan {
     int64_t ldw;
-    size_t off_dz, off_h, off_p0, off_p1, total;
+    size_t off_dz, off_h, off_p[kWSet], total;
     int nw;                                // 1 + number of projections
-    Split sp[COLA_GROUP_MAX + 1];          // split of each product (shared within a launched pair)
-    bool paired[COLA_GROUP_MAX + 1];       // pair starting at an even w launched together
+    Split sp[COLA_GROUP_MAX + 1];          // split of each product (shared within a launched set)
+    bool set[COLA_GROUP_MAX + 1];          // the set starting at w runs in one launch
     Pack wa, wb[COLA_GROUP_MAX], px, py[COLA_GROUP_MAX], ph[COLA_GROUP_MAX];
 };
 
@@ -1197,34 +1176,35 @@ GBwdPlan plan_group_bwd(const GDims& g, bool recompute, bool copies = true) {
     const size_t zbytes = align256((size_t)g.T * (size_t)p.ldw * g.esize);
     p.off_dz = 0;
     p.off_h = zbytes;
-    p.off_p0 = p.off_h + (recompute ? zbytes : 0);
+    size_t next = p.off_h + (recompute ? zbytes : 0);
     copies = copies && g.bf16;
     p.nw = g.n + 1;
-    size_t pb[2] = {0, 0};
-    for (int w0 = 0; w0 < p.nw; w0 += 2) {
-        const int cnt = w0 + 1 < p.nw ? 2 : 1;
-        WShape w[2];
-        bool al[2] = {true, true};
+    size_t pb[kWSet] = {};
+    for (int w0 = 0; w0 < p.nw; w0 += kWSet) {
+        const int cnt = p.nw - w0 < kWSet ? p.nw - w0 : kWSet;
+        WShape w[kWSet];
+        bool al[kWSet], all = true;
         for (int k = 0; k < cnt; ++k) {
             w[k] = group_wgrad_shape(g, w0 + k);
             al[k] = copies || (w0 + k == 0 ? pitch16(g.ldx)
                                            : group_h_aligned(g, recompute, w0 + k - 1) && pitch16(g.ldy[w0 + k - 1]));
+            all = all && al[k];
         }
-        p.paired[w0] = cnt == 2 && pair_wgrads(g.bf16, al[0] && al[1]);
-        if (p.paired[w0]) {
-            p.sp[w0] = p.sp[w0 + 1] = plan_split(g.bf16, w, 2, g.T, true);
-        } else {
-            for (int k = 0; k < cnt; ++k) p.sp[w0 + k] = plan_split(g.bf16, w + k, 1, g.T, al[k]);
-        }
+        p.set[w0] = cnt > 1 && pair_wgrads(g.bf16, all);
+        if (p.set[w0]) p.sp[w0] = plan_split(g.bf16, w, cnt, g.T, true);
         for (int k = 0; k < cnt; ++k) {
-            const Split& sp = p.sp[w0 + k];
+            Split& sp = p.sp[w0 + k];
+            sp = p.set[w0] ? p.sp[w0] : plan_split(g.bf16, w + k, 1, g.T, al[k]);
             const size_t b = sp.splits > 1 ? align256((size_t)sp.splits * (size_t)(w[k].M * w[k].N) * 4) : 0;
             if (b > pb[k]) pb[k] = b;
         }
     }
-    p.off_p1 = p.off_p0 + pb[0];
-    p.wa = plan_weight(g.bf16, g.R, g.d_in, p.off_p1 + pb[1]);
-    size_t next = p.wa.off + p.wa.bytes;
+    for (int k = 0; k < kWSet; ++k) {
+        p.off_p[k] = next;
+        next += pb[k];
+    }
+    p.wa = plan_weight(g.bf16, g.R, g.d_in, next);
+    next = p.wa.off + p.wa.bytes;
     for (int q = 0; q < g.n; ++q) {
         p.wb[q] = plan_weight(g.bf16, g.d_out[q], g.r[q], next);
         next = p.wb[q].off + p.wb[q].bytes;
@@ -1445,7 +1425,7 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
         const char* Hbuf = recompute ? w + p.off_h : reinterpret_cast<const char*>(H_all);
         const int64_t ldh = recompute ? p.ldw : g.ldz;
         const double es = (double)g.esize;
-        const void *Aw, *X, *dYw[COLA_GROUP_MAX], *Hw[COLA_GROUP_MAX];
+        const void *Aw, *X, *dYw[COLA_GROUP_MAX];
         hipError_t e = use_packed(p.wa, A_all, g.d_in, w, &Aw, s);
         if (e == hipSuccess) e = use_packed(p.px, X_in, g.ldx, w, &X, s);
         for (int q = 0; q < g.n && e == hipSuccess; ++q) e = use_packed(p.py[q], dY[q], g.ldy[q], w, &dYw[q], s);
@@ -1480,36 +1460,29 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
         if (e != hipSuccess) return hip_fail(e, "bwd_dx");
 
         // K5 for every projection at once, dA_all = dZ_all^T X (product 0),
-        // and K6 per projection, dB_p = dY_p^T H_p (product 1 + p), in pairs
-        struct Prod {
-            int64_t M, N;
-            const void *P, *Q;
-            int64_t ldp, ldq;
-            float* C;
-            int kc;
-        };
-        Prod pr[COLA_GROUP_MAX + 1];
-        pr[0] = Prod{g.R, g.d_in, dZ, X, p.ldw, p.px.ld, dA_all, COLA_KC_BWD_DA};
-        for (int q = 0; q < g.n; ++q) {
-            e = use_packed(p.ph[q], Hbuf + g.off[q] * g.esize, ldh, w, &Hw[q], s);   // CoLA-M: K3 wrote it
-            if (e != hipSuccess) return hip_fail(e, "pack_rows");
-            pr[q + 1] = Prod{g.d_out[q], g.r[q], dYw[q], Hw[q], p.py[q].ld, p.ph[q].ld, dB[q], COLA_KC_BWD_DB};
-        }
-        float* part[2] = {reinterpret_cast<float*>(w + p.off_p0), reinterpret_cast<float*>(w + p.off_p1)};
-        auto in_bytes = [&](const Prod& a) { return es * ((double)g.T * a.M + (double)g.T * a.N); };
-        for (int w0 = 0; w0 < p.nw; w0 += 2) {
-            const int cnt = w0 + 1 < p.nw ? 2 : 1;
-            if (p.paired[w0]) {
-                const Prod &a = pr[w0], &b = pr[w0 + 1];
-                st = wgrad_pair(g.bf16, g.T, p.sp[w0], a.M, a.N, a.P, a.ldp, a.Q, a.ldq, a.C, part[0], b.M, b.N, b.P, b.ldp,
-                                b.Q, b.ldq, b.C, part[1], in_bytes(a) + in_bytes(b), s);
+        // and K6 per projection, dB_p = dY_p^T H_p (product 1 + p), in sets
+        for (int w0 = 0; w0 < p.nw; w0 += kWSet) {
+            const int cnt = p.nw - w0 < kWSet ? p.nw - w0 : kWSet;
+            WProd wp[kWSet];
+            for (int k = 0; k < cnt; ++k) {
+                float* part = reinterpret_cast<float*>(w + p.off_p[k]);
+                const int q = w0 + k - 1;
+                if (q < 0) {
+                    wp[k] = WProd{g.R, g.d_in, dZ, X, p.ldw, p.px.ld, dA_all, part, COLA_KC_BWD_DA};
+                    continue;
+                }
+                const void* Hw;                            // CoLA-M: K3 wrote H
+                e = use_packed(p.ph[q], Hbuf + g.off[q] * g.esize, ldh, w, &Hw, s);
+                if (e != hipSuccess) return hip_fail(e, "pack_rows");
+                wp[k] = WProd{g.d_out[q], g.r[q], dYw[q], Hw, p.py[q].ld, p.ph[q].ld, dB[q], part, COLA_KC_BWD_DB};
+            }
+            if (p.set[w0]) {
+                st = wgrads(g.bf16, g.T, p.sp[w0], wp, cnt, s);
                 if (st != COLA_OK) return st;
                 continue;
             }
             for (int k = 0; k < cnt; ++k) {
-                const Prod& a = pr[w0 + k];
-                st = wgrad(g.bf16, a.M, a.N, g.T, a.P, a.ldp, a.Q, a.ldq, a.C, p.sp[w0 + k], part[k], a.kc,
-                           in_bytes(a), s);
+                st = wgrads(g.bf16, g.T, p.sp[w0 + k], wp + k, 1, s);
                 if (st != COLA_OK) return st;
             }
         }

@@ -155,48 +155,57 @@ bool fused_epilogue_takes(const GemmArgs& a) {
     return route_of(a) != ROUTE_STREAM;
 }
 
-hipError_t launch_gemm_bf16_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
-    const int r0 = route_of(a0), r1 = route_of(a1);
-    if (r0 == r1 && r0 == ROUTE_PP) return launch_gemm_pp_pair(a0, a1, s);
-    if (r0 == r1 && r0 != ROUTE_STREAM) {
-        const GemmArgs both[2] = {a0, a1};
-        return launch_route(both, 2, r0, s);
+hipError_t launch_gemm_bf16_wgrads(const GemmArgs* a, int n, hipStream_t s) {
+    bool alike = n <= kMidBatch;
+    for (int i = 0; i < n; ++i) alike = alike && route_of(a[i]) == route_of(a[0]);
+    if (alike && route_of(a[0]) == ROUTE_PP) return launch_gemm_pp_batch(a, n, s);
+    if (alike) return launch_route(a, n, route_of(a[0]), s);
+    for (int i = 0; i < n; ++i) {
+        const hipError_t e = launch_gemm_bf16(a[i], s);
+        if (e != hipSuccess) return e;
     }
-    const hipError_t e = launch_route(&a0, 1, r0, s);
-    return e == hipSuccess ? launch_route(&a1, 1, r1, s) : e;
+    return hipSuccess;
 }
 
 hipError_t launch_gemm_bf16_batch(const GemmArgs* a, int n, hipStream_t s) {
-    // The tiles of all n products together decide the route: they run at once.
     int64_t K = 0;
-    bool ok = n > 1, skinny = n > 1;
-    for (int i = 0; i < n; ++i) skinny = skinny && skinny_takes(a[i]) && a[i].epi == a[0].epi;
-    if (skinny) return launch_route(a, n, ROUTE_SKINNY, s);
-    for (int i = 0; i < n && ok; ++i) {
-        ok = operands_ok(a[i]) && a[i].splits == 1 && !g_force_stream.load(std::memory_order_relaxed);
+    bool skinny = n > 1, ok = n > 1 && n <= kMidBatch && !g_force_stream.load(std::memory_order_relaxed);
+    for (int i = 0; i < n; ++i) {
+        skinny = skinny && skinny_takes(a[i]) && a[i].epi == a[0].epi;
+        ok = ok && operands_ok(a[i]) && a[i].splits == 1 && a[i].epi == a[0].epi;
         K = a[i].K > K ? a[i].K : K;
     }
+    if (skinny) return launch_route(a, n, ROUTE_SKINNY, s);
     if (ok) {
+        // Together on one route (their tiles run at once: four dZ products of 64
+        // 256 x 256 tiles fill the CUs that one leaves three quarters idle) or
+        // one by one, whichever the model says is faster.  256 x 256 tiles share a
+        // launch only while they fit one round: beyond it the persistent kernel
+        // of each product alone is the faster (2 x 1408 tiles with K = 256: 174
+        // us against 184 together; 2 x 128 tiles with K = 2736: 216 against 140).
         const int64_t steps = (K + BF16_BK - 1) / BF16_BK;
-        int best = ROUTE_STREAM;
-        double best_us = -1.0;
+        int best = ROUTE_AUTO;
+        double best_us = 0.0;
+        for (int i = 0; i < n; ++i) {
+            const int r = gemm_route(a[i].M, a[i].N, a[i].K);
+            best_us += r == ROUTE_STREAM ? 1e30 : route_us(r, route_tiles(r, a[i].M, a[i].N), steps, false);
+        }
         for (int r : kRoutes) {
-            double us = 0.0;
             int64_t tiles = 0;
-            bool fits = true;
+            bool fits = r != ROUTE_PP || a[0].epi == EPI_DZ || (a[0].epi == EPI_STORE && a[0].q_layout == KMAJ);
             for (int i = 0; i < n; ++i) {
                 tiles += route_tiles(r, a[i].M, a[i].N);
-                us += route_us(r, route_tiles(r, a[i].M, a[i].N), steps, false);    // PP: one launch each
                 fits = fits && route_fits(r, a[i].M, a[i].N, n);
             }
-            if (!fits) continue;
-            if (r != ROUTE_PP) us = route_us(r, tiles, steps, false);
-            if (best_us < 0 || us < best_us) {
+            fits = fits && (r != ROUTE_PP || tiles <= 256);
+            const double us = route_us(r, tiles, steps, false);
+            if (fits && us < best_us) {
                 best_us = us;
                 best = r;
             }
         }
-        return launch_route(a, n, best, s);
+        if (best == ROUTE_PP) return launch_gemm_pp_batch(a, n, s);
+        if (best != ROUTE_AUTO) return launch_route(a, n, best, s);
     }
     for (int i = 0; i < n; ++i) {
         const hipError_t e = launch_gemm_bf16(a[i], s);

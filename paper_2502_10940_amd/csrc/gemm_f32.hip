@@ -373,29 +373,23 @@ __device__ __forceinline__ void reduce_chunks_range(const float* __restrict__ pa
     }
 }
 
-__global__ __launch_bounds__(256) void reduce_chunks_kernel(const float* __restrict__ p0, int64_t st0,
-                                                            float* __restrict__ o0, int64_t n0, int64_t g0,
-                                                            const float* __restrict__ p1, int64_t st1,
-                                                            float* __restrict__ o1, int64_t n1, int splits) {
-    if ((int64_t)blockIdx.x < g0) reduce_chunks_range(p0, splits, st0, o0, n0, blockIdx.x);
-    else reduce_chunks_range(p1, splits, st1, o1, n1, (int64_t)blockIdx.x - g0);
-}
+// Up to kReduceBatch reductions with one split count in a launch: blocks
+// [first[i], first[i + 1]) sum the partials of job i (the order does not depend on
+// what shares the launch).
+struct ReduceBatch {
+    ReduceJob j[kReduceBatch];
+    int64_t first[kReduceBatch + 1];
+    int n, splits;
+};
 
-__global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restrict__ part, int splits,
-                                                            int64_t stride, float* __restrict__ out,
-                                                            int64_t n) {
-    reduce_splits_range(part, splits, stride, out, n, blockIdx.x, gridDim.x);
-}
-
-// Two reductions with the same split count in one launch: blocks [0, g0) sum
-// the partials of output 0, the rest those of output 1 (same order, so the
-// same bits as two launches).
-__global__ __launch_bounds__(256) void reduce_splits2_kernel(const float* __restrict__ p0, int64_t st0,
-                                                             float* __restrict__ o0, int64_t n0, int64_t g0,
-                                                             const float* __restrict__ p1, int64_t st1,
-                                                             float* __restrict__ o1, int64_t n1, int splits) {
-    if ((int64_t)blockIdx.x < g0) reduce_splits_range(p0, splits, st0, o0, n0, blockIdx.x, g0);
-    else reduce_splits_range(p1, splits, st1, o1, n1, (int64_t)blockIdx.x - g0, (int64_t)gridDim.x - g0);
+template <bool CHUNKS>
+__global__ __launch_bounds__(256) void reduce_kernel(const ReduceBatch bt) {
+    const int64_t b = blockIdx.x;
+    int i = 0;
+    while (i + 1 < bt.n && b >= bt.first[i + 1]) ++i;
+    const ReduceJob& r = bt.j[i];
+    if constexpr (CHUNKS) reduce_chunks_range(r.part, bt.splits, r.n, r.out, r.n, b - bt.first[i]);
+    else reduce_splits_range(r.part, bt.splits, r.n, r.out, r.n, b - bt.first[i], bt.first[i + 1] - bt.first[i]);
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ out, int64_t n) {
@@ -502,35 +496,24 @@ static bool chunks_ok(const float* part, int64_t stride, const float* out, int64
 }
 static int64_t chunk_blocks(int64_t n) { return (n / 4 + 256 / kChunkLanes - 1) / (256 / kChunkLanes); }
 
-hipError_t launch_reduce_splits2(const float* p0, int64_t st0, float* o0, int64_t n0, const float* p1, int64_t st1,
-                                 float* o1, int64_t n1, int splits, hipStream_t s) {
-    if (n0 <= 0) return launch_reduce_splits(p1, splits, st1, o1, n1, s);
-    if (n1 <= 0) return launch_reduce_splits(p0, splits, st0, o0, n0, s);
-    if (chunks_ok(p0, st0, o0, n0, splits) && chunks_ok(p1, st1, o1, n1, splits)) {
-        const int64_t b0 = chunk_blocks(n0), b1 = chunk_blocks(n1);
-        if (b0 + b1 > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL(reduce_chunks_kernel, dim3((unsigned)(b0 + b1)), dim3(256), 0, s, p0, st0, o0, n0, b0, p1,
-                           st1, o1, n1, splits);
-        return hipGetLastError();
+hipError_t launch_reduce(const ReduceJob* jobs, int n, int splits, hipStream_t s) {
+    if (n < 1 || n > kReduceBatch) return hipErrorInvalidValue;
+    ReduceBatch bt;
+    bt.n = n;
+    bt.splits = splits;
+    bool chunks = true;
+    for (int i = 0; i < n; ++i) chunks = chunks && chunks_ok(jobs[i].part, jobs[i].n, jobs[i].out, jobs[i].n, splits);
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        if (jobs[i].n <= 0) return hipErrorInvalidValue;
+        bt.j[i] = jobs[i];
+        bt.first[i] = blocks;
+        blocks += chunks ? chunk_blocks(jobs[i].n) : (int64_t)grid_for((jobs[i].n + 3) / 4);
     }
-    const unsigned g0 = grid_for((n0 + 3) / 4), g1 = grid_for((n1 + 3) / 4);
-    hipLaunchKernelGGL(reduce_splits2_kernel, dim3(g0 + g1), dim3(256), 0, s, p0, st0, o0, n0, (int64_t)g0, p1, st1,
-                       o1, n1, splits);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce_splits(const float* part, int splits, int64_t stride, float* out, int64_t n,
-                                hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    if (chunks_ok(part, stride, out, n, splits)) {
-        const int64_t b = chunk_blocks(n);
-        if (b > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL(reduce_chunks_kernel, dim3((unsigned)b), dim3(256), 0, s, part, stride, out, n, b, part,
-                           stride, out, (int64_t)0, splits);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3(grid_for((n + 3) / 4)), dim3(256), 0, s, part, splits,
-                       stride, out, n);
+    for (int i = n; i <= kReduceBatch; ++i) bt.first[i] = blocks;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    if (chunks) hipLaunchKernelGGL(reduce_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, bt);
+    else hipLaunchKernelGGL(reduce_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, bt);
     return hipGetLastError();
 }
 

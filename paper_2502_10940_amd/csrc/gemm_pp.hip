@@ -274,16 +274,23 @@ __global__ __launch_bounds__(NTHR, 1) void gemm_pp_kernel(GemmArgs a) {
     pp_one_tile<BK, PL, QL, EPI>(a, xcd_block(), smem);
 }
 
-// Two products of the same kind in one grid: blocks [0, nb0) are the tiles
-// and splits of a0, the rest those of a1 (the two weight gradients of a
-// layer, which share K = T: one launch, one set of partials per split for
-// both, and their tiles together fill the CUs).
-template <int BK, int PL, int QL, int EPI, int TAG>
-__global__ __launch_bounds__(NTHR, 1) void gemm_pp_pair_kernel(GemmArgs a0, GemmArgs a1, int64_t nb0) {
+// Up to kMidBatch products of one kind in one grid: blocks [first[i],
+// first[i + 1]) are the tiles and splits of product i (the weight gradients of a
+// layer or group, which share K = T and one split; a group's dZ or Y products
+// whose tiles would not fill the CUs one launch at a time).
+struct PPBatch {
+    GemmArgs a[kMidBatch];
+    int64_t first[kMidBatch + 1];
+    int n;
+};
+
+template <int BK, int PL, int QL, int EPI>
+__global__ __launch_bounds__(NTHR, 1) void gemm_pp_batch_kernel(const PPBatch bt) {
     __shared__ __attribute__((aligned(1024))) char smem[pp_smem_bytes<PL, QL, BK>()];
     const int64_t b = xcd_block();
-    if (b < nb0) pp_one_tile<BK, PL, QL, EPI>(a0, b, smem);
-    else pp_one_tile<BK, PL, QL, EPI>(a1, b - nb0, smem);
+    int i = 0;
+    while (i + 1 < bt.n && b >= bt.first[i + 1]) ++i;
+    pp_one_tile<BK, PL, QL, EPI>(bt.a[i], b - bt.first[i], smem);
 }
 
 // ---- persistent variant (every K range a whole number of K tiles, at
@@ -572,20 +579,34 @@ hipError_t launch_p(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int PL, int QL, int EPI>
+hipError_t launch_b(const GemmArgs* a, int n, hipStream_t s) {
+    PPBatch bt;
+    bt.n = n;
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        if (a[i].p_layout != PL || a[i].q_layout != QL || a[i].epi != EPI) return hipErrorInvalidValue;
+        bt.a[i] = a[i];
+        bt.first[i] = blocks;
+        blocks += ((a[i].M + BM - 1) / BM) * ((a[i].N + BN - 1) / BN) * (int64_t)a[i].splits;
+    }
+    for (int i = n; i <= kMidBatch; ++i) bt.first[i] = blocks;
+    if (blocks <= 0) return hipSuccess;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((gemm_pp_batch_kernel<kPPBK, PL, QL, EPI>), dim3((unsigned)blocks), dim3(NTHR), 0, s, bt);
+    return hipGetLastError();
+}
+
 }  // namespace
 
-hipError_t launch_gemm_pp_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
-    for (const GemmArgs* a : {&a0, &a1})
-        if (a->p_layout != MNMAJ || a->q_layout != MNMAJ || a->epi != EPI_STORE_F32) return hipErrorInvalidValue;
-    auto blocks = [](const GemmArgs& a) {
-        return ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * (int64_t)a.splits;
-    };
-    const int64_t nb0 = blocks(a0), nb1 = blocks(a1);
-    if (nb0 + nb1 <= 0) return hipSuccess;
-    if (nb0 + nb1 > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((gemm_pp_pair_kernel<kPPBK, MNMAJ, MNMAJ, EPI_STORE_F32, TAG_BWD_DA>),
-                       dim3((unsigned)(nb0 + nb1)), dim3(NTHR), 0, s, a0, a1, nb0);
-    return hipGetLastError();
+hipError_t launch_gemm_pp_batch(const GemmArgs* a, int n, hipStream_t s) {
+    if (n < 1 || n > kMidBatch) return hipErrorInvalidValue;
+    switch (a[0].epi) {
+        case EPI_STORE_F32: return launch_b<MNMAJ, MNMAJ, EPI_STORE_F32>(a, n, s);
+        case EPI_DZ: return launch_b<KMAJ, MNMAJ, EPI_DZ>(a, n, s);
+        case EPI_STORE: return launch_b<KMAJ, KMAJ, EPI_STORE>(a, n, s);
+        default: return hipErrorNotSupported;
+    }
 }
 
 hipError_t launch_gemm_pp(const GemmArgs& a, hipStream_t s) {

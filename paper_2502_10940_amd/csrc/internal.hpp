@@ -53,20 +53,21 @@ struct GemmArgs {
 
 // Enqueue one GEMM.  Return hipSuccess or the launch error.
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
-// n products of one kind (same tag, all unsplit): the ones routed alike to MID
-// tiles share launches.
+// n products of one kind (same tag, all unsplit), in shared launches where that is
+// faster.
 hipError_t launch_gemm_bf16_batch(const GemmArgs* a, int n, hipStream_t s);
 // The kernel families behind launch_gemm_bf16:
 //   STREAM -- BM x 128 tiles, direct-to-LDS loads, three K stages, two per CU
 //   PP     -- 256 x 256 tiles, two wave groups per workgroup in ping-pong
 hipError_t launch_gemm_stream(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_pp(const GemmArgs& a, hipStream_t s);
-// Two weight-gradient products (both operands m-contiguous, fp32 output) in
-// one PP grid: a0's tiles and splits, then a1's.  Operands as for PP.
-hipError_t launch_gemm_pp_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s);
-// Two weight-gradient products planned for one route: one launch when their
-// operands are aligned (else one launch each, as launch_gemm_bf16).
-hipError_t launch_gemm_bf16_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s);
+// n products of one kind (n <= kMidBatch; both operands m-contiguous and fp32
+// output, or EPI_STORE of k-contiguous operands, or EPI_DZ) in one PP grid, one
+// workgroup per tile and split.
+hipError_t launch_gemm_pp_batch(const GemmArgs* a, int n, hipStream_t s);
+// n weight-gradient products planned for one route (n <= kMidBatch): one launch
+// when their operands are aligned (else one each, as launch_gemm_bf16).
+hipError_t launch_gemm_bf16_wgrads(const GemmArgs* a, int n, hipStream_t s);
 
 //   MID -- 128 x 128, 128 x 64 or 64 x 64 tiles, for outputs too small for PP
 // n products of one kind (same layouts and epilogue) in one launch.
@@ -118,12 +119,15 @@ hipError_t launch_gemm_f32_batch(const GemmArgs* a, int n, hipStream_t s);
 // tb x tb output tiles of an M x N product.
 inline int64_t f32_tiles(int64_t tb, int64_t M, int64_t N) { return ((M + tb - 1) / tb) * ((N + tb - 1) / tb); }
 
-// out[i] = sum_{s < splits} part[s * stride + i], s in increasing order (fp32).
-hipError_t launch_reduce_splits(const float* part, int splits, int64_t stride,
-                                float* out, int64_t n, hipStream_t s);
-// Both at once for two outputs with the same split count (one launch).
-hipError_t launch_reduce_splits2(const float* p0, int64_t st0, float* o0, int64_t n0, const float* p1, int64_t st1,
-                                 float* o1, int64_t n1, int splits, hipStream_t s);
+// out[i] = sum_{k < splits} part[k * n + i], i < n, in a fixed order of k (fp32);
+// up to kReduceBatch of them with one split count in a launch.
+constexpr int kReduceBatch = 4;
+struct ReduceJob {
+    const float* part;
+    float* out;
+    int64_t n;
+};
+hipError_t launch_reduce(const ReduceJob* jobs, int n, int splits, hipStream_t s);
 // dst[r][c] = src[r][c] for c < width, 0 for width <= c < ld (16-bit elements;
 // src rows src_ld apart, any alignment; dst 16-byte aligned, ld a multiple of
 // 8).  Gives operands with odd widths or pitches aligned rows.
