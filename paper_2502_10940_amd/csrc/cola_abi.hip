@@ -242,11 +242,11 @@ Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned, int64_t c
 }
 
 // Split of the fp32 weight gradients that share a launch: a workgroup of 32 x 32
-// tiles takes four K tiles at once in about 0.6 us (two such workgroups a CU
-// before a round costs more), against the reduction's launch (4 us) and partials
-// at about 4 TB/s.
+// tiles takes eight K tiles at once in about 0.9 us (a CU's matrix cores need that
+// long for them), against the reduction's launch (4 us) and partials at about
+// 4 TB/s.
 Split plan_split_f32(const WShape* w, int n, int64_t K, int64_t cap) {
-    const int64_t steps = (K + 4 * F32_BK - 1) / (4 * F32_BK);
+    const int64_t steps = (K + 8 * F32_BK - 1) / (8 * F32_BK);
     if (steps < 1) return Split{1, F32_BK, ROUTE_AUTO};
     double elems = 0.0;
     int64_t tiles = 0;
@@ -254,16 +254,16 @@ Split plan_split_f32(const WShape* w, int n, int64_t K, int64_t cap) {
         elems += (double)w[i].M * (double)w[i].N;
         tiles += f32_tiles(32, w[i].M, w[i].N);
     }
-    Split best{1, steps * 4 * F32_BK, ROUTE_AUTO};
+    Split best{1, steps * 8 * F32_BK, ROUTE_AUTO};
     double best_cost = -1.0;
     for (int64_t s = 1; s <= (steps < cap ? steps : cap); ++s) {
         const int64_t chunk = (steps + s - 1) / s;
         const int64_t eff_s = (steps + chunk - 1) / chunk;
-        const double rounds = (double)((tiles * eff_s + 511) / 512);
-        const double cost = rounds * (double)chunk * 0.6 + (eff_s > 1 ? 4.0 + (double)eff_s * elems * 8.0 / 4.0e6 : 0.0);
+        const double rounds = (double)((tiles * eff_s + 255) / 256);
+        const double cost = rounds * (double)chunk * 0.9 + (eff_s > 1 ? 4.0 + (double)eff_s * elems * 8.0 / 4.0e6 : 0.0);
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
-            best = Split{(int)eff_s, chunk * 4 * F32_BK, ROUTE_AUTO};
+            best = Split{(int)eff_s, chunk * 8 * F32_BK, ROUTE_AUTO};
         }
     }
     return best;

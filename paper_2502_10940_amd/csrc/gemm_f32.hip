@@ -6,10 +6,10 @@
 // What bounds it: the products of this path are small (a few hundred to a few
 // thousand rows), so a launch is a chain of latencies on a mostly idle chip;
 // 32-deep K tiles go global -> registers (one tile ahead) -> LDS -> fragments.
-//  * narrow: 32 x 32 output tiles; the four waves of a workgroup take every
-//    fourth K tile each, through LDS of their own (no barriers in the K loop),
+//  * narrow: 32 x 32 output tiles; the eight waves of a workgroup take every
+//    eighth K tile each, through LDS of their own (no barriers in the K loop),
 //    and their sums are added in wave order at the end.  Fills the chip from
-//    256 tiles of 32 x 32 on and shortens the K chain fourfold.
+//    256 tiles of 32 x 32 on and shortens the K chain eightfold.
 //  * wide: 64 x 64 tiles, each wave a 32 x 32 quarter over all of K, operands
 //    shared through double-buffered LDS: half the traffic per flop.  Used once
 //    256 such tiles (or splits of them) exist.
@@ -43,6 +43,17 @@ struct FTile {
     // rows row0 .., k from k0; zeros past the edges
     __device__ __forceinline__ void load(const float* base, int64_t ld, int64_t row0, int64_t rows, int64_t k0,
                                          int64_t kend, int t) {
+        // whole tiles (a uniform condition): every load in flight at once (guarded
+        // one by one they wait for each other)
+        if (row0 + R <= rows && k0 + BK <= kend) {
+            const float* p = LAYOUT == KMAJ ? base + row0 * ld + k0 : base + k0 * ld + row0;
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int id = t + NT * i;
+                __builtin_memcpy(&v[i], p + (int64_t)(id / CPR) * ld + 4 * (id % CPR), 16);   // 4-byte alignment is enough
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int id = t + NT * i;
@@ -54,7 +65,7 @@ struct FTile {
             if (o < olim) {
                 const float* p = base + o * ld + e;
                 if (e + 4 <= elim) {
-                    __builtin_memcpy(&x, p, 16);                      // 4-byte alignment is enough
+                    __builtin_memcpy(&x, p, 16);
                 } else {
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
@@ -140,32 +151,33 @@ __device__ __forceinline__ void mfma_tile(f32x16_t& acc, const float* ps, const 
     }
 }
 
+constexpr int NWK = 8;                                                // waves that share K (narrow)
+
 template <int PL, int QL, int EPI, bool WIDE>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Batch bt) {
+__global__ __launch_bounds__(WIDE ? 256 : 64 * NWK) void gemm_f32_kernel(const F32Batch bt) {
     constexpr int TB = WIDE ? 64 : 32;
     constexpr int NT = WIDE ? 256 : 64;                               // threads that share an LDS tile
     using TP = FTile<PL, TB, NT>;
     using TQ = FTile<QL, TB, NT>;
     constexpr int STAGE = TP::FLOATS + TQ::FLOATS;
     constexpr int RLD = 36;                                           // narrow: the waves' sums, [wave][32][36]
-    constexpr int TILES = (WIDE ? 2 : 4) * STAGE;
-    constexpr int SMEM = TILES > 4 * 32 * RLD ? TILES : 4 * 32 * RLD;
+    constexpr int TILES = (WIDE ? 2 : NWK) * STAGE;
+    constexpr int SMEM = WIDE || TILES > NWK * 32 * RLD ? TILES : NWK * 32 * RLD;
     __shared__ __attribute__((aligned(16))) float smem[SMEM];
 
-    int64_t b = blockIdx.x;
     int pi = 0;
-    while (pi + 1 < bt.n && b >= bt.first[pi + 1]) ++pi;
+    while (pi + 1 < bt.n && (int64_t)blockIdx.x >= bt.first[pi + 1]) ++pi;
     const GemmArgs& a = bt.a[pi];
-    b -= bt.first[pi];
-    const int64_t tiles_n = (a.N + TB - 1) / TB;
-    const int64_t per_split = tiles_n * ((a.M + TB - 1) / TB);
+    uint32_t b = blockIdx.x - (uint32_t)bt.first[pi];                 // fewer than 2^31 blocks
+    const uint32_t tiles_n = (uint32_t)((a.N + TB - 1) / TB);
+    const uint32_t per_split = tiles_n * (uint32_t)((a.M + TB - 1) / TB);
     int split = 0;
     if (a.splits > 1) {
         split = (int)(b / per_split);
-        b -= (int64_t)split * per_split;
+        b -= (uint32_t)split * per_split;
     }
-    const int64_t tm = b / tiles_n;
-    const int64_t m0 = tm * TB, n0 = (b - tm * tiles_n) * TB;
+    const uint32_t tm = b / tiles_n;
+    const int64_t m0 = (int64_t)tm * TB, n0 = (int64_t)(b - tm * tiles_n) * TB;
     const int64_t kbeg = (int64_t)split * a.k_chunk;
     const int64_t kend = min(a.K, kbeg + a.k_chunk);
     const float* P = reinterpret_cast<const float*>(a.p);
@@ -205,13 +217,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Batch bt) {
         int64_t k0 = kbeg + wave * BK;
         tp.load(P, a.ldp, m0, a.M, k0, kend, lane);
         tq.load(Q, a.ldq, n0, a.N, k0, kend, lane);
-        for (; k0 < kend; k0 += 4 * BK) {
+        for (; k0 < kend; k0 += NWK * BK) {
             // one wave's LDS accesses execute in order: no barrier needed
             tp.put(s, lane);
             tq.put(s + TP::FLOATS, lane);
-            if (k0 + 4 * BK < kend) {
-                tp.load(P, a.ldp, m0, a.M, k0 + 4 * BK, kend, lane);
-                tq.load(Q, a.ldq, n0, a.N, k0 + 4 * BK, kend, lane);
+            if (k0 + NWK * BK < kend) {
+                tp.load(P, a.ldp, m0, a.M, k0 + NWK * BK, kend, lane);
+                tq.load(Q, a.ldq, n0, a.N, k0 + NWK * BK, kend, lane);
             }
             __builtin_amdgcn_wave_barrier();
             mfma_tile<TP, TQ>(acc, s, s + TP::FLOATS, 0, 0, lane);
@@ -223,10 +235,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32Batch bt) {
             *reinterpret_cast<f32x4_t*>(smem + (32 * wave + (lane & 31)) * RLD + 8 * g + 4 * (lane >> 5)) =
                 f32x4_t{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
         __syncthreads();
+        if (threadIdx.x >= 256) return;
         const int r = threadIdx.x >> 3, c = 4 * (threadIdx.x & 7);
         f32x4_t x = *reinterpret_cast<const f32x4_t*>(smem + r * RLD + c);
 #pragma unroll
-        for (int w = 1; w < 4; ++w) x += *reinterpret_cast<const f32x4_t*>(smem + (32 * w + r) * RLD + c);
+        for (int w = 1; w < NWK; ++w) x += *reinterpret_cast<const f32x4_t*>(smem + (32 * w + r) * RLD + c);
         epilogue<EPI>(a, split, m0 + r, n0 + c, x);
     }
 }
@@ -251,7 +264,7 @@ hipError_t launch_t(const GemmArgs* a, int n, hipStream_t s) {
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     if (wide) hipLaunchKernelGGL((gemm_f32_kernel<PL, QL, EPI, true>), dim3((unsigned)blocks), dim3(256), 0, s, bt);
-    else hipLaunchKernelGGL((gemm_f32_kernel<PL, QL, EPI, false>), dim3((unsigned)blocks), dim3(256), 0, s, bt);
+    else hipLaunchKernelGGL((gemm_f32_kernel<PL, QL, EPI, false>), dim3((unsigned)blocks), dim3(64 * NWK), 0, s, bt);
     return hipGetLastError();
 }
 
