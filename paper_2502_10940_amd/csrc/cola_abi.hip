@@ -11,6 +11,7 @@
 //              K6  dB partials = dY^T H             (split over tokens)
 //                  (K5 and K6 in one launch, one split of T for both)
 //              K7  dA, dB = fixed-order sums of the partials
+//                  (small layers: K4, K5 and K6 in one launch)
 //   dense    : Y = X W^T ; dX = dY W ; dW = dY^T X (split over tokens + K7)
 #include <mutex>
 #include <new>
@@ -460,12 +461,26 @@ struct WProd {
 };
 
 // n weight gradients (n <= kWSet) over K = T in one launch with one split, then
-// the fixed-order reductions of their partials in another.
+// the fixed-order reductions of their partials in another.  `dx`: the dX = dZ A
+// product not yet launched; it joins the launch where that is faster, or goes
+// first in one of its own (bytes: its own traffic).
 constexpr int kWSet = 4;
 static_assert(kWSet <= kMidBatch && kWSet <= kF32Batch && kWSet <= kReduceBatch, "a set is one launch");
 
-int wgrads(bool bf16, int64_t T, const Split& sp, const WProd* w, int n, hipStream_t s) {
-    GemmArgs a[kWSet];
+struct DxProd {
+    GemmArgs a;
+    double bytes;
+};
+
+int launch_dx(bool bf16, const DxProd& dx, hipStream_t s) {
+    const hipError_t e = timed(COLA_KC_BWD_DX, gemm_flops(dx.a.M, dx.a.N, dx.a.K), dx.bytes, s,
+                               [&] { return gemm(dx.a, bf16, s); });
+    return e == hipSuccess ? COLA_OK : hip_fail(e, "bwd_dx");
+}
+
+int wgrads(bool bf16, int64_t T, const Split& sp, const WProd* w, int n, hipStream_t s, const DxProd* dx = nullptr) {
+    GemmArgs all[kWSet + 1];
+    GemmArgs* const a = all + 1;
     ReduceJob red[kWSet];
     double flops = 0.0, elems = 0.0, in = 0.0;
     for (int i = 0; i < n; ++i) {
@@ -484,8 +499,21 @@ int wgrads(bool bf16, int64_t T, const Split& sp, const WProd* w, int n, hipStre
         elems += (double)w[i].M * (double)w[i].N;
         in += (bf16 ? 2.0 : 4.0) * (double)T * (double)(w[i].M + w[i].N);
     }
-    const int kc = n > 1 ? (int)COLA_KC_BWD_DADB : w[0].kc;
+    bool joined = false;
+    if (dx) {
+        all[0] = dx->a;
+        joined = bf16 ? bf16_dxw_takes(all, n + 1) : f32_dxw_takes(all, n + 1);
+        if (!joined) {
+            const int st = launch_dx(bf16, *dx, s);
+            if (st != COLA_OK) return st;
+        } else {
+            flops += gemm_flops(dx->a.M, dx->a.N, dx->a.K);
+            in += dx->bytes;
+        }
+    }
+    const int kc = n > 1 || joined ? (int)COLA_KC_BWD_DADB : w[0].kc;
     hipError_t e = timed(kc, flops, in + elems * 4.0 * sp.splits, s, [&] {
+        if (joined) return bf16 ? launch_gemm_bf16_dxw(all, n + 1, s) : launch_gemm_f32_dxw(all, n + 1, s);
         if (!bf16) return launch_gemm_f32_batch(a, n, s);
         return n > 1 ? launch_gemm_bf16_wgrads(a, n, s) : launch_gemm_bf16(a[0], s);
     });
@@ -623,15 +651,20 @@ int layer_backward(const Dims& x, const BwdPlan& p, int act, bool recompute, con
             b4 = es * ((double)x.T * x.r + (double)x.r * x.d_in + 4.0 * x.T * x.d_in);
         }
     }
-    e = timed(COLA_KC_BWD_DX, gemm_flops(x.T, x.d_in, x.r), b4, s, [&] { return gemm(k4, x.bf16, s); });
-    if (e != hipSuccess) return hip_fail(e, "bwd_dx");
+    const DxProd dxp{k4, b4};
+    const bool alone = k4.epi != EPI_STORE;                    // the gated products have a launch of their own
+    if (alone) {
+        const int st = launch_dx(x.bf16, dxp, s);
+        if (st != COLA_OK) return st;
+    }
+    const DxProd* const with = alone ? nullptr : &dxp;
 
     // K5: dA = dZ^T X ; K6: dB = dY^T H  (+ K7 fixed-order reductions); one launch
     // for both where planned
     const WProd wp[2] = {{x.r, x.d_in, dZ, X, p.ldw, ldx, dA, reinterpret_cast<float*>(w + p.off_pa), COLA_KC_BWD_DA},
                          {x.d_out, x.r, dY, Hbuf, ldy, ldh, dB, reinterpret_cast<float*>(w + p.off_pb), COLA_KC_BWD_DB}};
-    if (p.pair) return wgrads(x.bf16, x.T, p.sa, wp, 2, s);
-    const int st = wgrads(x.bf16, x.T, p.sa, wp, 1, s);
+    if (p.pair) return wgrads(x.bf16, x.T, p.sa, wp, 2, s, with);
+    const int st = wgrads(x.bf16, x.T, p.sa, wp, 1, s, with);
     return st != COLA_OK ? st : wgrads(x.bf16, x.T, p.sb, wp + 1, 1, s);
 }
 
@@ -1456,8 +1489,7 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
         GemmArgs k4 = make_args(TAG_BWD_DX, g.T, g.d_in, g.R, dZ, p.ldw, KMAJ, Aw, lda, MNMAJ, dX, g.ldx, EPI_STORE,
                                 desc->act);
         const double b4 = es * ((double)g.T * g.R + (double)g.R * g.d_in + (double)g.T * g.d_in);
-        e = timed(COLA_KC_BWD_DX, gemm_flops(g.T, g.d_in, g.R), b4, s, [&] { return gemm(k4, g.bf16, s); });
-        if (e != hipSuccess) return hip_fail(e, "bwd_dx");
+        const DxProd dxp{k4, b4};
 
         // K5 for every projection at once, dA_all = dZ_all^T X (product 0),
         // and K6 per projection, dB_p = dY_p^T H_p (product 1 + p), in sets
@@ -1477,12 +1509,12 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
                 wp[k] = WProd{g.d_out[q], g.r[q], dYw[q], Hw, p.py[q].ld, p.ph[q].ld, dB[q], part, COLA_KC_BWD_DB};
             }
             if (p.set[w0]) {
-                st = wgrads(g.bf16, g.T, p.sp[w0], wp, cnt, s);
+                st = wgrads(g.bf16, g.T, p.sp[w0], wp, cnt, s, w0 == 0 ? &dxp : nullptr);
                 if (st != COLA_OK) return st;
                 continue;
             }
             for (int k = 0; k < cnt; ++k) {
-                st = wgrads(g.bf16, g.T, p.sp[w0 + k], wp + k, 1, s);
+                st = wgrads(g.bf16, g.T, p.sp[w0 + k], wp + k, 1, s, w0 + k == 0 ? &dxp : nullptr);
                 if (st != COLA_OK) return st;
             }
         }

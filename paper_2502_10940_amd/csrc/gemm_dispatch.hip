@@ -167,6 +167,22 @@ hipError_t launch_gemm_bf16_wgrads(const GemmArgs* a, int n, hipStream_t s) {
     return hipSuccess;
 }
 
+// While all tiles of the weight gradients' route run at once (two workgroups a
+// CU): a launch less, and either part fills the CUs the other leaves idle.
+bool bf16_dxw_takes(const GemmArgs* a, int n) {
+    if (n > kMidBatch || (a[1].route != ROUTE_MID_128x64 && a[1].route != ROUTE_MID_64x64)) return false;
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) {
+        if (!operands_ok(a[i]) || (i > 0 && a[i].route != a[1].route)) return false;
+        tiles += route_tiles(a[1].route, a[i].M, a[i].N) * a[i].splits;
+    }
+    return tiles <= 512 && !g_force_stream.load(std::memory_order_relaxed);
+}
+
+hipError_t launch_gemm_bf16_dxw(const GemmArgs* a, int n, hipStream_t s) {
+    return launch_gemm_mid_dxw(a, n, a[1].route - ROUTE_MID_128x128, s);
+}
+
 hipError_t launch_gemm_bf16_batch(const GemmArgs* a, int n, hipStream_t s) {
     int64_t K = 0;
     bool skinny = n > 1, ok = n > 1 && n <= kMidBatch && !g_force_stream.load(std::memory_order_relaxed);

@@ -153,22 +153,32 @@ __device__ __forceinline__ void mfma_tile(f32x16_t& acc, const float* ps, const 
 
 constexpr int NWK = 8;                                                // waves that share K (narrow)
 
+// LDS floats of a workgroup; narrow: also room for the waves' sums,
+// [wave][32][RLD].
+constexpr int RLD = 36;
+template <int PL, int QL, bool WIDE>
+constexpr int f32_smem() {
+    constexpr int TB = WIDE ? 64 : 32, NT = WIDE ? 256 : 64;
+    constexpr int tiles = (WIDE ? 2 : NWK) * (FTile<PL, TB, NT>::FLOATS + FTile<QL, TB, NT>::FLOATS);
+    return WIDE || tiles > NWK * 32 * RLD ? tiles : NWK * 32 * RLD;
+}
+
+// This block's product, and its number within it.
+__device__ __forceinline__ uint32_t f32_block(const F32Batch& bt, int* product) {
+    int pi = 0;
+    while (pi + 1 < bt.n && (int64_t)blockIdx.x >= bt.first[pi + 1]) ++pi;
+    *product = pi;
+    return blockIdx.x - (uint32_t)bt.first[pi];                       // fewer than 2^31 blocks
+}
+
+// Output tile (and split) number b of the product a.
 template <int PL, int QL, int EPI, bool WIDE>
-__global__ __launch_bounds__(WIDE ? 256 : 64 * NWK) void gemm_f32_kernel(const F32Batch bt) {
+__device__ __forceinline__ void f32_tile(const GemmArgs& a, uint32_t b, float* smem) {
     constexpr int TB = WIDE ? 64 : 32;
     constexpr int NT = WIDE ? 256 : 64;                               // threads that share an LDS tile
     using TP = FTile<PL, TB, NT>;
     using TQ = FTile<QL, TB, NT>;
     constexpr int STAGE = TP::FLOATS + TQ::FLOATS;
-    constexpr int RLD = 36;                                           // narrow: the waves' sums, [wave][32][36]
-    constexpr int TILES = (WIDE ? 2 : NWK) * STAGE;
-    constexpr int SMEM = WIDE || TILES > NWK * 32 * RLD ? TILES : NWK * 32 * RLD;
-    __shared__ __attribute__((aligned(16))) float smem[SMEM];
-
-    int pi = 0;
-    while (pi + 1 < bt.n && (int64_t)blockIdx.x >= bt.first[pi + 1]) ++pi;
-    const GemmArgs& a = bt.a[pi];
-    uint32_t b = blockIdx.x - (uint32_t)bt.first[pi];                 // fewer than 2^31 blocks
     const uint32_t tiles_n = (uint32_t)((a.N + TB - 1) / TB);
     const uint32_t per_split = tiles_n * (uint32_t)((a.M + TB - 1) / TB);
     int split = 0;
@@ -244,14 +254,36 @@ __global__ __launch_bounds__(WIDE ? 256 : 64 * NWK) void gemm_f32_kernel(const F
     }
 }
 
+template <int PL, int QL, int EPI, bool WIDE>
+__global__ __launch_bounds__(WIDE ? 256 : 64 * NWK) void gemm_f32_kernel(const F32Batch bt) {
+    __shared__ __attribute__((aligned(16))) float smem[f32_smem<PL, QL, WIDE>()];
+    int pi;
+    const uint32_t b = f32_block(bt, &pi);
+    f32_tile<PL, QL, EPI, WIDE>(bt.a[pi], b, smem);
+}
+
+// dX = dZ A (product 0) and the weight gradients (the rest), which both follow
+// from dZ, in one grid.
+__global__ __launch_bounds__(64 * NWK) void gemm_f32_dxw_kernel(const F32Batch bt) {
+    constexpr int S0 = f32_smem<KMAJ, MNMAJ, false>(), S1 = f32_smem<MNMAJ, MNMAJ, false>();
+    __shared__ __attribute__((aligned(16))) float smem[S0 > S1 ? S0 : S1];
+    int pi;
+    const uint32_t b = f32_block(bt, &pi);
+    if (pi == 0) f32_tile<KMAJ, MNMAJ, EPI_STORE, false>(bt.a[0], b, smem);
+    else f32_tile<MNMAJ, MNMAJ, EPI_STORE_F32, false>(bt.a[pi], b, smem);
+}
+
+bool f32_wide(const GemmArgs* a, int n) {
+    int64_t t64 = 0;
+    for (int i = 0; i < n; ++i) t64 += f32_tiles(64, a[i].M, a[i].N) * a[i].splits;
+    return t64 >= 256;
+}
+
 template <int PL, int QL, int EPI>
 hipError_t launch_t(const GemmArgs* a, int n, hipStream_t s) {
-    int64_t t64 = 0;
-    for (int i = 0; i < n; ++i) {
+    for (int i = 0; i < n; ++i)
         if (a[i].p_layout != PL || a[i].q_layout != QL || a[i].epi != EPI) return hipErrorInvalidValue;
-        t64 += f32_tiles(64, a[i].M, a[i].N) * a[i].splits;
-    }
-    const bool wide = t64 >= 256;
+    const bool wide = f32_wide(a, n);
     F32Batch bt;
     bt.n = n;
     int64_t blocks = 0;
@@ -294,6 +326,28 @@ hipError_t launch_gemm_f32_batch(const GemmArgs* a, int n, hipStream_t s) {
             break;
     }
     return hipErrorNotSupported;
+}
+
+bool f32_dxw_takes(const GemmArgs* a, int n) { return n <= kF32Batch && !f32_wide(a, 1) && !f32_wide(a + 1, n - 1); }
+
+hipError_t launch_gemm_f32_dxw(const GemmArgs* a, int n, hipStream_t s) {
+    if (n < 2 || n > kF32Batch) return hipErrorInvalidValue;
+    F32Batch bt;
+    bt.n = n;
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        if (a[i].p_layout != (i == 0 ? KMAJ : MNMAJ) || a[i].q_layout != MNMAJ ||
+            a[i].epi != (i == 0 ? EPI_STORE : EPI_STORE_F32))
+            return hipErrorInvalidValue;
+        bt.a[i] = a[i];
+        bt.first[i] = blocks;
+        blocks += f32_tiles(32, a[i].M, a[i].N) * a[i].splits;
+    }
+    for (int i = n; i <= kF32Batch; ++i) bt.first[i] = blocks;
+    if (blocks <= 0) return hipSuccess;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(gemm_f32_dxw_kernel, dim3((unsigned)blocks), dim3(64 * NWK), 0, s, bt);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

@@ -144,8 +144,27 @@ struct MidBatch {
     int n;
 };
 
-template <int BM, int BN, int NS, int OCC, int PL, int QL, int EPI>
-__global__ __launch_bounds__(NTHR, OCC) void gemm_mid_kernel(const MidBatch bt) {
+// LDS of a workgroup.
+template <int BM, int BN, int NS>
+constexpr int mid_smem_bytes() {
+    return NS * (BM + BN) * 128;
+}
+
+// This block's number with an XCD-aware renumbering (block b runs on XCD b % 8):
+// contiguous tiles per XCD; and the product it falls in.
+__device__ __forceinline__ int mid_block(const MidBatch& bt, int* product) {
+    const int nb = (int)gridDim.x;
+    int b = (int)blockIdx.x;
+    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+    int pi = 0;
+    while (pi + 1 < bt.n && b >= bt.first[pi + 1]) ++pi;
+    *product = pi;
+    return b - bt.first[pi];
+}
+
+// Output tile (and split) number b of the product a.
+template <int BM, int BN, int NS, int PL, int QL, int EPI>
+__device__ __forceinline__ void mid_tile(const GemmArgs& a, int b, char* smem) {
     using TP = MTile<BM, PL>;
     using TQ = MTile<BN, QL>;
     constexpr int TM = BM / 64, TN = BN / 64;                  // 32 x 32 tiles per wave
@@ -153,16 +172,6 @@ __global__ __launch_bounds__(NTHR, OCC) void gemm_mid_kernel(const MidBatch bt) 
     constexpr int OPS = TP::DPW + TQ::DPW;                     // loads per wave per K tile
     constexpr int NMFMA = NSUB * TM * TN;
     constexpr int NFRAG = NSUB * (TM + TN);
-    __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
-
-    // XCD-aware renumbering (block b runs on XCD b % 8): contiguous tiles per XCD
-    const int nb = (int)gridDim.x;
-    int b = (int)blockIdx.x;
-    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
-    int pi = 0;
-    while (pi + 1 < bt.n && b >= bt.first[pi + 1]) ++pi;
-    const GemmArgs& a = bt.a[pi];
-    b -= bt.first[pi];
 
     const int tiles_n = (int)((a.N + BN - 1) / BN);
     const int per_split = tiles_n * (int)((a.M + BM - 1) / BM);
@@ -320,20 +329,61 @@ __global__ __launch_bounds__(NTHR, OCC) void gemm_mid_kernel(const MidBatch bt) 
 }
 
 template <int BM, int BN, int NS, int OCC, int PL, int QL, int EPI>
-hipError_t launch_t(const GemmArgs* a, int n, hipStream_t s) {
-    MidBatch bt;
+__global__ __launch_bounds__(NTHR, OCC) void gemm_mid_kernel(const MidBatch bt) {
+    __shared__ __attribute__((aligned(1024))) char smem[mid_smem_bytes<BM, BN, NS>()];
+    int pi;
+    const int b = mid_block(bt, &pi);
+    mid_tile<BM, BN, NS, PL, QL, EPI>(bt.a[pi], b, smem);
+}
+
+// dX = dZ A (product 0) and the weight gradients (the rest), which both follow
+// from dZ, in one grid.
+template <int BM, int BN, int NS, int OCC>
+__global__ __launch_bounds__(NTHR, OCC) void gemm_mid_dxw_kernel(const MidBatch bt) {
+    __shared__ __attribute__((aligned(1024))) char smem[mid_smem_bytes<BM, BN, NS>()];
+    int pi;
+    const int b = mid_block(bt, &pi);
+    if (pi == 0) mid_tile<BM, BN, NS, KMAJ, MNMAJ, EPI_STORE>(bt.a[0], b, smem);
+    else mid_tile<BM, BN, NS, MNMAJ, MNMAJ, EPI_STORE_F32>(bt.a[pi], b, smem);
+}
+
+// The batch and its block count (0: nothing to do).
+hipError_t fill_batch(MidBatch& bt, const GemmArgs* a, int n, int bm, int bn, int64_t* blocks) {
     bt.n = n;
-    int64_t blocks = 0;
+    *blocks = 0;
     for (int i = 0; i < n; ++i) {
-        if (a[i].p_layout != PL || a[i].q_layout != QL || a[i].epi != EPI) return hipErrorInvalidValue;
         bt.a[i] = a[i];
-        bt.first[i] = (int)blocks;
-        blocks += ((a[i].M + BM - 1) / BM) * ((a[i].N + BN - 1) / BN) * (int64_t)a[i].splits;
-        if (blocks >= kMidBatch * kMidMaxBlocks) return hipErrorInvalidConfiguration;
+        bt.first[i] = (int)*blocks;
+        *blocks += ((a[i].M + bm - 1) / bm) * ((a[i].N + bn - 1) / bn) * (int64_t)a[i].splits;
+        if (*blocks >= kMidBatch * kMidMaxBlocks) return hipErrorInvalidConfiguration;
     }
-    if (blocks <= 0) return hipSuccess;
-    for (int i = n; i <= kMidBatch; ++i) bt.first[i] = (int)blocks;
+    for (int i = n; i <= kMidBatch; ++i) bt.first[i] = (int)*blocks;
+    return hipSuccess;
+}
+
+template <int BM, int BN, int NS, int OCC, int PL, int QL, int EPI>
+hipError_t launch_t(const GemmArgs* a, int n, hipStream_t s) {
+    for (int i = 0; i < n; ++i)
+        if (a[i].p_layout != PL || a[i].q_layout != QL || a[i].epi != EPI) return hipErrorInvalidValue;
+    MidBatch bt;
+    int64_t blocks;
+    const hipError_t e = fill_batch(bt, a, n, BM, BN, &blocks);
+    if (e != hipSuccess || blocks == 0) return e;
     hipLaunchKernelGGL((gemm_mid_kernel<BM, BN, NS, OCC, PL, QL, EPI>), dim3((unsigned)blocks), dim3(NTHR), 0, s, bt);
+    return hipGetLastError();
+}
+
+template <int BM, int BN, int NS, int OCC>
+hipError_t launch_dxw(const GemmArgs* a, int n, hipStream_t s) {
+    for (int i = 0; i < n; ++i)
+        if (a[i].p_layout != (i == 0 ? KMAJ : MNMAJ) || a[i].q_layout != MNMAJ ||
+            a[i].epi != (i == 0 ? EPI_STORE : EPI_STORE_F32))
+            return hipErrorInvalidValue;
+    MidBatch bt;
+    int64_t blocks;
+    const hipError_t e = fill_batch(bt, a, n, BM, BN, &blocks);
+    if (e != hipSuccess || blocks == 0) return e;
+    hipLaunchKernelGGL((gemm_mid_dxw_kernel<BM, BN, NS, OCC>), dim3((unsigned)blocks), dim3(NTHR), 0, s, bt);
     return hipGetLastError();
 }
 
@@ -362,6 +412,15 @@ hipError_t launch_gemm_mid(const GemmArgs* a, int n, int tile, hipStream_t s) {
             return a[0].q_layout == KMAJ ? launch_l<KMAJ, KMAJ, EPI_STORE>(a, n, tile, s)
                                          : launch_l<KMAJ, MNMAJ, EPI_STORE>(a, n, tile, s);
         default: return hipErrorNotSupported;
+    }
+}
+
+hipError_t launch_gemm_mid_dxw(const GemmArgs* a, int n, int tile, hipStream_t s) {
+    if (n < 2 || n > kMidBatch) return hipErrorInvalidValue;
+    switch (tile) {
+        case MID_128x64: return launch_dxw<128, 64, 3, 2>(a, n, s);
+        case MID_64x64: return launch_dxw<64, 64, 4, 2>(a, n, s);
+        default: return hipErrorInvalidValue;
     }
 }
 

@@ -68,6 +68,10 @@ hipError_t launch_gemm_pp_batch(const GemmArgs* a, int n, hipStream_t s);
 // n weight-gradient products planned for one route (n <= kMidBatch): one launch
 // when their operands are aligned (else one each, as launch_gemm_bf16).
 hipError_t launch_gemm_bf16_wgrads(const GemmArgs* a, int n, hipStream_t s);
+// dX = dZ A (a[0]) and the weight gradients a[1 ..] in one launch: whether that is
+// the faster way, and the launch.
+bool bf16_dxw_takes(const GemmArgs* a, int n);
+hipError_t launch_gemm_bf16_dxw(const GemmArgs* a, int n, hipStream_t s);
 
 //   MID -- 128 x 128, 128 x 64 or 64 x 64 tiles, for outputs too small for PP
 // n products of one kind (same layouts and epilogue) in one launch.
@@ -78,6 +82,9 @@ constexpr int64_t kSkinnyRows = 64;
 hipError_t launch_gemm_skinny(const GemmArgs* a, int n, hipStream_t s);
 // Whether the forward products of M tokens run there.
 bool skinny_rows(int64_t M);
+// dX = dZ A (a[0]) and the weight gradients a[1 ..] of a small layer in one grid
+// (MID_128x64 or MID_64x64).
+hipError_t launch_gemm_mid_dxw(const GemmArgs* a, int n, int tile, hipStream_t s);
 enum MidTile : int { MID_128x128 = 0, MID_128x64 = 1, MID_64x64 = 2 };
 constexpr int kMidBatch = 4;
 constexpr int64_t kMidMaxBlocks = int64_t(1) << 20;
@@ -116,6 +123,10 @@ int get_option(int option);
 // fp32 storage: n products of one kind (same layouts and epilogue) in one launch.
 constexpr int kF32Batch = 4;
 hipError_t launch_gemm_f32_batch(const GemmArgs* a, int n, hipStream_t s);
+// dX = dZ A (a[0]) and the weight gradients a[1 ..] of a small layer in one grid of
+// 32 x 32 tiles, and whether both parts would use that tile anyway.
+bool f32_dxw_takes(const GemmArgs* a, int n);
+hipError_t launch_gemm_f32_dxw(const GemmArgs* a, int n, hipStream_t s);
 // tb x tb output tiles of an M x N product.
 inline int64_t f32_tiles(int64_t tb, int64_t M, int64_t N) { return ((M + tb - 1) / tb) * ((N + tb - 1) / tb); }
 
