@@ -412,9 +412,10 @@ BwdPlan plan_bwd(const Dims& x, bool recompute, bool copies = true, int64_t cap 
 
 // The plan that `ws_bytes` has room for: with copies of unaligned rows, or the
 // lean one (which is refused if that is too large as well).
-template <class Plan>
-Plan fitting(size_t ws_bytes, Plan full, Plan lean) {
-    return ws_bytes >= full.total ? full : lean;
+template <class F>
+auto fitting(size_t ws_bytes, F&& plan) {
+    const auto full = plan(true);
+    return ws_bytes >= full.total ? full : plan(false);
 }
 
 hipError_t gemm(const GemmArgs& a, bool bf16, hipStream_t s) {
@@ -690,7 +691,7 @@ int bwd_checked(const cola_desc* desc, const void* dY, const void* X, const void
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (x.T == 0) return zero_weight_grads(x, dA, dB, s);
     if (!dY || !X || !Z || !A || !B || !dX) return COLA_ERR_INVALID_ARG;
-    const BwdPlan p = fitting(ws_bytes, plan_bwd(x, recompute), plan_bwd(x, recompute, false));
+    const BwdPlan p = fitting(ws_bytes, [&](bool copies) { return plan_bwd(x, recompute, copies); });
     if (!ws || ws_bytes < p.total) return COLA_ERR_WORKSPACE;
     return layer_backward(x, p, desc->act, recompute, dY, X, Z, H, A, B, dX, dA, dB,
                           reinterpret_cast<char*>(ws), s, gate);
@@ -801,7 +802,7 @@ int cola_fwd(const cola_desc* desc, const void* X, const void* A, const void* B,
         if (recompute ? (H != nullptr) : (H == nullptr && x.T > 0)) return COLA_ERR_INVALID_ARG;
         if (x.T == 0) return COLA_OK;
         if (!X || !A || !B || !Y || !Z) return COLA_ERR_INVALID_ARG;
-        const FwdPlan p = fitting(ws ? ws_bytes : 0, plan_fwd(x, recompute), plan_fwd(x, recompute, false));
+        const FwdPlan p = fitting(ws ? ws_bytes : 0, [&](bool copies) { return plan_fwd(x, recompute, copies); });
         if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
         return layer_forward(x, p, desc->act, recompute, X, A, B, Y, Z, H, -1, nullptr, reinterpret_cast<char*>(ws),
                              reinterpret_cast<hipStream_t>(stream));
@@ -819,7 +820,7 @@ int cola_fwd_outer(const cola_desc* desc, int outer_act, const void* X, const vo
         if (recompute ? (H != nullptr) : (H == nullptr && x.T > 0)) return COLA_ERR_INVALID_ARG;
         if (x.T == 0) return COLA_OK;
         if (!X || !A || !B || !Y || !P || !Z) return COLA_ERR_INVALID_ARG;
-        const FwdPlan p = fitting(ws ? ws_bytes : 0, plan_fwd(x, recompute), plan_fwd(x, recompute, false));
+        const FwdPlan p = fitting(ws ? ws_bytes : 0, [&](bool copies) { return plan_fwd(x, recompute, copies); });
         if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
         return layer_forward(x, p, desc->act, recompute, X, A, B, Y, Z, H, outer_act, P, reinterpret_cast<char*>(ws),
                              reinterpret_cast<hipStream_t>(stream));
@@ -933,7 +934,7 @@ int cola_bwd_scratch(const cola_desc* desc, const void* dY, const void* X, const
         if (x.T == 0) return zero_weight_grads(x, dA, dB, s);
         if (!dY || !X || !Z || !A || !B || !dX) return COLA_ERR_INVALID_ARG;
         if (scratch_demand(x, recompute) > COLA_SCRATCH_BYTES) return COLA_ERR_SCRATCH;
-        BwdPlan p = fitting(COLA_SCRATCH_BYTES, plan_bwd(x, recompute), plan_bwd(x, recompute, false));
+        BwdPlan p = fitting(COLA_SCRATCH_BYTES, [&](bool copies) { return plan_bwd(x, recompute, copies); });
         // fewer splits where their partials do not fit (with one split the rest
         // is part of the demand)
         for (int64_t cap = kMaxSplits / 2; p.total > COLA_SCRATCH_BYTES && cap >= 1; cap /= 2)
@@ -961,7 +962,7 @@ int cola_bwd_outer(const cola_desc* desc, int outer_act, const void* dY, const v
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         if (x.T == 0) return zero_weight_grads(x, dA, dB, s);
         if (!dY || !P || !X || !Z || !A || !B || !dX) return COLA_ERR_INVALID_ARG;
-        const OuterPlan o = fitting(ws_bytes, plan_outer_bwd(x, recompute), plan_outer_bwd(x, recompute, false));
+        const OuterPlan o = fitting(ws_bytes, [&](bool copies) { return plan_outer_bwd(x, recompute, copies); });
         if (!ws || ws_bytes < o.total) return COLA_ERR_WORKSPACE;
         char* w = reinterpret_cast<char*>(ws);
         // dP = dY (.) sigma_out'(P), rounded to the storage dtype like dZ
@@ -1374,7 +1375,7 @@ int group_fwd_checked(const cola_group_desc* desc, const void* X, const void* A_
     if (!X || !A_all || !B || !Y || !Z_all) return COLA_ERR_INVALID_ARG;
     for (int q = 0; q < g.n; ++q)
         if (!B[q] || !Y[q]) return COLA_ERR_INVALID_ARG;
-    const GFwdPlan p = fitting(ws ? ws_bytes : 0, plan_group_fwd(g, recompute), plan_group_fwd(g, recompute, false));
+    const GFwdPlan p = fitting(ws ? ws_bytes : 0, [&](bool copies) { return plan_group_fwd(g, recompute, copies); });
     if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
     return group_forward(g, p, desc->act, X, A_all, B, Y, Z_all, H_all, recompute, reinterpret_cast<char*>(ws),
                          reinterpret_cast<hipStream_t>(stream), gate);
@@ -1386,7 +1387,7 @@ int infer_checked(const GDims& g, int act, const void* X, const void* A_all, con
     if (!X || !A_all || !B || !Y) return COLA_ERR_INVALID_ARG;
     for (int q = 0; q < g.n; ++q)
         if (!B[q] || !Y[q]) return COLA_ERR_INVALID_ARG;
-    const GFwdPlan p = fitting(ws ? ws_bytes : 0, plan_group_fwd(g, true), plan_group_fwd(g, true, false));
+    const GFwdPlan p = fitting(ws ? ws_bytes : 0, [&](bool copies) { return plan_group_fwd(g, true, copies); });
     if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
     return group_forward(g, p, act, X, A_all, B, Y, nullptr, nullptr, true, reinterpret_cast<char*>(ws),
                          reinterpret_cast<hipStream_t>(stream));
@@ -1450,7 +1451,7 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
         if (!dY || !X_in || !Z_all || !A_all || !B || !dX) return COLA_ERR_INVALID_ARG;
         for (int q = 0; q < g.n; ++q)
             if (!dY[q] || !B[q]) return COLA_ERR_INVALID_ARG;
-        const GBwdPlan p = fitting(ws_bytes, plan_group_bwd(g, recompute), plan_group_bwd(g, recompute, false));
+        const GBwdPlan p = fitting(ws_bytes, [&](bool copies) { return plan_group_bwd(g, recompute, copies); });
         if (!ws || ws_bytes < p.total) return COLA_ERR_WORKSPACE;
 
         char* w = reinterpret_cast<char*>(ws);
