@@ -7,13 +7,12 @@
 //  * MID (gemm_mid.hip): 128 x 128, 128 x 64 or 64 x 64 tiles, for outputs
 //    that would leave most CUs without a 256 x 256 tile (token batches of a few
 //    thousand, products of width r).
-//  * SKINNY (gemm_skinny.hip): the forward products of at most 64 tokens.
+//  * SKINNY (gemm_skinny.hip): the forward products of at most 32 tokens.
 //  * STREAM (gemm_stream.hip): BM x 128 tiles; operands without 16-byte aligned
 //    rows.
-// PP and MID need 16-byte aligned rows.  Both sum over k in increasing order
-// (as STREAM does with unaligned operands), so the choice among them never
-// changes a bit of an unsplit product's result; SKINNY has an order of its own,
-// and which products it takes depends on the token count and the step alone.
+// PP and MID need 16-byte aligned rows.  They and SKINNY sum over k in increasing
+// order (as STREAM does with unaligned operands), so the choice among them never
+// changes a bit of an unsplit product's result.
 #include <atomic>
 
 #include "internal.hpp"
@@ -116,8 +115,10 @@ static bool operands_ok(const GemmArgs& a) {
     return al(a.p, a.ldp) && al(a.q, a.ldq);
 }
 
-// Up to 64 tokens: one token of a 1B projection 8.6 us of kernels against 14.3
-// with 64 x 64 tiles, 32 tokens of 7B q, k, v 17 against 34.
+// Up to 32 tokens: one token of a 1B projection 9.4 us of kernels against 14.3
+// with 64 x 64 tiles, 32 tokens of 7B q, k, v 18.6 against 34.  With a 64-row variant
+// of the kernel, 48 tokens of a 1B projection took 14.2 us against 13.5 with MID
+// tiles, of 7B 20.9 against 20.1, of 7B gate and up 32.9 against 24.8.
 bool skinny_rows(int64_t M) { return M <= kSkinnyRows && !g_force_stream.load(std::memory_order_relaxed); }
 
 static bool skinny_takes(const GemmArgs& a) {
@@ -148,12 +149,7 @@ static hipError_t launch_route(const GemmArgs* a, int n, int route, hipStream_t 
     return hipSuccess;
 }
 
-// Not where the plain product would run in SKINNY: its sums have their own order,
-// and the fused and separate gated products must give the same bits.
-bool fused_epilogue_takes(const GemmArgs& a) {
-    if (a.tag == TAG_FWD_YG && skinny_rows(a.M)) return false;
-    return route_of(a) != ROUTE_STREAM;
-}
+bool fused_epilogue_takes(const GemmArgs& a) { return route_of(a) != ROUTE_STREAM; }
 
 hipError_t launch_gemm_bf16_wgrads(const GemmArgs* a, int n, hipStream_t s) {
     bool alike = n <= kMidBatch;

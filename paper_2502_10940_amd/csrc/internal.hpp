@@ -76,9 +76,9 @@ hipError_t launch_gemm_bf16_dxw(const GemmArgs* a, int n, hipStream_t s);
 //   MID -- 128 x 128, 128 x 64 or 64 x 64 tiles, for outputs too small for PP
 // n products of one kind (same layouts and epilogue) in one launch.
 //   SKINNY -- at most kSkinnyRows token rows against weight rows (both
-//   k-contiguous, any alignment), K shared by a workgroup's waves; n products
-//   of one kind and the same tokens in one launch (n <= kMidBatch).
-constexpr int64_t kSkinnyRows = 64;
+//   k-contiguous, any alignment); n products of one kind and the same tokens in
+//   one launch (n <= kMidBatch).
+constexpr int64_t kSkinnyRows = 32;
 hipError_t launch_gemm_skinny(const GemmArgs* a, int n, hipStream_t s);
 // Whether the forward products of M tokens run there.
 bool skinny_rows(int64_t M);

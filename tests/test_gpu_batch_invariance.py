@@ -1,0 +1,56 @@
+"""A token's results do not depend on how many tokens share the call: every bf16
+forward kernel sums over k in increasing order, the one for at most 64 tokens as
+the tiles of larger calls, so the rows of a small call equal, bit for bit, the
+same rows of a call with more tokens.  Token counts around the 16 / 32 / 64 row
+tiles, K from one partial K tile to several windows of four, any alignment."""
+import pytest
+import torch
+
+from paper_2502_10940_amd import cola
+
+from layer_runner import DEV
+
+pytestmark = pytest.mark.gpu
+
+# (d_in, d_out, r, padded rows)
+SHAPES = [(2048, 520, 512, True), (4096, 136, 1024, True), (5461, 264, 65, False), (40, 5461, 1369, False),
+          (512, 72, 128, True)]
+MANY = 300
+
+
+def _rows(T, width, padded, src=None):
+    ld = -(-width // 64) * 64 if padded else width
+    x = torch.full((T, ld), float("nan"), dtype=torch.bfloat16, device=DEV)[:, :width]
+    if src is not None:
+        x.copy_(src[:T])
+    return x
+
+
+def _forward(T, shape, X, A, B, act):
+    d_in, d_out, r, padded = shape
+    x, Y, Z, H, Yi = (_rows(T, w, padded, s) for w, s in ((d_in, X), (d_out, None), (r, None), (r, None),
+                                                          (d_out, None)))
+    d = cola.desc(T, d_in, d_out, r, "bf16", act, ldx=x.stride(0), ldy=Y.stride(0), ldz=Z.stride(0))
+    ws = torch.empty(max(1, cola.workspace_bytes(d, 0), cola.workspace_bytes(d, 2)), dtype=torch.uint8, device=DEV)
+    cola.fwd(d, x, A, B, Y, Z, H, ws)
+    cola.infer(d, x, A, B, Yi, ws)
+    torch.cuda.synchronize()
+    return {"Y": Y, "Z": Z, "H": H, "infer": Yi}
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=["%dx%d-r%d-%s" % (*s[:3], "pad" if s[3] else "tight") for s in SHAPES])
+def test_rows_do_not_depend_on_the_batch(shape):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    d_in, d_out, r, _ = shape
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1700 + d_in)
+    normal = lambda *s: torch.randn(s, generator=g, device=DEV)
+    X = normal(MANY, d_in).bfloat16()
+    A, B = (normal(r, d_in) * d_in ** -0.5).bfloat16(), (normal(d_out, r) * r ** -0.5).bfloat16()
+    many = _forward(MANY, shape, X, A, B, "silu")
+    for T in (1, 2, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65):
+        few = _forward(T, shape, X, A, B, "silu")
+        for k, v in few.items():
+            a, b = v.contiguous().view(torch.int16), many[k][:T].contiguous().view(torch.int16)
+            assert torch.equal(a, b), f"T={T} {k}: {(a != b).sum().item()} of {a.numel()} values differ"

@@ -1,6 +1,6 @@
-"""Forward products of at most 64 tokens (and 65, the first count past them):
-token counts around the 16 / 32 / 64 row tiles, K around the 64-deep tiles that
-eight waves share, odd and tight widths, one layer and groups, against the fp64
+"""Forward products of a few tokens: token counts around the 16 / 32 row tiles of
+the kernel for at most 32 and the 64 row tiles past it, K around 64-deep tiles,
+odd and tight widths, one layer and groups, against the fp64
 oracle (1e-2) and the storage-policy reference (1e-3, as in the shape sweep);
 the inference forward's Y bit for bit the training forward's."""
 import numpy as np
