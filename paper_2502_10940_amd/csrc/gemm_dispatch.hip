@@ -29,8 +29,11 @@ std::atomic<int> g_fuse_gate{1};
 // steps * (step + load * x) + store * x microseconds, x the share of the CUs
 // with a tile in it (all CUs busy share L2 and HBM), after `fixed` for the launch,
 // the first loads and the last stores.  Fitted to MI355X timings of the products of
-// the LLaMA shapes (60M to 7B) at 256 to 65536 tokens; the model is within
-// about 15 % of them.  E.g. T = 1024, K1 of a 1B projection (N = 512, K = 2048):
+// the LLaMA shapes (60M to 7B) at 256 to 65536 tokens run by themselves over and
+// over; the model is within about 15 % of them.  It has no term for bytes: products
+// that are bound by memory take up to twice its time within a step, where their
+// operands come from HBM (60M dZ 70 us against 35, the 350M group's dZ 140 against 77,
+// Y of the both-sigma 350M layer 49 against 25), on every route alike.  E.g. T = 1024, K1 of a 1B projection (N = 512, K = 2048):
 // 256 x 256 tiles 42 us (8 of them), 128 x 128 17, 128 x 64 13, 64 x 64 10;
 // T = 4096 at 7B (N = 1024, K = 4096): 75, 36, 45, 55; T = 16384: 108, 138,
 // 164, 210.  Weight gradients of one launch (r = 512, 2048 x 2048): at
@@ -97,7 +100,17 @@ int gemm_route(int64_t M, int64_t N, int64_t K) {
     double best_us = -1.0;
     for (int r : kRoutes) {
         if (!route_fits(r, M, N, 1)) continue;
-        const double us = route_us(r, route_tiles(r, M, N), steps, false);
+        const int64_t tiles = route_tiles(r, M, N);
+        double us = route_us(r, tiles, steps, false);
+        // 256 x 256 tiles on half the CUs or more give way only to a gain above the
+        // model's error: the CUs they leave free are not lost to a caller with a
+        // second stream, and work per CU is the better.  Z and dZ of the 350M shape
+        // at 32768 tokens (128 such tiles), two streams: a step of 7 projections
+        // takes 1.51 ms with them and 1.69 with the 128 x 128 tiles that the model
+        // prefers by 3 to 13 %; one stream 2.17 and 2.15.  Not with a short K, where
+        // a tile is mostly its stores (dX of 8192 x 1024, K = 256: the both-sigma
+        // layer's step 167.5 us with 128 x 64 tiles, 169.0 with 256 x 256).
+        if (r == ROUTE_PP && tiles >= 128 && steps >= 8) us *= 0.85;
         if (best_us < 0 || us < best_us) {
             best_us = us;
             best = r;
