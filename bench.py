@@ -76,8 +76,43 @@ COPY_BYTES = 1 << 30
 # the workload of the headline line (LLaMA-1B-shaped block); its counter readings sit at the
 # top level of profiles/traffic.json
 HEADLINE_WORKLOAD = 4
+# GEMM kernels by what their template arguments say.  The streaming and the one-product
+# 256 x 256 kernels end in the step's tag; the others name the operand layouts (0: k-contiguous,
+# 1: m-contiguous) and the epilogue, which stand for one step of a layer each, but for the steps
+# of a dense layer and of the both-sigma variant, which share them.
 KERNEL_TAGS = {0: "fwd_z_sigma", 1: "fwd_y", 2: "bwd_dz", 3: "bwd_dx", 4: "bwd_da", 5: "bwd_db",
-               7: "dense_fwd", 8: "dense_dx", 9: "dense_dw"}
+               7: "dense_fwd", 8: "dense_dx", 9: "dense_dw", 11: "infer_h", 12: "fwd_y", 13: "fwd_y", 14: "bwd_dx"}
+TAGGED_KERNELS = ("gemm_stream_kernel", "gemm_pp_kernel", "gemm_pp_persist_kernel")
+SHARING_TAGS = (7, 8, 9, 12)
+# where the layouts and the epilogue sit among the template arguments
+EPILOGUE_KERNELS = {"gemm_pp_batch_kernel": slice(1, 4), "gemm_mid_kernel": slice(4, 7),
+                    "gemm_f32_kernel": slice(0, 3)}
+EPILOGUE_CLASSES = {("0", "0", "2"): "fwd_z_sigma", ("0", "0", "0"): "fwd_y", ("0", "0", "5"): "fwd_y",
+                    ("0", "0", "4"): "infer_h", ("0", "1", "3"): "bwd_dz", ("0", "1", "0"): "bwd_dx",
+                    ("0", "1", "6"): "bwd_dx", ("1", "1", "1"): "bwd_da_db"}
+
+
+def gemm_class(name):
+    """(class of the library's kernel timing, step tag or None) of a GEMM kernel's demangled name in
+    a run of the layer; None for a kernel that is no GEMM; SystemExit for a GEMM it does not know."""
+    import re
+    m = re.search(r"\b(gemm_\w+_kernel)(?:<([^>]*)>)?", name)
+    if not m:
+        return None
+    kernel, args = m.group(1), [a.strip() for a in (m.group(2) or "").split(",")]
+    cls, tag = None, None
+    if kernel in TAGGED_KERNELS and args[-1].isdigit():
+        tag = int(args[-1])
+        cls = KERNEL_TAGS.get(tag)
+    elif kernel in EPILOGUE_KERNELS:
+        cls = EPILOGUE_CLASSES.get(tuple(args[EPILOGUE_KERNELS[kernel]]))
+    elif kernel == "gemm_skinny_kernel":
+        cls = EPILOGUE_CLASSES.get(("0", "0", args[-1]))
+    elif kernel in ("gemm_mid_dxw_kernel", "gemm_f32_dxw_kernel"):
+        cls = "bwd_da_db"
+    if cls is None:
+        raise SystemExit(f"unknown GEMM kernel {name!r}: gemm_class() must learn it")
+    return cls, tag
 
 
 def copy_calibration():
@@ -151,9 +186,6 @@ def traffic_summary(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, worklo
     that copy.  The headline workload's classes sit at the top level of
     profiles/traffic.json, another workload's under "workload_<n>"; the other
     sections of the file are kept."""
-    import hashlib
-    import re
-
     def copy_factor(path, counter):
         vals = [v for name, _, v in _pmc_rows(path, counter) if "copy" in name.lower()
                 or "elementwise" in name.lower()]
@@ -170,15 +202,20 @@ def traffic_summary(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv, worklo
           and v * 1024 > 0.25 * COPY_BYTES]
     ff_ro = COPY_BYTES / (sorted(ro)[len(ro) // 2] * 1024.0) if ro else None
     per = {}
+    sharing = untagged = False
     for path, counter, scale, key in ((fetch_csv, "FETCH_SIZE", ff, "fetch"),
                                       (write_csv, "WRITE_SIZE", fw, "write")):
         for name, _, v in _pmc_rows(path, counter):
-            m = re.search(r"gemm_\w+_kernel<[^>]*, (\d+)>", name)
-            if not m:
+            known = gemm_class(name)
+            if known is None:
                 continue
-            # the launch of both weight gradients carries the dA tag
-            cls = "bwd_da_db" if "pair_kernel" in name else KERNEL_TAGS.get(int(m.group(1)))
+            cls, tag = known
+            sharing |= tag in SHARING_TAGS
+            untagged |= tag is None
             per.setdefault(cls, {}).setdefault(key, []).append(v * 1024.0 * scale)
+    if sharing and untagged:
+        raise SystemExit("the run holds products of a dense layer or of the both-sigma variant beside kernels "
+                         "whose names do not tell them from the layer's: count one mode at a time (--only)")
     h = kernel_source_hash()
     sec = {"_note": "HBM bytes per launch from rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled by a "
                     "1 GiB copy (fetch factor %.4f, write factor %.4f; a read-only 1 GiB pass gives fetch "
@@ -411,7 +448,7 @@ def kernel_table(cola):
 
 # the sources the layer's GEMM kernels and their launch plans are built from
 GEMM_SOURCES = ("cola_abi.hip", "device_math.hpp", "epilogue.hpp", "gemm_dispatch.hip", "gemm_f32.hip",
-                "gemm_pp.hip", "gemm_stream.hip", "internal.hpp", "lds_tile.hpp")
+                "gemm_mid.hip", "gemm_pp.hip", "gemm_skinny.hip", "gemm_stream.hip", "internal.hpp", "lds_tile.hpp")
 
 
 def kernel_source_hash():

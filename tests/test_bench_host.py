@@ -5,6 +5,8 @@ counted as one class), and the refusal of more than one GPU."""
 import csv
 import json
 import os
+import re
+import shutil
 import subprocess
 import sys
 import types
@@ -71,7 +73,7 @@ def test_traffic_summary_attribution_and_calibration(tmp_path, monkeypatch):
     monkeypatch.setattr(bench, "ROOT", str(tmp_path))
     monkeypatch.setattr(bench, "kernel_source_hash", lambda: "0123456789abcdef")
     gib_kib = bench.COPY_BYTES / 1024.0
-    pair = "void gemm_pp_pair_kernel<64, 1, 1, 1, 4>(GemmArgs, GemmArgs, long) [clone .kd]"
+    pair = "void gemm_pp_batch_kernel<64, 1, 1, 1>(PPBatch) [clone .kd]"
     fwd_y = "void gemm_pp_persist_kernel<64, 0, 1, 0, 1>(GemmArgs) [clone .kd]"
     copy = "void at::native::elementwise_kernel<128, 4>(int, copy_functor) [clone .kd]"
     f = tmp_path / "fetch.csv"
@@ -97,6 +99,53 @@ def test_traffic_summary_attribution_and_calibration(tmp_path, monkeypatch):
     assert bench.load_traffic("bwd_da_db") == pytest.approx(p["bytes_per_launch"])
     monkeypatch.setattr(bench, "kernel_source_hash", lambda: "fedcba9876543210")
     assert bench.load_traffic("bwd_da_db") is None
+
+
+def test_every_gemm_kernel_has_its_class():
+    """The kernels in the built library, by the names a profiler reports."""
+    lib = os.path.join(ROOT, "paper_2502_10940_amd", "libcola.so")
+    if not os.path.exists(lib) or not shutil.which("nm"):
+        pytest.skip("no built library or no nm")
+    syms = subprocess.run(["nm", "-C", lib], capture_output=True, text=True, check=True, timeout=60).stdout
+    names = sorted(set(re.findall(r"gemm_\w+_kernel(?:<[^>]*>)?\(", syms)))
+    assert len(names) > 50
+    epilogues = {0: {"fwd_y", "bwd_dx"}, 1: {"bwd_da_db"}, 2: {"fwd_z_sigma"}, 3: {"bwd_dz"}, 4: {"infer_h"},
+                 5: {"fwd_y"}, 6: {"bwd_dx"}}
+    for n in names:
+        cls, tag = bench.gemm_class(n)
+        if "dxw" in n:
+            assert cls == "bwd_da_db", n
+        elif tag is None:
+            a = re.search("<(.*)>", n).group(1).replace(", false", "").replace(", true", "").split(", ")
+            assert cls in epilogues[int(a[-1])], n
+            assert "skinny" in n or (cls == "bwd_dx") == (a[-3:-1] == ["0", "1"] and a[-1] in "06"), n
+        else:
+            assert cls == bench.KERNEL_TAGS[tag], n
+
+
+def test_unknown_gemm_kernels_are_refused(tmp_path, monkeypatch):
+    assert bench.gemm_class("void reduce_kernel<true>(ReduceBatch)") is None
+    for n in ("gemm_pp_pair_kernel<64, 1, 1, 1, 4>(GemmArgs, GemmArgs, long)", "gemm_new_kernel<64, 0, 0, 2>()",
+              "gemm_mid_kernel<64, 64, 4, 2, 1, 0, 1>()", "gemm_pp_kernel<64, 0, 0, 0, 77>(GemmArgs)"):
+        with pytest.raises(SystemExit, match="unknown GEMM kernel"):
+            bench.gemm_class(n)
+    # a dense product beside kernels that would run one under the same name
+    (tmp_path / "profiles").mkdir()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    copy = ("void at::native::elementwise_kernel<128, 4>(int, copy_functor)", bench.COPY_BYTES / 1024.0)
+    rows = [("gemm_pp_kernel<64, 0, 0, 0, 7>(GemmArgs)", 1.0), ("gemm_mid_kernel<64, 64, 4, 2, 0, 0, 0>(MidBatch)", 1.0)]
+    f, w, c, d = (tmp_path / n for n in ("f.csv", "w.csv", "cf.csv", "cw.csv"))
+    write_pmc(f, "FETCH_SIZE", rows)
+    write_pmc(w, "WRITE_SIZE", rows)
+    write_pmc(c, "FETCH_SIZE", [copy])
+    write_pmc(d, "WRITE_SIZE", [copy])
+    with pytest.raises(SystemExit, match="one mode at a time"):
+        bench.traffic_summary(str(f), str(w), str(c), str(d))
+
+
+def test_counter_readings_depend_on_every_gemm_source():
+    src = set(os.listdir(os.path.join(ROOT, "paper_2502_10940_amd", "csrc")))
+    assert {n for n in src if n.startswith("gemm_")} <= set(bench.GEMM_SOURCES) <= src
 
 
 def test_traffic_summary_needs_copy_dispatch(tmp_path, monkeypatch):
@@ -151,7 +200,7 @@ def test_traffic_summary_keeps_workload_sections(tmp_path, monkeypatch):
     monkeypatch.setattr(bench, "ROOT", str(tmp_path))
     monkeypatch.setattr(bench, "kernel_source_hash", lambda: "0123456789abcdef")
     gib_kib = bench.COPY_BYTES / 1024.0
-    pair = "void gemm_pp_pair_kernel<64, 1, 1, 1, 4>(GemmArgs, GemmArgs, long) [clone .kd]"
+    pair = "void gemm_pp_batch_kernel<64, 1, 1, 1>(PPBatch) [clone .kd]"
     copy = "void at::native::elementwise_kernel<128, 4>(int, copy_functor) [clone .kd]"
     cf, cw = tmp_path / "cf.csv", tmp_path / "cw.csv"
     write_pmc(cf, "FETCH_SIZE", [(copy, 0.8 * gib_kib)])
