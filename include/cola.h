@@ -48,7 +48,8 @@
  *
  * Determinism.  Results are bitwise reproducible run to run: the T-long
  * weight-gradient sums are split into a fixed number of chunks whose fp32
- * partials are added in a fixed order.
+ * partials are added in a fixed order.  They depend neither on the workspace's
+ * contents nor on how much of it there is.
  */
 #ifndef COLA_H
 #define COLA_H
@@ -146,9 +147,8 @@ int cola_bwd(const cola_desc* desc,
 
 /* Backward for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
- * same computation and results as cola_bwd (bitwise, where that call's workspace
- * fits the array), with its workspace in a static device array of the library
- * instead of a caller buffer.  Nothing is
+ * same computation and results as cola_bwd (bitwise), with its workspace in a
+ * static device array of the library instead of a caller buffer.  Nothing is
  * allocated or freed by the call; the array (COLA_SCRATCH_BYTES per GPU) is
  * placed when the library's code object is loaded on a GPU and held until the
  * process ends.  Each GPU has its own array, shared by every call on that
@@ -156,8 +156,8 @@ int cola_bwd(const cola_desc* desc,
  * replays in flight) race on it and must be ordered by the caller.  A call
  * whose dZ, H (CoLA-M), repacked weights and weight-gradient partials exceed
  * COLA_SCRATCH_BYTES returns COLA_ERR_SCRATCH and enqueues nothing; aligned
- * copies of unaligned token rows and surplus splits are left out where only
- * they would exceed it.  Arguments, ownership,
+ * copies of unaligned token rows are left out where they would exceed it
+ * (slower).  Arguments, ownership,
  * errors and T = 0 as cola_bwd. */
 #define COLA_SCRATCH_BYTES ((size_t)64 << 20)
 int cola_bwd_scratch(const cola_desc* desc,

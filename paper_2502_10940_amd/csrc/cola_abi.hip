@@ -154,7 +154,10 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Split of a token-long (K = T) weight-gradient GEMM into chunks of whole K
 // tiles, and the kernel it was planned for.  Depends only on the shape (and
-// the tuning options), so results are reproducible run to run.
+// the tuning options), so results are reproducible run to run; in particular not
+// on the room for copies of unaligned rows, nor on whether H is stored: the kernels
+// for aligned and for unaligned rows sum a chunk in the same order, so that dA and
+// dB have the same bits in every workspace, in CoLA and in CoLA-M.
 struct Split {
     int splits;
     int64_t k_chunk;
@@ -165,19 +168,34 @@ struct WShape {
     int64_t M, N;
 };
 
+constexpr int64_t kMaxSplits = 64;
+
+// Bytes of the fp32 partials of n products (none for one split).
+size_t partial_bytes(const WShape* w, int n, int64_t splits) {
+    size_t b = 0;
+    for (int i = 0; i < n && splits > 1; ++i) b += align256((size_t)splits * (size_t)(w[i].M * w[i].N) * 4);
+    return b;
+}
+
+// Tiles of the streaming family: 256 x 128, or 128 x 128 for at most 128 rows.
+int64_t stream_tiles(const WShape& w) {
+    const int64_t bm = w.M > 128 ? 256 : 128;
+    return ((w.M + bm - 1) / bm) * ((w.N + 127) / 128);
+}
+
 // Split of the streaming family: the split count S minimises rounds(S) * ceil(ktiles / S) K-tile steps of about 2 us
 // each, where rounds(S) = ceil(tiles * S / slots) and slots is the number of
 // workgroups the chip runs at once -- a split that leaves a few workgroups for a
 // second round costs a whole round -- plus writing and re-reading the S fp32
 // partials (`elems` values per split) at about 4 TB/s.
-Split plan_split_tiles(int64_t bk, int64_t tiles, int64_t slots, int64_t K, double elems, int64_t cap) {
+Split plan_split_tiles(int64_t bk, int64_t tiles, int64_t slots, int64_t K, double elems) {
     const int64_t ktiles = (K + bk - 1) / bk;
     if (ktiles < 1) return Split{1, bk, ROUTE_AUTO};           // empty batch: nothing to split
     const double step_us = 2.0;
     const double partial_us_per_split = elems * 8.0 / 4.0e6;
     int64_t maxs = ktiles / 4;
     if (maxs < 1) maxs = 1;
-    if (maxs > cap) maxs = cap;
+    if (maxs > kMaxSplits) maxs = kMaxSplits;
     int64_t best_s = 1;
     double best_cost = -1.0;
     for (int64_t s = 1; s <= maxs; ++s) {
@@ -204,20 +222,20 @@ Split plan_split_tiles(int64_t bk, int64_t tiles, int64_t slots, int64_t K, doub
 // of K = T: the pair that minimises the routes' cost model (which covers storing
 // the partials) plus the reduction: its launch (2 us), and the partials and the
 // result at about 5 TB/s (8 splits of 2.1 M values: 14 us; 2 of 8.4 M: 18 us).
-// Products with unaligned rows (aligned false) run in the streaming family.
-Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned, int64_t cap) {
+// `stream`: planned for the streaming family.  `room`: for the partials.
+Split plan_split_bf16(const WShape* w, int n, int64_t K, bool stream, size_t room) {
     const int64_t ktiles = (K + BF16_BK - 1) / BF16_BK;
     if (ktiles < 1) return Split{1, BF16_BK, ROUTE_AUTO};
     double elems = 0.0;
     for (int i = 0; i < n; ++i) elems += (double)w[i].M * (double)w[i].N;
-    if (!aligned || get_option(OPT_STREAM_ONLY) == 1) {
+    if (stream || get_option(OPT_STREAM_ONLY) == 1) {
         int64_t tiles = 0;
-        for (int i = 0; i < n; ++i) tiles += ((w[i].M + 255) / (w[i].M > 128 ? 256 : 128)) * ((w[i].N + 127) / 128);
-        return plan_split_tiles(BF16_BK, tiles, 512, K, elems, cap);
+        for (int i = 0; i < n; ++i) tiles += stream_tiles(w[i]);
+        return plan_split_tiles(BF16_BK, tiles, 512, K, elems);
     }
     int64_t maxs = ktiles / 4;
     if (maxs < 1) maxs = 1;
-    if (maxs > cap) maxs = cap;
+    if (maxs > kMaxSplits) maxs = kMaxSplits;
     Split best{1, ktiles * BF16_BK, ROUTE_AUTO};
     double best_cost = -1.0;
     for (int route = ROUTE_PP; route <= ROUTE_MID_64x64; ++route) {
@@ -231,6 +249,7 @@ Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned, int64_t c
         for (int64_t s = 1; s <= maxs; ++s) {
             const int64_t chunk = (ktiles + s - 1) / s;
             const int64_t eff_s = (ktiles + chunk - 1) / chunk;
+            if (partial_bytes(w, n, eff_s) > room) break;
             const double cost = route_us(route, tiles * eff_s, chunk, true) +
                                 (eff_s > 1 ? 2.0 + (double)(eff_s + 1) * elems * 4.0 / 5.0e6 : 0.0);
             if (best_cost < 0 || cost < best_cost) {
@@ -246,7 +265,7 @@ Split plan_split_bf16(const WShape* w, int n, int64_t K, bool aligned, int64_t c
 // tiles takes eight K tiles at once in about 0.9 us (a CU's matrix cores need that
 // long for them), against the reduction's launch (4 us) and partials at about
 // 4 TB/s.
-Split plan_split_f32(const WShape* w, int n, int64_t K, int64_t cap) {
+Split plan_split_f32(const WShape* w, int n, int64_t K, size_t room) {
     const int64_t steps = (K + 8 * F32_BK - 1) / (8 * F32_BK);
     if (steps < 1) return Split{1, F32_BK, ROUTE_AUTO};
     double elems = 0.0;
@@ -257,9 +276,10 @@ Split plan_split_f32(const WShape* w, int n, int64_t K, int64_t cap) {
     }
     Split best{1, steps * 8 * F32_BK, ROUTE_AUTO};
     double best_cost = -1.0;
-    for (int64_t s = 1; s <= (steps < cap ? steps : cap); ++s) {
+    for (int64_t s = 1; s <= (steps < kMaxSplits ? steps : kMaxSplits); ++s) {
         const int64_t chunk = (steps + s - 1) / s;
         const int64_t eff_s = (steps + chunk - 1) / chunk;
+        if (partial_bytes(w, n, eff_s) > room) break;
         const double rounds = (double)((tiles * eff_s + 255) / 256);
         const double cost = rounds * (double)chunk * 0.9 + (eff_s > 1 ? 4.0 + (double)eff_s * elems * 8.0 / 4.0e6 : 0.0);
         if (best_cost < 0 || cost < best_cost) {
@@ -270,19 +290,42 @@ Split plan_split_f32(const WShape* w, int n, int64_t K, int64_t cap) {
     return best;
 }
 
-// At most kMaxSplits splits, or `cap` of them where the workspace is short.
-constexpr int64_t kMaxSplits = 64;
-
-Split plan_split(bool bf16, const WShape* w, int n, int64_t K, bool aligned, int64_t cap = kMaxSplits) {
-    return bf16 ? plan_split_bf16(w, n, K, aligned, cap) : plan_split_f32(w, n, K, cap);
+Split plan_split(bool bf16, const WShape* w, int n, int64_t K, bool stream = false, size_t room = SIZE_MAX) {
+    return bf16 ? plan_split_bf16(w, n, K, stream, room) : plan_split_f32(w, n, K, room);
 }
 
-// The two weight gradients of a layer in one launch (bf16: aligned rows): their
-// tiles share the slots and one split of K = T.  The option
-// COLA_OPT_WGRAD_PAIR = 0 launches them one by one (tuning, comparisons).
-bool pair_wgrads(bool bf16, bool aligned) {
-    return get_option(OPT_WGRAD_PAIR) == 1 && (!bf16 || (get_option(OPT_STREAM_ONLY) == 0 && aligned));
+// The two weight gradients of a layer in one launch: their tiles share the slots
+// and one split of K = T.  The option COLA_OPT_WGRAD_PAIR = 0 launches them one by
+// one (tuning, comparisons).
+bool pair_wgrads(bool bf16) {
+    return get_option(OPT_WGRAD_PAIR) == 1 && (!bf16 || get_option(OPT_STREAM_ONLY) == 0);
 }
+
+// Room for the partials of a layer's weight gradients that share a launch (n = 2)
+// or do not (n = 1): what the splits of the 256 x 256, streaming and 64 x 64 fp32
+// kernels take.  A rule of its own, so that the calls that cola_bwd_scratch accepts
+// do not move with the choice of kernels, and that call and cola_bwd have one plan.
+// It binds in 2 of 3000 shapes of 16 to 65536 tokens, 64 to 11008 wide: the others'
+// splits for smaller tiles take less.
+size_t partial_room(bool bf16, const WShape* w, int n, int64_t T) {
+    const bool stream = get_option(OPT_STREAM_ONLY) == 1;
+    const int64_t bk = bf16 ? 64 : 16;
+    int64_t tiles[2] = {0, 0}, slots[2] = {0, 0};
+    bool wide = n == 2;
+    for (int i = 0; i < n; ++i) {
+        const bool pp = bf16 && !stream && w[i].M >= 128 && w[i].N >= 128;
+        wide = wide && pp;
+        tiles[i] = !bf16 ? f32_tiles(64, w[i].M, w[i].N) : (pp ? f32_tiles(256, w[i].M, w[i].N) : stream_tiles(w[i]));
+        slots[i] = !bf16 ? 1024 : (pp ? 256 : 512);
+    }
+    auto elems = [&](int i) { return (double)w[i].M * (double)w[i].N; };
+    if (wide)
+        return partial_bytes(w, 2, plan_split_tiles(bk, tiles[0] + tiles[1], 256, T, elems(0) + elems(1)).splits);
+    size_t b = 0;
+    for (int i = 0; i < n; ++i) b += partial_bytes(w + i, 1, plan_split_tiles(bk, tiles[i], slots[i], T, elems(i)).splits);
+    return b;
+}
+
 // Rows of pitch ld start on 16-byte boundaries (bf16).
 bool pitch16(int64_t ld) { return ld % 8 == 0; }
 
@@ -344,9 +387,13 @@ hipError_t use_packed(const Pack& pk, const void* src, int64_t src_ld, char* ws,
     return launch_pack_rows(src, src_ld, pk.rows, pk.width, ws + pk.off, pk.ld, s);
 }
 
-// Token rows are copied (copies = true) when the workspace has room for them; a
-// caller that brings only the `lean` size gets the kernels for unaligned rows.
+// Token rows are copied when the workspace has room for them (`copies`: a mask); a
+// caller that brings only the `lean` size gets the kernels for unaligned rows (the
+// same bits, more slowly).
 // cola_workspace_bytes returns the full size.
+enum Copies : unsigned { COPY_DY = 1, COPY_H = 2, COPY_X = 4 };
+constexpr unsigned kAllCopies = COPY_DY | COPY_H | COPY_X;
+
 struct FwdPlan {
     int64_t ldw;          // pitch of the workspace copy of H (CoLA-M)
     size_t off_h, total;
@@ -354,16 +401,16 @@ struct FwdPlan {
     Pack px, ph;          // repacked X and H
 };
 
-FwdPlan plan_fwd(const Dims& x, bool recompute, bool copies = true) {
+FwdPlan plan_fwd(const Dims& x, bool recompute, unsigned copies = kAllCopies) {
     FwdPlan p;
     p.ldw = line_pitch(x.bf16, x.r);
     p.off_h = 0;
     const size_t hbytes = recompute ? align256((size_t)x.T * (size_t)p.ldw * x.esize) : 0;
     p.pa = plan_weight(x.bf16, x.r, x.d_in, hbytes);
     p.pb = plan_weight(x.bf16, x.d_out, x.r, p.pa.off + p.pa.bytes);
-    copies = copies && x.bf16;
-    p.px = plan_pack(copies && !pitch16(x.ldx), x.T, x.d_in, x.ldx, p.pb.off + p.pb.bytes);
-    p.ph = plan_pack(copies && !recompute && !pitch16(x.ldz), x.T, x.r, recompute ? p.ldw : x.ldz,
+    if (!x.bf16) copies = 0;
+    p.px = plan_pack((copies & COPY_X) && !pitch16(x.ldx), x.T, x.d_in, x.ldx, p.pb.off + p.pb.bytes);
+    p.ph = plan_pack((copies & COPY_H) && !recompute && !pitch16(x.ldz), x.T, x.r, recompute ? p.ldw : x.ldz,
                      p.px.off + p.px.bytes);
     p.total = p.ph.off + p.ph.bytes;
     if (x.T == 0) p.total = 0;
@@ -379,43 +426,48 @@ struct BwdPlan {
     Pack px, py, ph;      // repacked X, dY and H
 };
 
-BwdPlan plan_bwd(const Dims& x, bool recompute, bool copies = true, int64_t cap = kMaxSplits) {
+BwdPlan plan_bwd(const Dims& x, bool recompute, unsigned copies = kAllCopies) {
     BwdPlan p;
     p.ldw = line_pitch(x.bf16, x.r);
     const size_t zbytes = align256((size_t)x.T * (size_t)p.ldw * x.esize);
-    copies = copies && x.bf16;
-    const bool al_a = copies || pitch16(x.ldx), al_b = copies || (pitch16(x.ldy) && (recompute || pitch16(x.ldz)));
-    p.pair = pair_wgrads(x.bf16, al_a && al_b);
+    if (!x.bf16) copies = 0;
+    p.pair = pair_wgrads(x.bf16);
     const WShape w[2] = {{x.r, x.d_in}, {x.d_out, x.r}};
     if (p.pair) {
-        p.sa = p.sb = plan_split(x.bf16, w, 2, x.T, true, cap);
+        p.sa = p.sb = plan_split(x.bf16, w, 2, x.T, false, partial_room(x.bf16, w, 2, x.T));
     } else {
-        p.sa = plan_split(x.bf16, w, 1, x.T, al_a, cap);
-        p.sb = plan_split(x.bf16, w + 1, 1, x.T, al_b, cap);
+        p.sa = plan_split(x.bf16, w, 1, x.T, false, partial_room(x.bf16, w, 1, x.T));
+        p.sb = plan_split(x.bf16, w + 1, 1, x.T, false, partial_room(x.bf16, w + 1, 1, x.T));
     }
     p.off_dz = 0;
     p.off_h = zbytes;
     p.off_pa = p.off_h + (recompute ? zbytes : 0);
-    const size_t pa = p.sa.splits > 1 ? align256((size_t)p.sa.splits * (size_t)(x.r * x.d_in) * 4) : 0;
-    p.off_pb = p.off_pa + pa;
-    const size_t pb = p.sb.splits > 1 ? align256((size_t)p.sb.splits * (size_t)(x.d_out * x.r) * 4) : 0;
-    p.wa = plan_weight(x.bf16, x.r, x.d_in, p.off_pb + pb);
+    p.off_pb = p.off_pa + partial_bytes(w, 1, p.sa.splits);
+    p.wa = plan_weight(x.bf16, x.r, x.d_in, p.off_pb + partial_bytes(w + 1, 1, p.sb.splits));
     p.wb = plan_weight(x.bf16, x.d_out, x.r, p.wa.off + p.wa.bytes);
-    p.px = plan_pack(copies && !pitch16(x.ldx), x.T, x.d_in, x.ldx, p.wb.off + p.wb.bytes);
-    p.py = plan_pack(copies && !pitch16(x.ldy), x.T, x.d_out, x.ldy, p.px.off + p.px.bytes);
-    p.ph = plan_pack(copies && !recompute && !pitch16(x.ldz), x.T, x.r, recompute ? p.ldw : x.ldz,
+    p.px = plan_pack((copies & COPY_X) && !pitch16(x.ldx), x.T, x.d_in, x.ldx, p.wb.off + p.wb.bytes);
+    p.py = plan_pack((copies & COPY_DY) && !pitch16(x.ldy), x.T, x.d_out, x.ldy, p.px.off + p.px.bytes);
+    p.ph = plan_pack((copies & COPY_H) && !recompute && !pitch16(x.ldz), x.T, x.r, recompute ? p.ldw : x.ldz,
                      p.py.off + p.py.bytes);
     p.total = p.ph.off + p.ph.bytes;
     if (x.T == 0) p.total = 0;
     return p;
 }
 
-// The plan that `ws_bytes` has room for: with copies of unaligned rows, or the
-// lean one (which is refused if that is too large as well).
+// The plan that `ws_bytes` has room for: with every copy of unaligned rows, or with
+// those that fit (dY first: two products read it, the dB of an uncopied H still one),
+// or the lean one, which is refused if that is too large as well.  40000 tokens,
+// 257 -> 255, r = 129 in cola_bwd_scratch: 826 us without copies, 429 with those of
+// dY and H.
 template <class F>
 auto fitting(size_t ws_bytes, F&& plan) {
-    const auto full = plan(true);
-    return ws_bytes >= full.total ? full : plan(false);
+    auto p = plan(kAllCopies);
+    constexpr unsigned order[] = {COPY_DY | COPY_H, COPY_DY | COPY_X, COPY_DY, COPY_H | COPY_X, COPY_X, 0u};
+    for (unsigned copies : order) {
+        if (ws_bytes >= p.total) break;
+        p = plan(copies);
+    }
+    return p;
 }
 
 hipError_t gemm(const GemmArgs& a, bool bf16, hipStream_t s) {
@@ -691,7 +743,7 @@ int bwd_checked(const cola_desc* desc, const void* dY, const void* X, const void
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (x.T == 0) return zero_weight_grads(x, dA, dB, s);
     if (!dY || !X || !Z || !A || !B || !dX) return COLA_ERR_INVALID_ARG;
-    const BwdPlan p = fitting(ws_bytes, [&](bool copies) { return plan_bwd(x, recompute, copies); });
+    const BwdPlan p = fitting(ws_bytes, [&](unsigned copies) { return plan_bwd(x, recompute, copies); });
     if (!ws || ws_bytes < p.total) return COLA_ERR_WORKSPACE;
     return layer_backward(x, p, desc->act, recompute, dY, X, Z, H, A, B, dX, dA, dB,
                           reinterpret_cast<char*>(ws), s, gate);
@@ -704,7 +756,7 @@ struct OuterPlan {
     BwdPlan bwd;          // of the layer, which reads dP
 };
 
-OuterPlan plan_outer_bwd(const Dims& x, bool recompute, bool copies = true) {
+OuterPlan plan_outer_bwd(const Dims& x, bool recompute, unsigned copies = kAllCopies) {
     OuterPlan o;
     o.ldg = line_pitch(x.bf16, x.d_out);
     Dims dp = x;
@@ -802,7 +854,7 @@ int cola_fwd(const cola_desc* desc, const void* X, const void* A, const void* B,
         if (recompute ? (H != nullptr) : (H == nullptr && x.T > 0)) return COLA_ERR_INVALID_ARG;
         if (x.T == 0) return COLA_OK;
         if (!X || !A || !B || !Y || !Z) return COLA_ERR_INVALID_ARG;
-        const FwdPlan p = fitting(ws ? ws_bytes : 0, [&](bool copies) { return plan_fwd(x, recompute, copies); });
+        const FwdPlan p = fitting(ws ? ws_bytes : 0, [&](unsigned copies) { return plan_fwd(x, recompute, copies); });
         if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
         return layer_forward(x, p, desc->act, recompute, X, A, B, Y, Z, H, -1, nullptr, reinterpret_cast<char*>(ws),
                              reinterpret_cast<hipStream_t>(stream));
@@ -820,7 +872,7 @@ int cola_fwd_outer(const cola_desc* desc, int outer_act, const void* X, const vo
         if (recompute ? (H != nullptr) : (H == nullptr && x.T > 0)) return COLA_ERR_INVALID_ARG;
         if (x.T == 0) return COLA_OK;
         if (!X || !A || !B || !Y || !P || !Z) return COLA_ERR_INVALID_ARG;
-        const FwdPlan p = fitting(ws ? ws_bytes : 0, [&](bool copies) { return plan_fwd(x, recompute, copies); });
+        const FwdPlan p = fitting(ws ? ws_bytes : 0, [&](unsigned copies) { return plan_fwd(x, recompute, copies); });
         if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
         return layer_forward(x, p, desc->act, recompute, X, A, B, Y, Z, H, outer_act, P, reinterpret_cast<char*>(ws),
                              reinterpret_cast<hipStream_t>(stream));
@@ -859,36 +911,14 @@ ScratchPtrs& scratch_ptrs() {
 }
 
 // The size by which cola_bwd_scratch accepts a call: dZ, H (CoLA-M), repacked
-// weights and the partials of the 256 x 256, streaming and 64 x 64 fp32 kernels'
-// splits.  A rule of its own, so that which calls are accepted does not move
-// with the choice of kernels.
+// weights and the room for partials, which the lean plan never exceeds.
 size_t scratch_demand(const Dims& x, bool recompute) {
     if (x.T == 0) return 0;
     const WShape w[2] = {{x.r, x.d_in}, {x.d_out, x.r}};
-    const bool stream = get_option(OPT_STREAM_ONLY) == 1;
-    int64_t tiles[2], slots[2];
-    double elems[2];
-    bool wide[2];
-    for (int i = 0; i < 2; ++i) {
-        const int64_t M = w[i].M, N = w[i].N;
-        wide[i] = x.bf16 && !stream && M >= 128 && N >= 128;
-        const int64_t bm = x.bf16 ? (M > 128 ? 256 : 128) : 64, bn = x.bf16 ? (wide[i] ? 256 : 128) : 64;
-        tiles[i] = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-        slots[i] = !x.bf16 ? 1024 : (wide[i] ? 256 : 512);
-        elems[i] = (double)M * (double)N;
-    }
-    const int64_t bk = x.bf16 ? 64 : 16;
-    Split s[2];
-    if (wide[0] && wide[1] && get_option(OPT_WGRAD_PAIR) == 1) {
-        s[0] = s[1] = plan_split_tiles(bk, tiles[0] + tiles[1], 256, x.T, elems[0] + elems[1], kMaxSplits);
-    } else {
-        for (int i = 0; i < 2; ++i) s[i] = plan_split_tiles(bk, tiles[i], slots[i], x.T, elems[i], kMaxSplits);
-    }
     size_t total = align256((size_t)x.T * (size_t)line_pitch(x.bf16, x.r) * x.esize) * (recompute ? 2 : 1);
-    for (int i = 0; i < 2; ++i)
-        total += (s[i].splits > 1 ? align256((size_t)s[i].splits * (size_t)(w[i].M * w[i].N) * 4) : 0) +
-                 plan_weight(x.bf16, w[i].M, w[i].N, 0).bytes;
-    return total;
+    for (int i = 0; i < 2; ++i) total += plan_weight(x.bf16, w[i].M, w[i].N, 0).bytes;
+    if (get_option(OPT_WGRAD_PAIR) == 1) return total + partial_room(x.bf16, w, 2, x.T);
+    return total + partial_room(x.bf16, w, 1, x.T) + partial_room(x.bf16, w + 1, 1, x.T);
 }
 
 // Device address of this device's scratch (looked up once per device, with
@@ -934,11 +964,7 @@ int cola_bwd_scratch(const cola_desc* desc, const void* dY, const void* X, const
         if (x.T == 0) return zero_weight_grads(x, dA, dB, s);
         if (!dY || !X || !Z || !A || !B || !dX) return COLA_ERR_INVALID_ARG;
         if (scratch_demand(x, recompute) > COLA_SCRATCH_BYTES) return COLA_ERR_SCRATCH;
-        BwdPlan p = fitting(COLA_SCRATCH_BYTES, [&](bool copies) { return plan_bwd(x, recompute, copies); });
-        // fewer splits where their partials do not fit (with one split the rest
-        // is part of the demand)
-        for (int64_t cap = kMaxSplits / 2; p.total > COLA_SCRATCH_BYTES && cap >= 1; cap /= 2)
-            p = plan_bwd(x, recompute, false, cap);
+        const BwdPlan p = fitting(COLA_SCRATCH_BYTES, [&](unsigned copies) { return plan_bwd(x, recompute, copies); });
         if (p.total > COLA_SCRATCH_BYTES) return COLA_ERR_SCRATCH;
         void* w = nullptr;
         st = scratch_of_current_device(&w);
@@ -962,7 +988,7 @@ int cola_bwd_outer(const cola_desc* desc, int outer_act, const void* dY, const v
         hipStream_t s = reinterpret_cast<hipStream_t>(stream);
         if (x.T == 0) return zero_weight_grads(x, dA, dB, s);
         if (!dY || !P || !X || !Z || !A || !B || !dX) return COLA_ERR_INVALID_ARG;
-        const OuterPlan o = fitting(ws_bytes, [&](bool copies) { return plan_outer_bwd(x, recompute, copies); });
+        const OuterPlan o = fitting(ws_bytes, [&](unsigned copies) { return plan_outer_bwd(x, recompute, copies); });
         if (!ws || ws_bytes < o.total) return COLA_ERR_WORKSPACE;
         char* w = reinterpret_cast<char*>(ws);
         // dP = dY (.) sigma_out'(P), rounded to the storage dtype like dZ
@@ -999,7 +1025,7 @@ struct DensePlan {
 static DensePlan plan_dense(const Dims& x, int phase) {
     DensePlan p;
     const WShape w{x.d_out, x.d_in};
-    p.sp = plan_split(x.bf16, &w, 1, x.T, pitch16(x.ldx) && pitch16(x.ldy));
+    p.sp = plan_split(x.bf16, &w, 1, x.T, !pitch16(x.ldx) || !pitch16(x.ldy));
     p.parts = (phase == 1 && p.sp.splits > 1) ? align256((size_t)p.sp.splits * (size_t)(x.d_out * x.d_in) * 4) : 0;
     p.pw = plan_weight(x.bf16, x.d_out, x.d_in, p.parts);
     p.total = p.pw.off + p.pw.bytes;
@@ -1160,7 +1186,7 @@ bool group_h_aligned(const GDims& g, bool recompute, int p) {
     return g.off[p] % 8 == 0 && (recompute || pitch16(g.ldz));
 }
 
-GFwdPlan plan_group_fwd(const GDims& g, bool recompute, bool copies = true) {
+GFwdPlan plan_group_fwd(const GDims& g, bool recompute, unsigned copies = kAllCopies) {
     GFwdPlan p;
     p.ldw = line_pitch(g.bf16, g.R);
     p.off_h = 0;
@@ -1171,11 +1197,12 @@ GFwdPlan plan_group_fwd(const GDims& g, bool recompute, bool copies = true) {
         p.pb[q] = plan_weight(g.bf16, g.d_out[q], g.r[q], next);
         next = p.pb[q].off + p.pb[q].bytes;
     }
-    copies = copies && g.bf16;
-    p.px = plan_pack(copies && !pitch16(g.ldx), g.T, g.d_in, g.ldx, next);
+    if (!g.bf16) copies = 0;
+    p.px = plan_pack((copies & COPY_X) && !pitch16(g.ldx), g.T, g.d_in, g.ldx, next);
     next = p.px.off + p.px.bytes;
     for (int q = 0; q < g.n; ++q) {
-        p.ph[q] = plan_pack(copies && !group_h_aligned(g, recompute, q), g.T, g.r[q], recompute ? p.ldw : g.ldz, next);
+        p.ph[q] = plan_pack((copies & COPY_H) && !group_h_aligned(g, recompute, q), g.T, g.r[q],
+                            recompute ? p.ldw : g.ldz, next);
         next = p.ph[q].off + p.ph[q].bytes;
     }
     p.total = g.T == 0 ? 0 : next;
@@ -1185,7 +1212,7 @@ GFwdPlan plan_group_fwd(const GDims& g, bool recompute, bool copies = true) {
 // The weight gradients of a group are the products w = 0 (dA_all, R x d_in)
 // and w = 1 + p (dB_p, d_out_p x r_p), all over K = T.  They run in sets of up to
 // kWSet, w = 0 .. 3, 4 .. 7, 8: one launch with one split for a set, or one launch
-// each where sets are off or rows unaligned.  Their tiles together fill the CUs with
+// each where sets are off.  Their tiles together fill the CUs with
 // fewer splits (gate and up of the 350M shape at 32768 tokens: dA with one dB and
 // the other dB apart 197 us with their reductions, the three together 141).
 // Workspace: [dZ_all] [H_all (CoLA-M)] [partials of the set's products, reused set
@@ -1204,32 +1231,26 @@ WShape group_wgrad_shape(const GDims& g, int w) {
     return w == 0 ? WShape{g.R, g.d_in} : WShape{g.d_out[w - 1], g.r[w - 1]};
 }
 
-GBwdPlan plan_group_bwd(const GDims& g, bool recompute, bool copies = true) {
+GBwdPlan plan_group_bwd(const GDims& g, bool recompute, unsigned copies = kAllCopies) {
     GBwdPlan p;
     p.ldw = line_pitch(g.bf16, g.R);
     const size_t zbytes = align256((size_t)g.T * (size_t)p.ldw * g.esize);
     p.off_dz = 0;
     p.off_h = zbytes;
     size_t next = p.off_h + (recompute ? zbytes : 0);
-    copies = copies && g.bf16;
+    if (!g.bf16) copies = 0;
     p.nw = g.n + 1;
     size_t pb[kWSet] = {};
     for (int w0 = 0; w0 < p.nw; w0 += kWSet) {
         const int cnt = p.nw - w0 < kWSet ? p.nw - w0 : kWSet;
         WShape w[kWSet];
-        bool al[kWSet], all = true;
-        for (int k = 0; k < cnt; ++k) {
-            w[k] = group_wgrad_shape(g, w0 + k);
-            al[k] = copies || (w0 + k == 0 ? pitch16(g.ldx)
-                                           : group_h_aligned(g, recompute, w0 + k - 1) && pitch16(g.ldy[w0 + k - 1]));
-            all = all && al[k];
-        }
-        p.set[w0] = cnt > 1 && pair_wgrads(g.bf16, all);
-        if (p.set[w0]) p.sp[w0] = plan_split(g.bf16, w, cnt, g.T, true);
+        for (int k = 0; k < cnt; ++k) w[k] = group_wgrad_shape(g, w0 + k);
+        p.set[w0] = cnt > 1 && pair_wgrads(g.bf16);
+        if (p.set[w0]) p.sp[w0] = plan_split(g.bf16, w, cnt, g.T);
         for (int k = 0; k < cnt; ++k) {
             Split& sp = p.sp[w0 + k];
-            sp = p.set[w0] ? p.sp[w0] : plan_split(g.bf16, w + k, 1, g.T, al[k]);
-            const size_t b = sp.splits > 1 ? align256((size_t)sp.splits * (size_t)(w[k].M * w[k].N) * 4) : 0;
+            sp = p.set[w0] ? p.sp[w0] : plan_split(g.bf16, w + k, 1, g.T);
+            const size_t b = partial_bytes(w + k, 1, sp.splits);
             if (b > pb[k]) pb[k] = b;
         }
     }
@@ -1243,12 +1264,12 @@ GBwdPlan plan_group_bwd(const GDims& g, bool recompute, bool copies = true) {
         p.wb[q] = plan_weight(g.bf16, g.d_out[q], g.r[q], next);
         next = p.wb[q].off + p.wb[q].bytes;
     }
-    p.px = plan_pack(copies && !pitch16(g.ldx), g.T, g.d_in, g.ldx, next);
+    p.px = plan_pack((copies & COPY_X) && !pitch16(g.ldx), g.T, g.d_in, g.ldx, next);
     next = p.px.off + p.px.bytes;
     for (int q = 0; q < g.n; ++q) {
-        p.py[q] = plan_pack(copies && !pitch16(g.ldy[q]), g.T, g.d_out[q], g.ldy[q], next);
-        p.ph[q] = plan_pack(copies && !group_h_aligned(g, recompute, q), g.T, g.r[q], recompute ? p.ldw : g.ldz,
-                            p.py[q].off + p.py[q].bytes);
+        p.py[q] = plan_pack((copies & COPY_DY) && !pitch16(g.ldy[q]), g.T, g.d_out[q], g.ldy[q], next);
+        p.ph[q] = plan_pack((copies & COPY_H) && !group_h_aligned(g, recompute, q), g.T, g.r[q],
+                            recompute ? p.ldw : g.ldz, p.py[q].off + p.py[q].bytes);
         next = p.ph[q].off + p.ph[q].bytes;
     }
     p.total = g.T == 0 ? 0 : next;
@@ -1375,7 +1396,7 @@ int group_fwd_checked(const cola_group_desc* desc, const void* X, const void* A_
     if (!X || !A_all || !B || !Y || !Z_all) return COLA_ERR_INVALID_ARG;
     for (int q = 0; q < g.n; ++q)
         if (!B[q] || !Y[q]) return COLA_ERR_INVALID_ARG;
-    const GFwdPlan p = fitting(ws ? ws_bytes : 0, [&](bool copies) { return plan_group_fwd(g, recompute, copies); });
+    const GFwdPlan p = fitting(ws ? ws_bytes : 0, [&](unsigned copies) { return plan_group_fwd(g, recompute, copies); });
     if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
     return group_forward(g, p, desc->act, X, A_all, B, Y, Z_all, H_all, recompute, reinterpret_cast<char*>(ws),
                          reinterpret_cast<hipStream_t>(stream), gate);
@@ -1387,7 +1408,7 @@ int infer_checked(const GDims& g, int act, const void* X, const void* A_all, con
     if (!X || !A_all || !B || !Y) return COLA_ERR_INVALID_ARG;
     for (int q = 0; q < g.n; ++q)
         if (!B[q] || !Y[q]) return COLA_ERR_INVALID_ARG;
-    const GFwdPlan p = fitting(ws ? ws_bytes : 0, [&](bool copies) { return plan_group_fwd(g, true, copies); });
+    const GFwdPlan p = fitting(ws ? ws_bytes : 0, [&](unsigned copies) { return plan_group_fwd(g, true, copies); });
     if (p.total > 0 && (!ws || ws_bytes < p.total)) return COLA_ERR_WORKSPACE;
     return group_forward(g, p, act, X, A_all, B, Y, nullptr, nullptr, true, reinterpret_cast<char*>(ws),
                          reinterpret_cast<hipStream_t>(stream));
@@ -1451,7 +1472,7 @@ int cola_group_bwd(const cola_group_desc* desc, const void* const* dY, const voi
         if (!dY || !X_in || !Z_all || !A_all || !B || !dX) return COLA_ERR_INVALID_ARG;
         for (int q = 0; q < g.n; ++q)
             if (!dY[q] || !B[q]) return COLA_ERR_INVALID_ARG;
-        const GBwdPlan p = fitting(ws_bytes, [&](bool copies) { return plan_group_bwd(g, recompute, copies); });
+        const GBwdPlan p = fitting(ws_bytes, [&](unsigned copies) { return plan_group_bwd(g, recompute, copies); });
         if (!ws || ws_bytes < p.total) return COLA_ERR_WORKSPACE;
 
         char* w = reinterpret_cast<char*>(ws);
