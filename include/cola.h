@@ -83,7 +83,7 @@ typedef enum {
     COLA_ERR_INVALID_ARG = 1,      /* NULL desc/pointer, bad enum, H vs recompute mismatch */
     COLA_ERR_BAD_SHAPE = 2,        /* d_in, d_out or r < 1, T < 0, ld < width, a row pitch above
                                       COLA_MAX_PITCH, size overflow */
-    COLA_ERR_WORKSPACE = 3,        /* ws_bytes below what the call needs (cola_workspace_bytes() is enough) */
+    COLA_ERR_WORKSPACE = 3,        /* ws_bytes below the least size (COLA_WS_LEAN) cola_workspace_bytes() returns */
     COLA_ERR_HIP = 4,              /* a launch failed; cola_strerror() returns HIP's text */
     COLA_ERR_UNSUPPORTED = 5,      /* combination not compiled in */
     COLA_ERR_SCRATCH = 6           /* cola_bwd_scratch: needs more than COLA_SCRATCH_BYTES */
@@ -115,13 +115,18 @@ const char* cola_strerror(int status);
  * whatever recompute says.  The both-sigma backward needs the backward's
  * workspace plus T*d_out elements for dP.  Weights whose row length is not a
  * multiple of 8 (bf16) add a padded copy.  Buffers the library lays out
- * itself get row pitches of whole 128-byte cache lines.
+ * itself get row pitches of whole 128-byte cache lines.  bf16 inputs whose row
+ * pitch is not a multiple of 8 add a copy with such rows (X, dY, H).
+ * phase + COLA_WS_LEAN: the least the call accepts, without the copies of inputs.
+ * It makes those that what it gets has room for; the results have the same bits,
+ * but each product that reads an uncopied input takes up to several times as long.
  *
  * Layout advice for the caller's activations (X, Y, Z, H, dX, dY): rows must
  * be 16-byte aligned for the vector path (else a slower guarded path runs);
  * rows that start on 128-byte cache lines (pitch a multiple of 64 bf16 or 32
  * fp32 elements) are faster still -- up to 1.4x on a GEMM whose K-contiguous
  * operand would otherwise straddle lines (measured on MI355X). */
+#define COLA_WS_LEAN 16
 size_t cola_workspace_bytes(const cola_desc* desc, int phase);
 
 /* Forward (Eq. main-fwd): Z = X A^T, H = sigma(Z), Y = H B^T.

@@ -20,6 +20,7 @@ ACTS = {"identity": ACT_IDENTITY, "silu": ACT_SILU, "gelu": ACT_GELU}
 
 OK, ERR_INVALID_ARG, ERR_BAD_SHAPE, ERR_WORKSPACE, ERR_HIP, ERR_UNSUPPORTED, ERR_SCRATCH = range(7)
 SCRATCH_BYTES = 64 << 20      # COLA_SCRATCH_BYTES
+WS_LEAN = 16                  # COLA_WS_LEAN: added to a phase, the least workspace the call accepts
 
 KERNEL_CLASSES = ("fwd_z_sigma", "fwd_y", "bwd_dz", "bwd_dx", "bwd_da", "bwd_db",
                   "reduce_splits", "dense_fwd", "dense_dx", "dense_dw", "fill_zero", "infer_h",

@@ -394,6 +394,13 @@ hipError_t use_packed(const Pack& pk, const void* src, int64_t src_ld, char* ws,
 enum Copies : unsigned { COPY_DY = 1, COPY_H = 2, COPY_X = 4 };
 constexpr unsigned kAllCopies = COPY_DY | COPY_H | COPY_X;
 
+// The copies that a queried size has room for; takes COLA_WS_LEAN off the phase.
+unsigned phase_copies(int* phase) {
+    const bool lean = *phase >= COLA_WS_LEAN;
+    if (lean) *phase -= COLA_WS_LEAN;
+    return lean ? 0 : kAllCopies;
+}
+
 struct FwdPlan {
     int64_t ldw;          // pitch of the workspace copy of H (CoLA-M)
     size_t off_h, total;
@@ -836,10 +843,11 @@ const char* cola_kernel_name(int kc) {
 size_t cola_workspace_bytes(const cola_desc* desc, int phase) {
     Dims x;
     if (check_desc(desc, &x) != COLA_OK) return 0;
-    if (phase == 0) return plan_fwd(x, desc->recompute == 1).total;
-    if (phase == 1) return plan_bwd(x, desc->recompute == 1).total;
-    if (phase == 2) return plan_fwd(x, true).total;     // inference: H in the workspace, as CoLA-M's forward
-    if (phase == 3) return plan_outer_bwd(x, desc->recompute == 1).total;
+    const unsigned copies = phase_copies(&phase);
+    if (phase == 0) return plan_fwd(x, desc->recompute == 1, copies).total;
+    if (phase == 1) return plan_bwd(x, desc->recompute == 1, copies).total;
+    if (phase == 2) return plan_fwd(x, true, copies).total;     // inference: H in the workspace, as CoLA-M's forward
+    if (phase == 3) return plan_outer_bwd(x, desc->recompute == 1, copies).total;
     return 0;
 }
 
@@ -1283,9 +1291,10 @@ extern "C" {
 size_t cola_group_workspace_bytes(const cola_group_desc* desc, int phase) {
     GDims g;
     if (check_group(desc, &g) != COLA_OK) return 0;
-    if (phase == 0) return plan_group_fwd(g, desc->recompute == 1).total;
-    if (phase == 1) return plan_group_bwd(g, desc->recompute == 1).total;
-    if (phase == 2) return plan_group_fwd(g, true).total;
+    const unsigned copies = phase_copies(&phase);
+    if (phase == 0) return plan_group_fwd(g, desc->recompute == 1, copies).total;
+    if (phase == 1) return plan_group_bwd(g, desc->recompute == 1, copies).total;
+    if (phase == 2) return plan_group_fwd(g, true, copies).total;
     return 0;
 }
 

@@ -163,6 +163,35 @@ def test_workspace_sizes():
     assert cola.workspace_bytes(empty, 0) == 0 and cola.workspace_bytes(empty, 1) == 0
 
 
+@pytest.mark.parametrize("T,d_in,d_out,r", [(65536, 2048, 5461, 512), (1000, 77, 40, 9), (300, 512, 333, 65)])
+def test_lean_workspace_sizes(T, d_in, d_out, r):
+    """Tight odd rows: the lean size is that of the same layer on padded rows (no
+    copies of token rows), less than the full one, and the least accepted."""
+    pad = lambda w: -(-w // 8) * 8
+    for rc in (False, True):
+        tight = cola.desc(T, d_in, d_out, r, recompute=rc)
+        padded = cola.desc(T, d_in, d_out, r, "bf16", "silu", rc, pad(d_in), pad(d_out), pad(r))
+        for phase in range(4):
+            lean = cola.workspace_bytes(tight, phase + cola.WS_LEAN)
+            assert lean == cola.workspace_bytes(padded, phase) == cola.workspace_bytes(padded, phase + cola.WS_LEAN)
+            assert lean <= cola.workspace_bytes(tight, phase)
+        lean = cola.workspace_bytes(tight, 1 + cola.WS_LEAN)
+        assert lean < cola.workspace_bytes(tight, 1)
+        H = None if rc else FAKE
+        assert bwd_status(tight, H=H, ws=FAKE, ws_bytes=lean - 1) == cola.ERR_WORKSPACE
+        g = cola.group_desc(T, d_in, [r, r], [d_out, d_out], recompute=rc)
+        for phase in range(3):
+            assert cola.group_workspace_bytes(g, phase + cola.WS_LEAN) <= cola.group_workspace_bytes(g, phase)
+        assert 0 < cola.group_workspace_bytes(g, 1 + cola.WS_LEAN) < cola.group_workspace_bytes(g, 1)
+    for phase in (4, 15, 4 + cola.WS_LEAN, 2 * cola.WS_LEAN, -1, -cola.WS_LEAN):
+        assert cola.workspace_bytes(tight, phase) == 0
+    assert cola.group_workspace_bytes(g, 3 + cola.WS_LEAN) == 0
+    # 129 MB where the full size is 850
+    if T == 65536:
+        d = cola.desc(T, d_in, d_out, r)
+        assert cola.workspace_bytes(d, 1 + cola.WS_LEAN) < 160 << 20 < cola.workspace_bytes(d, 1)
+
+
 def test_empty_forward_is_a_noop():
     # T = 0 is an empty batch: nothing to compute, nothing enqueued
     d = cola.desc(0, 32, 32, 8)

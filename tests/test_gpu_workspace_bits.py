@@ -1,6 +1,7 @@
 """The bits of a layer's results do not depend on how much workspace the caller
-brings: with room for the aligned copies of unaligned rows, without it (one byte
-less than cola_workspace_bytes), and in cola_bwd_scratch's array; nor on whether H
+brings: with room for the aligned copies of unaligned rows, for some of them (one
+byte less than cola_workspace_bytes) or none (the lean size), and in
+cola_bwd_scratch's array; nor on whether H
 was stored (CoLA) or is made again (CoLA-M) in any of them.  Bitwise: one plan of
 the weight gradients' splits, and every kernel sums a split in order."""
 import numpy as np
@@ -40,13 +41,16 @@ def test_layer(case, outer):
     ins = I.layer_inputs(1800, 0, d_in, d_out, r, T, "bf16")
     first = None
     for recompute in (False, True):
-        for lean in (False, True):
+        for lean in (0, 1, 2):
             if outer:
                 run = OuterRun(ins, T, d_in, d_out, r, "bf16", "silu", "silu", recompute)
             else:
                 run = LayerRun(ins, T, d_in, d_out, r, "bf16", "silu", recompute)
             wf, wb = cola.workspace_bytes(run.desc, 0), cola.workspace_bytes(run.desc, 3 if outer else 1)
-            if lean:
+            if lean == 2:
+                wf = cola.workspace_bytes(run.desc, 0 + cola.WS_LEAN)
+                wb = cola.workspace_bytes(run.desc, (3 if outer else 1) + cola.WS_LEAN)
+            elif lean:
                 # less by a byte wherever that only costs the copies
                 wf -= 1 if d_in % 8 or (r % 8 and not recompute) else 0
                 wb -= 1 if d_in % 8 or (d_out % 8 and not outer) or (r % 8 and not recompute) else 0
@@ -67,9 +71,12 @@ def test_group():
     X, As, Bs, dYs = group_inputs(91, T, d_in, ranks, widths, "bf16")
     first = None
     for recompute in (False, True):
-        for lean in (0, 1):
+        for lean in (0, 1, 2):
             run = GroupRun(X, As, Bs, dYs, T, d_in, ranks, widths, "bf16", "silu", recompute)
-            wf, wb = (cola.group_workspace_bytes(run.desc, p) - lean for p in (0, 1))
+            if lean == 2:
+                wf, wb = (cola.group_workspace_bytes(run.desc, p + cola.WS_LEAN) for p in (0, 1))
+            else:
+                wf, wb = (cola.group_workspace_bytes(run.desc, p) - lean for p in (0, 1))
             cola.group_fwd(run.desc, run.X, run.A_all, run.B, run.Y, run.Z, run.H, run.ws, ws_bytes=wf)
             cola.group_bwd(run.desc, run.dY, run.X, run.Z, run.H, run.A_all, run.B, run.dX, run.dA, run.dB, run.ws,
                            ws_bytes=wb)
