@@ -374,9 +374,9 @@ int cola_block_bwd(const cola_block_desc* desc, const cola_block_weights* w, con
  * settings differ at most in the last bits of fp32 sums.
  *   COLA_OPT_STREAM_ONLY (default 0): 1 sends every bf16 product to the
  *     streaming kernel family (BM x 128 tiles) instead of the 256 x 256
- *     ping-pong family.
- *   COLA_OPT_WGRAD_PAIR (default 1): 0 launches the two weight gradients of a
- *     layer (and of a group) one by one instead of in one launch.
+ *     ping-pong family, the smaller tiles and the few-token kernel.
+ *   COLA_OPT_WGRAD_PAIR (default 1): 0 launches the weight gradients of a
+ *     layer or group one by one, and dX on its own, instead of together.
  *   COLA_OPT_FUSE_GATE (default 1): 0 keeps the decoder block's gated
  *     product (m = gate * up) and its backward in separate elementwise
  *     kernels instead of the epilogues of the up projection's Y = H B^T and
@@ -407,9 +407,11 @@ typedef enum {
     COLA_KC_FILL = 10,     /* zero fill (empty batches)                */
     COLA_KC_INFER_H = 11,  /* H = sigma(X A^T), Z not kept (inference) */
     COLA_KC_OUTER_GRAD = 12, /* dP = dY (.) sigma_out'(P), both-sigma variant */
-    COLA_KC_BWD_DADB = 13, /* dA and dB in one launch (bf16, both outputs
-                              wider than 128): the two token-split weight
-                              gradients share the launch and the split    */
+    COLA_KC_BWD_DADB = 13, /* weight gradients in one launch with one split
+                              (dA and dB of a layer; dA_all and the dB_p of
+                              a group, up to four at a time); in small
+                              layers with dX, which is then not in
+                              COLA_KC_BWD_DX                              */
     COLA_KC_ATTN_FWD = 14, /* block: causal attention forward             */
     COLA_KC_ATTN_BWD = 15, /* block: attention backward (dq, then dk dv)  */
     COLA_KC_NORM = 16,     /* block: RMSNorm forward (+ residual sum)     */

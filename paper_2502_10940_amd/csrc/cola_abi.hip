@@ -562,7 +562,8 @@ int wgrads(bool bf16, int64_t T, const Split& sp, const WProd* w, int n, hipStre
     bool joined = false;
     if (dx) {
         all[0] = dx->a;
-        joined = bf16 ? bf16_dxw_takes(all, n + 1) : f32_dxw_takes(all, n + 1);
+        joined = get_option(OPT_WGRAD_PAIR) == 1 &&
+                 (bf16 ? bf16_dxw_takes(all, n + 1) : f32_dxw_takes(all, n + 1));
         if (!joined) {
             const int st = launch_dx(bf16, *dx, s);
             if (st != COLA_OK) return st;
