@@ -1,11 +1,15 @@
-"""Build libcola.so (the gfx950 HIP kernels + C ABI) in-tree.
+"""Build libcola.so (the gfx950 HIP kernels + C ABI) in-tree, and the CPython
+extension with the argument checks of cola.py beside it.
 
 hipcc cross-compiles for gfx950 without a GPU.  Every source is compiled with
 packed-fp32 instructions disabled (the compiler would otherwise form
 v_pk_*_f32 from plain float code) and linked into
-``paper_2502_10940_amd/libcola.so``.
+``paper_2502_10940_amd/libcola.so``.  The extension is left out where g++, Python's
+headers or torch's are missing: libcola.so needs none of them, and cola.py then
+makes its checks in Python.
 """
 import os
+import shutil
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -20,8 +24,10 @@ ARGS = os.path.join(PKG, "_torch_args.so")          # CPython extension: checked
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["gemm_dispatch.hip", "gemm_stream.hip", "gemm_pp.hip", "gemm_mid.hip", "gemm_skinny.hip", "gemm_f32.hip", "cola_abi.hip",
-           "attention.hip", "block_ops.hip", "block_abi.hip"]
+CXX = "g++"
+
+SOURCES = ["gemm_dispatch.hip", "gemm_stream.hip", "gemm_pp.hip", "gemm_mid.hip", "gemm_skinny.hip", "gemm_f32.hip",
+           "cola_abi.hip", "attention.hip", "block_ops.hip", "block_abi.hip"]
 # Per-source extra flags.  The 256 x 256 kernel's epilogues run over 256
 # accumulators per lane: past the default limit the unroller stops and the
 # accumulators go to scratch memory.
@@ -50,15 +56,34 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
-def _build_args(verbose: bool) -> None:
-    """torch_args.cpp against this interpreter's torch, linked to libcola.so."""
+def _args_includes():
+    """Include paths of torch_args.cpp; a text that says what is missing if something is."""
     import sysconfig
-
-    import torch
-    from torch.utils import cpp_extension
-    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    if not shutil.which(CXX):
+        return f"no {CXX}"
+    try:
+        from torch.utils import cpp_extension
+    except ImportError as e:
+        return f"no torch ({e})"
     inc = [sysconfig.get_paths()["include"], *cpp_extension.include_paths()]
-    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden",
+    for h in ("Python.h", "torch/csrc/autograd/python_variable.h"):
+        if not any(os.path.exists(os.path.join(i, h)) for i in inc):
+            return f"no {h}"
+    return inc
+
+
+def _build_args(verbose: bool) -> bool:
+    """torch_args.cpp against this interpreter's torch, linked to libcola.so; False
+    (and no extension, not an old one either) where it cannot be built."""
+    inc = _args_includes()
+    if isinstance(inc, str):
+        print(f"_torch_args.so is not built ({inc}): cola.py makes its checks in Python", file=sys.stderr, flush=True)
+        if os.path.exists(ARGS):
+            os.remove(ARGS)
+        return False
+    import torch
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [CXX, "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *[f for i in inc for f in ("-isystem", i)], os.path.join(CSRC, "torch_args.cpp"), "-o", ARGS + ".tmp",
            "-L" + PKG, "-l:libcola.so", "-L" + tlib, "-ltorch_python", "-ltorch_cpu", "-lc10",
@@ -67,6 +92,7 @@ def _build_args(verbose: bool) -> None:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(ARGS + ".tmp", ARGS)
+    return True
 
 
 def build(verbose: bool = False) -> str:
