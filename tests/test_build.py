@@ -30,7 +30,8 @@ def test_no_torch(old_extension, monkeypatch, capsys):
 
 
 def test_no_headers(old_extension, monkeypatch, tmp_path, capsys):
-    monkeypatch.setattr(sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    real = sysconfig.get_paths
+    monkeypatch.setattr(sysconfig, "get_paths", lambda *a, **k: {**real(*a, **k), "include": str(tmp_path)})
     assert B._build_args(False) is False
     assert not old_extension.exists() and "no Python.h" in capsys.readouterr().err
 
