@@ -381,11 +381,16 @@ int cola_block_bwd(const cola_block_desc* desc, const cola_block_weights* w, con
  *     product (m = gate * up) and its backward in separate elementwise
  *     kernels instead of the epilogues of the up projection's Y = H B^T and
  *     the down projection's dX = dZ A (same roundings, so the same bits).
+ *   COLA_OPT_TILE (default 0, chosen by size): the output tile of every bf16
+ *     product that has a kernel for it (aligned operands, with 1 at least
+ *     128 x 128 outputs): 1 256 x 256, 2 128 x 128, 3 128 x 64, 4 64 x 64.
  * Workspace sizes depend on the settings: size the workspace after setting
  * them (a call whose workspace is too small returns COLA_ERR_WORKSPACE).
- * cola_set_option returns COLA_ERR_INVALID_ARG for an unknown option or a
- * value other than 0 or 1; cola_get_option returns the value, or -1. */
-typedef enum { COLA_OPT_STREAM_ONLY = 0, COLA_OPT_WGRAD_PAIR = 1, COLA_OPT_FUSE_GATE = 2 } cola_option;
+ * cola_set_option returns COLA_ERR_INVALID_ARG for an unknown option or
+ * value (0 or 1 but for COLA_OPT_TILE); cola_get_option returns the value, or -1. */
+typedef enum {
+    COLA_OPT_STREAM_ONLY = 0, COLA_OPT_WGRAD_PAIR = 1, COLA_OPT_FUSE_GATE = 2, COLA_OPT_TILE = 3
+} cola_option;
 int cola_set_option(int option, int value);
 int cola_get_option(int option);
 

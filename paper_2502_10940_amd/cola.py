@@ -120,7 +120,7 @@ EXPORTS = {
     "cola_get_option": ([ctypes.c_int], ctypes.c_int),
 }
 
-OPT_STREAM_ONLY, OPT_WGRAD_PAIR, OPT_FUSE_GATE = 0, 1, 2
+OPT_STREAM_ONLY, OPT_WGRAD_PAIR, OPT_FUSE_GATE, OPT_TILE = 0, 1, 2, 3
 
 
 def lib():
@@ -528,7 +528,7 @@ def kernel_name(kernel_class: int) -> str:
 
 
 def set_option(option: int, value: int):
-    """Process-wide tuning option (OPT_STREAM_ONLY, OPT_WGRAD_PAIR, OPT_FUSE_GATE) to 0 or 1."""
+    """Process-wide tuning option (OPT_STREAM_ONLY, OPT_WGRAD_PAIR, OPT_FUSE_GATE to 0 or 1, OPT_TILE to 0 .. 4)."""
     _check(lib().cola_set_option(int(option), int(value)))
 
 

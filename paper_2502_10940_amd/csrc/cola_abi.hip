@@ -246,6 +246,7 @@ Split plan_split_bf16(const WShape* w, int n, int64_t K, bool stream, size_t roo
             fits = fits && route_fits(route, w[i].M, w[i].N, maxs);
         }
         if (!fits) continue;
+        if (route == asked_route()) best_cost = -1.0;          // whatever the others cost
         for (int64_t s = 1; s <= maxs; ++s) {
             const int64_t chunk = (ktiles + s - 1) / s;
             const int64_t eff_s = (ktiles + chunk - 1) / chunk;
@@ -257,6 +258,7 @@ Split plan_split_bf16(const WShape* w, int n, int64_t K, bool stream, size_t roo
                 best = Split{(int)eff_s, chunk * BF16_BK, route};
             }
         }
+        if (route == asked_route()) break;
     }
     return best;
 }
@@ -812,7 +814,8 @@ extern "C" {
 int cola_abi_version(void) { return COLA_ABI_VERSION; }
 
 int cola_set_option(int option, int value) {
-    static_assert((int)COLA_OPT_STREAM_ONLY == (int)OPT_STREAM_ONLY && (int)COLA_OPT_WGRAD_PAIR == (int)OPT_WGRAD_PAIR,
+    static_assert((int)COLA_OPT_STREAM_ONLY == (int)OPT_STREAM_ONLY && (int)COLA_OPT_WGRAD_PAIR == (int)OPT_WGRAD_PAIR &&
+                      (int)COLA_OPT_FUSE_GATE == (int)OPT_FUSE_GATE && (int)COLA_OPT_TILE == (int)OPT_TILE,
                   "option numbering");
     return set_option(option, value) == 0 ? COLA_OK : COLA_ERR_INVALID_ARG;
 }

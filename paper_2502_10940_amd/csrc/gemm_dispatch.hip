@@ -24,6 +24,7 @@ namespace {
 std::atomic<int> g_force_stream{0};
 std::atomic<int> g_wgrad_pair{1};
 std::atomic<int> g_fuse_gate{1};
+std::atomic<int> g_tile{0};
 
 // Tile and modelled cost of a route.  Each round of up to 256 tiles costs
 // steps * (step + load * x) + store * x microseconds, x the share of the CUs
@@ -56,8 +57,9 @@ constexpr int kRoutes[] = {ROUTE_PP, ROUTE_MID_128x128, ROUTE_MID_128x64, ROUTE_
 }  // namespace
 
 int set_option(int option, int value) {
-    if (value != 0 && value != 1) return -1;
+    if (value < 0 || value > (option == OPT_TILE ? 4 : 1)) return -1;
     switch (option) {
+        case OPT_TILE: g_tile.store(value); return 0;
         case OPT_STREAM_ONLY: g_force_stream.store(value); return 0;
         case OPT_WGRAD_PAIR: g_wgrad_pair.store(value); return 0;
         case OPT_FUSE_GATE: g_fuse_gate.store(value); return 0;
@@ -70,6 +72,7 @@ int get_option(int option) {
         case OPT_STREAM_ONLY: return g_force_stream.load();
         case OPT_WGRAD_PAIR: return g_wgrad_pair.load();
         case OPT_FUSE_GATE: return g_fuse_gate.load();
+        case OPT_TILE: return g_tile.load();
         default: return -1;
     }
 }
@@ -93,8 +96,14 @@ bool route_fits(int route, int64_t M, int64_t N, int64_t splits) {
     return route_tiles(route, M, N) * splits < kMidMaxBlocks;
 }
 
+int asked_route() {
+    const int t = g_tile.load(std::memory_order_relaxed);
+    return t ? ROUTE_PP + t - 1 : ROUTE_AUTO;
+}
+
 int gemm_route(int64_t M, int64_t N, int64_t K) {
     if (g_force_stream.load(std::memory_order_relaxed)) return ROUTE_STREAM;
+    if (asked_route() != ROUTE_AUTO && route_fits(asked_route(), M, N, 1)) return asked_route();
     const int64_t steps = (K + BF16_BK - 1) / BF16_BK;
     int best = ROUTE_STREAM;
     double best_us = -1.0;
@@ -132,7 +141,9 @@ static bool operands_ok(const GemmArgs& a) {
 // with 64 x 64 tiles, 32 tokens of 7B q, k, v 18.6 against 34.  With a 64-row variant
 // of the kernel, 48 tokens of a 1B projection took 14.2 us against 13.5 with MID
 // tiles, of 7B 20.9 against 20.1, of 7B gate and up 32.9 against 24.8.
-bool skinny_rows(int64_t M) { return M <= kSkinnyRows && !g_force_stream.load(std::memory_order_relaxed); }
+bool skinny_rows(int64_t M) {
+    return M <= kSkinnyRows && !g_force_stream.load(std::memory_order_relaxed) && asked_route() == ROUTE_AUTO;
+}
 
 static bool skinny_takes(const GemmArgs& a) {
     return skinny_rows(a.M) && a.splits == 1 && a.p_layout == KMAJ && a.q_layout == KMAJ &&
@@ -224,11 +235,13 @@ hipError_t launch_gemm_bf16_batch(const GemmArgs* a, int n, hipStream_t s) {
             }
             fits = fits && (r != ROUTE_PP || tiles <= 256);
             const double us = route_us(r, tiles, steps, false);
-            if (fits && us < best_us) {
+            if (fits && (us < best_us || r == asked_route())) {
                 best_us = us;
                 best = r;
+                if (r == asked_route()) break;
             }
         }
+        if (asked_route() != ROUTE_AUTO && best != asked_route()) best = ROUTE_AUTO;
         if (best == ROUTE_PP) return launch_gemm_pp_batch(a, n, s);
         if (best != ROUTE_AUTO) return launch_route(a, n, best, s);
     }

@@ -73,8 +73,16 @@ hipError_t launch_gemm_bf16_wgrads(const GemmArgs* a, int n, hipStream_t s);
 bool bf16_dxw_takes(const GemmArgs* a, int n);
 hipError_t launch_gemm_bf16_dxw(const GemmArgs* a, int n, hipStream_t s);
 
-//   MID -- 128 x 128, 128 x 64 or 64 x 64 tiles, for outputs too small for PP
-// n products of one kind (same layouts and epilogue) in one launch.
+//   MID -- 128 x 128, 128 x 64 or 64 x 64 tiles, for outputs too small for PP;
+//   n products of one kind (same layouts and epilogue; n <= kMidBatch) in one
+//   launch, each of fewer than kMidMaxBlocks tiles.
+enum MidTile : int { MID_128x128 = 0, MID_128x64 = 1, MID_64x64 = 2 };
+constexpr int kMidBatch = 4;
+constexpr int64_t kMidMaxBlocks = int64_t(1) << 20;
+hipError_t launch_gemm_mid(const GemmArgs* a, int n, int tile, hipStream_t s);
+// dX = dZ A (a[0]) and the weight gradients a[1 ..] of a small layer in one grid
+// (MID_128x64 or MID_64x64).
+hipError_t launch_gemm_mid_dxw(const GemmArgs* a, int n, int tile, hipStream_t s);
 //   SKINNY -- at most kSkinnyRows token rows against weight rows (both
 //   k-contiguous, any alignment); n products of one kind and the same tokens in
 //   one launch (n <= kMidBatch).
@@ -82,13 +90,6 @@ constexpr int64_t kSkinnyRows = 32;
 hipError_t launch_gemm_skinny(const GemmArgs* a, int n, hipStream_t s);
 // Whether the forward products of M tokens run there.
 bool skinny_rows(int64_t M);
-// dX = dZ A (a[0]) and the weight gradients a[1 ..] of a small layer in one grid
-// (MID_128x64 or MID_64x64).
-hipError_t launch_gemm_mid_dxw(const GemmArgs* a, int n, int tile, hipStream_t s);
-enum MidTile : int { MID_128x128 = 0, MID_128x64 = 1, MID_64x64 = 2 };
-constexpr int kMidBatch = 4;
-constexpr int64_t kMidMaxBlocks = int64_t(1) << 20;
-hipError_t launch_gemm_mid(const GemmArgs* a, int n, int tile, hipStream_t s);
 
 // Kernel and tile of a bf16 product.
 enum Route : int {
@@ -100,6 +101,8 @@ enum Route : int {
 // model of gemm_dispatch.hip; the option OPT_STREAM_ONLY sends every product
 // to STREAM.
 int gemm_route(int64_t M, int64_t N, int64_t K);
+// The route that the option OPT_TILE asks for, where it fits; ROUTE_AUTO: none.
+int asked_route();
 // Modelled microseconds of `tiles` output tiles (splits included) of `steps`
 // 64-deep K tiles each on a PP or MID route; wgrad: both operands m-contiguous.
 double route_us(int route, int64_t tiles, int64_t steps, bool wgrad);
@@ -115,8 +118,8 @@ bool fused_epilogue_takes(const GemmArgs& a);
 
 // Process-wide tuning options (the public cola_set_option): the values of
 // cola_option in include/cola.h.  set_option returns 0, or -1 for an unknown
-// option or a value other than 0 / 1.
-enum Option : int { OPT_STREAM_ONLY = 0, OPT_WGRAD_PAIR = 1, OPT_FUSE_GATE = 2 };
+// option or value.
+enum Option : int { OPT_STREAM_ONLY = 0, OPT_WGRAD_PAIR = 1, OPT_FUSE_GATE = 2, OPT_TILE = 3 };
 int set_option(int option, int value);
 int get_option(int option);
 

@@ -39,6 +39,9 @@ CASES = [
     ("single_token_sequences", 5, 1, 128, 64, 1, 8, "silu"),
     # longer than the whole-sequence attention kernels take: the staged ones
     ("hd64_L300_staged_attention", 2, 300, 128, 96, 2, 16, "silu"),
+    # their chunks in work order, the masks of inner blocks left out, many stages
+    ("hd64_L2048_staged_attention", 1, 2048, 128, 96, 2, 16, "silu"),
+    ("hd128_L1111_staged_attention", 2, 1111, 256, 96, 2, 16, "silu"),
 ]
 
 
@@ -135,7 +138,8 @@ def test_block_cola_m_bitwise_equals_cola_and_is_deterministic(case):
 @pytest.mark.parametrize("case", [CASES[1], CASES[3]], ids=[CASES[1][0], CASES[3][0]])
 def test_block_gate_fusion_is_bitwise_the_elementwise_path(case, recompute):
     """The gated product m = gate * up and its backward in the GEMM epilogues
-    (the default where the ping-pong family takes the up and down products)
+    (the default for aligned operands; here on the 64 x 64 tiles that the sizes
+    take, in test_gpu_tiles.py on every tile)
     against the separate elementwise kernels (COLA_OPT_FUSE_GATE = 0): same
     roundings, so every output and saved tensor is bitwise the same."""
     name, n_seq, L, d, ffn, heads, r, act = case

@@ -2,9 +2,9 @@
 layers, grouped projections and the dense layer.
 
 Each of T, d_in, d_out and r is drawn from one of three bands -- below one
-32-wide MFMA tile, around the 128 / 256 tile edges (where the launcher
-switches between the streaming and the 256 x 256 families and where the
-ragged-edge paths start), and several tiles wide -- together with the storage
+32-wide MFMA tile, around the 128 / 256 tile edges (where the
+ragged-edge paths start; at these sizes the launcher takes the small tiles,
+test_gpu_tiles.py asks for the others), and several tiles wide -- together with the storage
 dtype, the activation, CoLA or CoLA-M, and tight or cache-line row pitches
 (tight pitches with odd widths take the guarded, unaligned paths).  Every
 draw runs forward and backward through the C ABI (and the inference

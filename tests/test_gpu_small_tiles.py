@@ -1,5 +1,5 @@
-"""Layers whose products run on the 128 x 128, 128 x 64 and 64 x 64 tiles:
-token counts and widths one below, at and one above tile edges, K of one
+"""Layers whose products run on the small tiles, as the library chooses them (64 x 64,
+for some 128 x 64; test_gpu_tiles.py asks for each tile): token counts and widths one below, at and one above tile edges, K of one
 partial tile up to more K tiles than LDS slots, and splits of the weight
 gradients, against the fp64 oracle (1e-2) and the reference that applies the
 path's bf16 storage policy (1e-3, as in the shape sweep)."""
