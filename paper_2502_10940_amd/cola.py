@@ -1,9 +1,12 @@
-"""Thin ctypes binding of libcola.so (include/cola.h).
+"""Thin binding of libcola.so (include/cola.h).
 
-Argument marshalling only: every step of the layer runs in the library's HIP
-kernels.  Tensors are passed as device pointers (``tensor.data_ptr()``), the
-stream is torch's current stream unless one is given.  There is no fallback:
-if ``libcola.so`` is missing or fails to load, every call raises.
+Argument checks and marshalling only: every step of the layer runs in the
+library's HIP kernels.  The layer and group calls go through a small CPython
+extension (csrc/torch_args.cpp) that checks and passes plain tensors; whatever it
+does not take, and every other call, goes through ctypes after the same checks
+here.  Tensors are passed as device pointers (``tensor.data_ptr()``), the stream
+is torch's current stream unless one is given.  There is no fallback for the
+kernels: if ``libcola.so`` is missing or fails to load, every call raises.
 """
 from __future__ import annotations
 

@@ -603,10 +603,10 @@ int guarded(F&& f) {
 }
 
 // The gated product of the decoder block's MLP fused into a GEMM epilogue
-// (ping-pong family only; the caller runs the elementwise kernels when
-// *fused comes back false): forward, the last projection of a group stores
-// u and m = g u, g being the group's first output; backward, the layer's
-// dX = dm GEMM stores dg = dm u and du = dm g instead.  g, u, m, dg and du
+// (256 x 256 and smaller tiles, not the streaming family; the caller runs the
+// elementwise kernels when *fused comes back false): forward, the last projection
+// of a group stores u and m = g u, g being the group's first output; backward, the
+// layer's dX = dm GEMM stores dg = dm u and du = dm g instead.  g, u, m, dg and du
 // share the row pitch ld.
 struct Gate {
     const void* g;

@@ -13,8 +13,10 @@
 //  * wide: 64 x 64 tiles, each wave a 32 x 32 quarter over all of K, operands
 //    shared through double-buffered LDS: half the traffic per flop.  Used once
 //    256 such tiles (or splits of them) exist.
-// A training step of T = 256, 512 -> 128 -> 512 takes 45 us, now bound by its five
+// A training step of T = 256, 512 -> 128 -> 512 takes 24 us, bound by its four
 // launches; a 64 x 64 VALU kernel took 213 (8 workgroups and 50 us for Z alone).
+// A value's last bits depend on the variant, and so on how many tokens share the
+// call: either order of the sum is within the fp32 rounding of the other.
 // LDS: k-contiguous operands as [row][32 k] with rows of 36 floats, m-contiguous
 // ones as [k][rows] with rows of rows + 8 floats: the 16-byte fragment reads of
 // the former and the two 4-byte half-wave rows (4 k apart) of the latter fall

@@ -1,5 +1,5 @@
 """A token's results do not depend on how many tokens share the call: every bf16
-forward kernel sums over k in increasing order, the one for at most 64 tokens as
+forward kernel sums over k in increasing order, the one for at most 32 tokens as
 the tiles of larger calls, so the rows of a small call equal, bit for bit, the
 same rows of a call with more tokens.  Token counts around the 16 / 32 / 64 row
 tiles, K from one partial K tile to several windows of four, any alignment."""

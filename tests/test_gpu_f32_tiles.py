@@ -1,5 +1,5 @@
 """fp32 layers around the edges of the fp32 kernel's tiles: K below, at and one
-past a 32-deep K tile and past the four K tiles its waves share, ragged rows and
+past a 32-deep K tile and past the eight K tiles its waves share, ragged rows and
 columns at any alignment, outputs on both sides of the switch from 32 x 32 to
 64 x 64 tiles (256 of the latter), and split weight gradients.  Against the fp64
 oracle: a dot product of n fp32 terms summed in any order is within n 2^-24 of
