@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 import torch
 
+import bench
 import oracle
 from paper_2502_10940_amd import cola
 from paper_2502_10940_amd import inputs as I
@@ -60,12 +61,15 @@ def _layer(case):
 
 
 def _kernels(fn):
-    """Names of the kernels that fn launches."""
+    """Names of the GEMM kernels that fn launches."""
     from torch.profiler import ProfilerActivity, profile
     with profile(activities=[ProfilerActivity.CUDA]) as p:
         fn()
         torch.cuda.synchronize()
-    return [e.name for e in p.events()]
+    names = [e.name for e in p.events() if "gemm_" in e.name]
+    if not names:
+        pytest.skip("the profiler reports no kernels here")
+    return names
 
 
 @pytest.mark.parametrize("name", TILES)
@@ -73,10 +77,38 @@ def test_the_tile_asked_for_runs(name):
     ins = I.layer_inputs(2000, 0, 264, 392, 136, 300, "bf16")
     with tile(TILES[name]):
         run = LayerRun(ins, 300, 264, 392, 136, "bf16", "silu", False)
-        names = [n for n in _kernels(lambda: (run.forward(), run.backward())) if "gemm_" in n]
-    assert names
+        names = _kernels(lambda: (run.forward(), run.backward()))
     part = "gemm_pp_" if name == "256x256" else "<" + name.replace("x", ", ") + ","
     assert all(part in n for n in names), names
+
+
+# (T, d_in, d_out, r): kernels of the forward's products and of dZ, dX as chosen by
+# size: 256 x 256 tiles on half the CUs stay unless another gains more than the
+# model's error (K of 512 or more), else the tile that the model prefers
+CHOSEN = [((32768, 1024, 1024, 256), {"fwd_z_sigma": "gemm_pp_", "bwd_dz": "gemm_pp_"}),
+          ((32768, 2048, 2048, 512), {"fwd_z_sigma": "gemm_pp_", "fwd_y": "gemm_pp_", "bwd_dz": "gemm_pp_",
+                                      "bwd_dx": "gemm_pp_"}),
+          ((8192, 1024, 2736, 256), {"bwd_dx": "gemm_mid_"}),
+          ((1024, 2048, 2048, 512), {"fwd_z_sigma": "gemm_mid_", "fwd_y": "gemm_mid_", "bwd_dz": "gemm_mid_"}),
+          ((33, 2048, 2048, 512), {"fwd_z_sigma": "gemm_mid_", "fwd_y": "gemm_mid_"}),
+          ((32, 2048, 2048, 512), {"fwd_z_sigma": "gemm_skinny_", "fwd_y": "gemm_skinny_"})]
+
+
+@pytest.mark.parametrize("case", CHOSEN, ids=["T%d-%dx%d-r%d" % c[0] for c in CHOSEN])
+def test_the_kernel_chosen_by_size(case):
+    (T, d_in, d_out, r), want = case
+    rows = lambda n, w: torch.zeros((n, w), dtype=torch.bfloat16, device="cuda:0")
+    d = cola.desc(T, d_in, d_out, r)
+    X, Y, Z, H, A, B = rows(T, d_in), rows(T, d_out), rows(T, r), rows(T, r), rows(r, d_in), rows(d_out, r)
+    dA, dB = (torch.empty(s, device="cuda:0") for s in ((r, d_in), (d_out, r)))
+    ws = torch.empty(max(1, cola.workspace_bytes(d, 1)), dtype=torch.uint8, device="cuda:0")
+
+    def step():
+        cola.fwd(d, X, A, B, Y, Z, H)
+        cola.bwd(d, Y, X, Z, H, A, B, rows(T, d_in), dA, dB, ws)
+    ran = {bench.gemm_class(n)[0]: n for n in _kernels(step)}
+    for step_name, kernel in want.items():
+        assert kernel in ran[step_name], (step_name, ran[step_name])
 
 
 @pytest.mark.parametrize("name", TILES)
